@@ -236,7 +236,7 @@ def kernel_rooflines(times, N, nocc, Ng, prec):
              "k_build_K_occ": (6 * Ng * Ng * nOP, PEAK["fp64"]),
              "k_build_K_occ_i8": (6 * Ng * Ng * occ_i8_columns(nocc) * I8_PRODUCTS, I8_PEAK),
              "k_gemm_tn_lds": (8 * Ng * P * P, PEAK[prec]), "k_gemm_tn_lp": (8 * Ng * P * P, PEAK[prec]),
-             "k_gemm2b_f64": (8 * Ng * P * P, PEAK["fp64"])}
+             "k_gemm_tn_f64": (8 * Ng * P * P, PEAK["fp64"])}
     out = {}
     for k, (n, t) in sorted(times.items(), key=lambda kv: -kv[1][1]):
         e = {"launches": n, "avg_ms": t / n * 1e3, "total_ms": t * 1e3, "share_of_step": None}

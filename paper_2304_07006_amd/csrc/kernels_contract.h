@@ -187,60 +187,6 @@ __global__ __launch_bounds__(256) void k_intermediates(const double* __restrict_
 }
 
 // --------------------------------------------------------------------------
-// Two-body assembly M[P][R] (+)= sum_c sum_{g<rows} C_c[g][P] D_c[g][R]
-// on FP64 MFMA.  Workgroup tile 128 x 128, four waves as 2 x 2, each wave
-// 64 x 64 (4 x 4 MFMA blocks).  Row block b of a wave maps logical row i to
-// P = P0 + 4 i + b (and likewise for columns), so every lane loads one
-// 32-byte vector of each operand per k-step.
-__global__ __launch_bounds__(256) void k_gemm2b_f64(const double* __restrict__ rho_rows,
-                                                    const double* __restrict__ K,
-                                                    const double* __restrict__ D, size_t dstride,
-                                                    int rows, int ldP, int n_t,
-                                                    double* __restrict__ M, int accumulate) {
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int pt = blockIdx.x % n_t, rt = blockIdx.x / n_t;
-    const int P0 = pt * 128 + 64 * (wave & 1);
-    const int R0 = rt * 128 + 64 * (wave >> 1);
-    const int kq = lane >> 4;
-    const int l16 = lane & 15;
-    const size_t kstride = (size_t)rows * ldP;
-    d4 acc[4][4];
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[b][c] = (d4){0.0, 0.0, 0.0, 0.0};
-    const d4 zero = {0.0, 0.0, 0.0, 0.0};
-    for (int comp = 0; comp < 4; ++comp) {
-        const double* A = (comp == 0 ? rho_rows : K + (size_t)(comp - 1) * kstride) + P0 + 4 * l16;
-        const double* B = D + (size_t)comp * dstride + R0 + 4 * l16;
-        int g = kq;
-        d4 a = g < rows ? *(const d4*)(A + (size_t)g * ldP) : zero;
-        d4 b = g < rows ? *(const d4*)(B + (size_t)g * ldP) : zero;
-        for (int kk = 0; kk < rows; kk += 4) {
-            const d4 ca = a, cb = b;
-            g += 4;
-            a = g < rows ? *(const d4*)(A + (size_t)g * ldP) : zero;
-            b = g < rows ? *(const d4*)(B + (size_t)g * ldP) : zero;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ca[i], cb[j], acc[i][j], 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int P = P0 + 4 * (lane >> 4) + 16 * v + i;   // logical row (l/16) + 4v
-            d4* out = (d4*)(M + (size_t)P * ldP + R0 + 4 * l16);
-            d4 val = {acc[i][0][v], acc[i][1][v], acc[i][2][v], acc[i][3][v]};
-            if (accumulate) val += *out;
-            *out = val;
-        }
-}
-
 // V2[p][q][r][s] = -(M2[P][R] + M1[R][P]).  Closed shell: M1 = M2 = M, and all
 // eight index symmetries hold bitwise because both terms are read for every
 // ordering.  Open shell, spins (s, t) of (pq, rs): M2 = M^t, M1 = M^s

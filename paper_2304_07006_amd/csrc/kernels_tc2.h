@@ -112,57 +112,6 @@ __global__ void k_rhog(const double* __restrict__ w, const double* __restrict__ 
     }
 }
 
-// M[i][j] (+)= sum_c sum_{g<rows} A_c[g][i] B_c[g][j] on FP64 MFMA, i < 128 n_it,
-// j < 128 n_jt.  Workgroup tile 128 x 128, four waves as 2 x 2 of 64 x 64;
-// row block b of a wave maps logical row i to I0 + 4 i + b (and likewise for
-// columns), so every lane loads one 32-byte vector of each operand per k-step.
-__global__ __launch_bounds__(256) void k_gemm_tn_f64(const double* __restrict__ A, size_t a_cstride, int lda,
-                                                     const double* __restrict__ B, size_t b_cstride, int ldb,
-                                                     int ncomp, int rows, int n_it, double* __restrict__ M,
-                                                     int ldm, int accumulate) {
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int it = blockIdx.x % n_it, jt = blockIdx.x / n_it;
-    const int I0 = it * 128 + 64 * (wave & 1);
-    const int J0 = jt * 128 + 64 * (wave >> 1);
-    const int kq = lane >> 4;
-    const int l16 = lane & 15;
-    d4 acc[4][4];
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[b][c] = (d4){0.0, 0.0, 0.0, 0.0};
-    const d4 zero = {0.0, 0.0, 0.0, 0.0};
-    for (int comp = 0; comp < ncomp; ++comp) {
-        const double* Ap = A + comp * a_cstride + I0 + 4 * l16;
-        const double* Bp = B + comp * b_cstride + J0 + 4 * l16;
-        int g = kq;
-        d4 a = g < rows ? *(const d4*)(Ap + (size_t)g * lda) : zero;
-        d4 b = g < rows ? *(const d4*)(Bp + (size_t)g * ldb) : zero;
-        for (int kk = 0; kk < rows; kk += 4) {
-            const d4 ca = a, cb = b;
-            g += 4;
-            a = g < rows ? *(const d4*)(Ap + (size_t)g * lda) : zero;
-            b = g < rows ? *(const d4*)(Bp + (size_t)g * ldb) : zero;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ca[i], cb[j], acc[i][j], 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int I = I0 + 4 * (lane >> 4) + 16 * v + i;
-            d4* out = (d4*)(M + (size_t)I * ldm + J0 + 4 * l16);
-            d4 val = {acc[i][0][v], acc[i][1][v], acc[i][2][v], acc[i][3][v]};
-            if (accumulate) val += *out;
-            *out = val;
-        }
-}
-
 // K2[p][q][r][s] = A[P][R] + B[p N + q][R] + B[r N + s][P], P = pair(p,q), R = pair(r,s),
 // with A taken as (A[P][R] + A[R][P]) / 2 (A is symmetric up to summation order)
 // and the two B terms added as one commutative pair, so that

@@ -19,6 +19,7 @@
 //   Kpart  [nsegK][3][kcap][ldL] f32  K-build segment partials of kcap rows (prec != FP64)
 //   CDlp   [8][NS][cap/8][ldL][8]     C and D of the chunk, k8-packed (prec != FP64)
 //   Mpart  [kMSegGroup][4][ldL][ldL] f32  two-body partials of a group of row segments
+//          (FP64: partials of a row-split product, at most kMpartF64Budget bytes)
 // and with XTC_WITH_BACKWARD in prec (the adjoint reuses M for Gbar):
 //   Kc [3][cap][ldP], Y [7][cap][ldP], T [cap][3][N][nocc], Wbar [cap][3],
 //   gpart [ceil(cap/32) * ngp/128][16], gacc [16], occw [N] f64, kidx [N],
@@ -51,6 +52,7 @@
 #include "kernels_build_k.h"
 #include "kernels_contract.h"
 #include "kernels_fc.h"
+#include "kernels_gemm_f64.h"
 #include "kernels_tc2.h"
 #include "kernels_lp.h"
 #include "kernels_bwd.h"
@@ -108,6 +110,11 @@ constexpr int kOccSegMax = 32;  // most segments of the FP64 occupied-block sum 
 constexpr size_t kKpartBudget = (size_t)16 << 30;  // bytes of K-build segment partials
 constexpr int kKpartQuant = 1024;                  // rows: 32 row tiles, one XCD's resident set
 constexpr int kMSegGroup = 2;                      // row segments per two-body GEMM launch
+// Row-split FP64 products: most row segments, and bytes of their partials (a
+// matrix too large for two partials has tiles enough to fill the chip).
+constexpr int kTnSplitMax = 64;
+constexpr size_t kMpartF64Budget = (size_t)192 << 20;
+constexpr int kCus = 256;                          // compute units of an MI355X (launch shapes only)
 
 struct Layout {
     int N, Ng, nocc, ldP, ngp, Npair, prec;
@@ -128,6 +135,7 @@ struct Layout {
     int kcap;            // rows of the K-build partial buffer: min(cap, kcap_max)
     size_t mslab;        // bytes of the two-body partials of one segM-row segment
     size_t cdw;          // packed operand elements per row and split (CDlp)
+    size_t mpart;        // bytes of the two-body partial buffer (Mpart)
     size_t S, D, Kpart, CDlp, Mpart, Kocc, Kc, Y, T, Wbar, gpart, KbL, Ftc, Rg, end;
 };
 
@@ -218,9 +226,10 @@ Layout make_layout(const xtc_problem* pb, int prec) {
     // packed operands: C and D of the two-body GEMM (8 components of ldL), or
     // w phi grad phi (3 of ldN) and K (3 of ldL) of the TC integrals
     L.cdw = std::max((size_t)8 * L.ldL, L.tc2 ? (size_t)3 * L.ldN + (size_t)3 * L.ldL : 0);
-    const size_t mslab = L.mslab;
+    L.mpart = lp ? (size_t)kMSegGroup * L.mslab
+                 : std::min(kMpartF64Budget, (size_t)kTnSplitMax * std::max(L.ldP, L.tc2 ? L.ldN : 0) * L.ldP * sizeof(double));
     L.chunk0 = off;
-    L.fixed = off + (size_t)kMSegGroup * mslab + (L.bwd ? gslab : 0) + 16 * kAlign;
+    L.fixed = off + L.mpart + (L.bwd ? gslab : 0) + 16 * kAlign;
     L.per_row = (size_t)L.nspin * (8 * sizeof(double) + (size_t)4 * L.ldP * sizeof(double));
     if (lp) L.per_row += (size_t)kOccSegMax * 3 * std::max(L.ldO, L.ldK8) * sizeof(double);
     if (lp) L.per_row += L.cdw * L.ns * L.es;
@@ -261,7 +270,7 @@ void place_chunk(Layout& L, size_t bytes) {
     L.D = off;       off = align_up(off + (size_t)L.nspin * 4 * cap * L.ldP * sizeof(double), kAlign);
     L.Kpart = off;   off = align_up(off + (lp ? (size_t)L.kcap * L.kpart_row : 0), kAlign);
     L.CDlp = off;    off = align_up(off + (lp ? L.cdw * L.ns * cap * L.es : 0), kAlign);
-    L.Mpart = off;   off = align_up(off + (size_t)kMSegGroup * L.mslab, kAlign);
+    L.Mpart = off;   off = align_up(off + L.mpart, kAlign);
     L.Kocc = off;    off = align_up(off + (lp ? (size_t)kOccSegMax * 3 * cap * std::max(L.ldO, L.ldK8) * sizeof(double) : 0),
                                     kAlign);
     const bool b = L.bwd;
@@ -698,6 +707,67 @@ xtc_status pack_kmajor_any(int form, const double* src, int nrows, int ld, void*
     return launched("pack_kmajor");
 }
 
+// How an FP64 product of imax x jmax outputs over `rows` rows of ncomp
+// components is laid out (k_gemm_tn_f64): the tile variant, the row segments
+// and their length, by the time of its MFMAs (64 cycles each, one workgroup
+// per CU and round) plus the sum over segments.  Large products take whole
+// rows in 128 x 128 tiles; a product with fewer tiles than CUs is cut along
+// the rows until the chip is full (N=8 on 2000 points is one tile: 1565 us in
+// one piece), and the 64 x 64 tiles, whose waves share the rows, waste less on
+// the padding of a small matrix.
+struct TnF64Plan {
+    int split, nseg, seg_rows;
+};
+TnF64Plan plan_tn_f64(int imax, int jmax, int ncomp, int rows, size_t max_parts) {
+    TnF64Plan best{1, 1, (int)align_up((size_t)rows, 16)};
+    double best_cycles = 1e300;
+    for (int split = 1; split <= 4; split += 3) {
+        const int tile = split == 1 ? 128 : 64;
+        const long tiles = (long)((imax + tile - 1) / tile) * ((jmax + tile - 1) / tile);
+        const int most = (int)std::min<size_t>({(size_t)kTnSplitMax, max_parts, (size_t)(rows + 31) / 32});
+        for (int want = 1; want <= std::max(1, most); ++want) {
+            const int seg = (int)align_up((size_t)((rows + want - 1) / want), 16);
+            const int nseg = (rows + seg - 1) / seg;
+            const double rounds = (double)((tiles * nseg + kCus - 1) / kCus);
+            double c = rounds * (ncomp * (double)((seg + 4 * split - 1) / (4 * split)) * 1024.0 * (split == 1 ? 1.0 : 1.1) +
+                                 (split == 1 ? 3000.0 : 6000.0));
+            if (nseg > 1) c += 10000.0 + 1e-3 * 8.0 * nseg * (double)imax * jmax;   // about 2.4 TB/s at 2.4 GHz
+            if (c < best_cycles) {
+                best_cycles = c;
+                best = {split, nseg, seg};
+            }
+        }
+    }
+    return best;
+}
+
+// M (+)= sum_c A_c^T B_c over `rows` rows in FP64 for outputs [0, imax) x
+// [0, jmax) of M (leading dimension ldm, padded to whole 128 x 128 tiles).
+xtc_status gemm_tn_f64(const Layout& L, const TnOperand& A, const TnOperand& B, int ncomp, int rows, int imax, int jmax,
+                       double* M, int ldm, int accumulate, void* ws, hipStream_t st) {
+    const size_t ld_rows = align_up((size_t)imax, 128);
+    const size_t msize = ld_rows * ldm;
+    const TnF64Plan p = plan_tn_f64(imax, jmax, ncomp, rows, L.mpart / (msize * sizeof(double)));
+    const bool parts = p.nseg > 1;
+    double* out = parts ? at<double>(ws, L.Mpart) : M;
+    const int tile = p.split == 1 ? 128 : 64;
+    const int n_it = (imax + tile - 1) / tile, n_jt = (jmax + tile - 1) / tile;
+    const dim3 grid(n_it * n_jt, p.nseg);
+    if (p.split == 1)
+        hipLaunchKernelGGL(k_gemm_tn_f64<1>, grid, dim3(256), 0, st, A, B, ncomp, rows, n_it, p.seg_rows, out, ldm,
+                           msize, parts ? 0 : accumulate);
+    else
+        hipLaunchKernelGGL(k_gemm_tn_f64<4>, grid, dim3(256), 0, st, A, B, ncomp, rows, n_it, p.seg_rows, out, ldm,
+                           msize, parts ? 0 : accumulate);
+    xtc_status s = launched("gemm_tn_f64");
+    if (s != XTC_OK || !parts) return s;
+    const int jmax4 = (int)align_up((size_t)jmax, 4);
+    const size_t n4 = (size_t)imax * (jmax4 / 4);
+    hipLaunchKernelGGL(k_reduce_M_f64, dim3((unsigned)std::min<size_t>((n4 + 255) / 256, 16384)), dim3(256), 0, st, out,
+                       p.nseg, msize, ldm, imax, jmax4, M, accumulate);
+    return launched("reduce_M_f64");
+}
+
 // The adjoint's X Gbar products in the split-BF16 3-product form (k_nt_bf16,
 // FP32 accumulation over all pairs): Y_c (+)= X_c Gm^T for NC consecutive
 // components sharing one right operand (X k-packed splits [NC][2][ldP/8][rows][8]
@@ -844,14 +914,15 @@ xtc_status xtc_contract_2body(const xtc_problem* pb, const double* K, int32_t g0
     if (L.form != 0) {
         if ((s = gemm2b_lp(L, K, g0, rows, (flags & XTC_RESET) ? 0 : 1, ws, st)) != XTC_OK) return s;
     } else {
-        const int n_t = L.ldP / 128;
         const double* rho_rows = at<double>(ws, L.rho) + (size_t)g0 * L.ldP;
         const size_t dstride = (size_t)L.cap * L.ldP;
+        const TnOperand C{rho_rows, K, (size_t)rows * L.ldP, L.ldP};
         for (int sp = 0; sp < L.nspin; ++sp) {
-            hipLaunchKernelGGL(k_gemm2b_f64, dim3(n_t * n_t), dim3(256), 0, st, rho_rows, K,
-                               at<double>(ws, L.D) + (size_t)sp * 4 * dstride, dstride, rows, L.ldP, n_t,
-                               at<double>(ws, L.M) + (size_t)sp * L.ldP * L.ldP, (flags & XTC_RESET) ? 0 : 1);
-            if ((s = launched("gemm_2body")) != XTC_OK) return s;
+            const double* D = at<double>(ws, L.D) + (size_t)sp * 4 * dstride;
+            if ((s = gemm_tn_f64(L, C, TnOperand{D, D + dstride, dstride, L.ldP}, 4, rows, L.Npair, L.Npair,
+                                 at<double>(ws, L.M) + (size_t)sp * L.ldP * L.ldP, L.ldP,
+                                 (flags & XTC_RESET) ? 0 : 1, ws, st)) != XTC_OK)
+                return s;
         }
     }
     if (flags & XTC_FINALIZE) {
@@ -1222,13 +1293,13 @@ xtc_status xtc_tc_2body(const xtc_problem* pb, const xtc_jastrow* jas, const dou
     double* Atc = at<double>(ws, L.Atc);
     double* Btc = at<double>(ws, L.Btc);
     if (L.form == 0) {
-        const int nP = L.ldP / 128, nN = L.ldN / 128;
-        hipLaunchKernelGGL(k_gemm_tn_f64, dim3(nP * nP), dim3(256), 0, st, rho_rows, (size_t)0, L.ldP, F, (size_t)0,
-                           L.ldP, 1, rows, nP, Atc, L.ldP, acc);
-        if ((s = launched("gemm_tc_A")) != XTC_OK) return s;
-        hipLaunchKernelGGL(k_gemm_tn_f64, dim3(nN * nP), dim3(256), 0, st, Rg, xs, L.ldN, K, (size_t)rows * L.ldP,
-                           L.ldP, 3, rows, nN, Btc, L.ldP, acc);
-        if ((s = launched("gemm_tc_B")) != XTC_OK) return s;
+        if ((s = gemm_tn_f64(L, TnOperand{rho_rows, rho_rows, 0, L.ldP}, TnOperand{F, F, 0, L.ldP}, 1, rows, L.Npair,
+                             L.Npair, Atc, L.ldP, acc, ws, st)) != XTC_OK)
+            return s;
+        const size_t ks = (size_t)rows * L.ldP;
+        if ((s = gemm_tn_f64(L, TnOperand{Rg, Rg + xs, xs, L.ldN}, TnOperand{K, K + ks, ks, L.ldP}, 3, rows, L.N * L.N,
+                             L.Npair, Btc, L.ldP, acc, ws, st)) != XTC_OK)
+            return s;
     } else {
         // reduced forms: both contractions as split products over the chunk rows,
         // FP32 partials per segM rows, FP64 reduction into the accumulators
