@@ -43,8 +43,8 @@ def kernel_sources_hash():
     profiles/ are only reported while it matches)."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("xtc_device.h", "kernels_build_k.h", "kernels_lp.h", "kernels_prepare.h", "kernels_occ_i8.h",
-              "occ_i8.hip", "xtc_api.hip"):
+    for f in ("xtc_device.h", "build_f64.h", "build_f64.hip", "kernels_build_f64.h", "kernels_gemm_f64.h",
+              "kernels_lp.h", "kernels_prepare.h", "kernels_occ_i8.h", "occ_i8.hip", "xtc_api.hip"):
         with open(os.path.join(ROOT, "paper_2304_07006_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -63,7 +63,8 @@ def traffic_record(prec, workload, chunk):
     return e
 
 
-KBUILD_KERNELS = ("k_build_K_lp", "k_reduce_K", "k_build_K_occ_i8", "k_build_K_occ", "k_reduce_occ", "k_build_K_f64")
+KBUILD_KERNELS = ("k_build_K_lp", "k_reduce_K", "k_build_K_occ_i8", "k_build_K_occ", "k_reduce_occ", "k_build_K_f64",
+                  "k_reduce_K_f64")
 
 
 def traffic_from(fetch_dir, write_dir, workload, prec, chunk, path=None):
@@ -232,7 +233,7 @@ def kernel_rooflines(times, N, nocc, Ng, prec):
     and its useful rate is given beside it as an FP64-class rate."""
     P = N * (N + 1) // 2
     nOP = nocc * (nocc + 1) // 2
-    table = {"k_build_K_lp": (6 * Ng * Ng * P, PEAK[prec]), "k_build_K_f64": (6 * Ng * Ng * P, PEAK["fp64"]),
+    table = {"k_build_K_lp": (6 * Ng * Ng * P, PEAK[prec]), "k_build_K_f64": (6 * Ng * Ng * (P if prec == "fp64" else nOP), PEAK["fp64"]),
              "k_build_K_occ": (6 * Ng * Ng * nOP, PEAK["fp64"]),
              "k_build_K_occ_i8": (6 * Ng * Ng * occ_i8_columns(nocc) * I8_PRODUCTS, I8_PEAK),
              "k_gemm_tn_lds": (8 * Ng * P * P, PEAK[prec]), "k_gemm_tn_lp": (8 * Ng * P * P, PEAK[prec]),

@@ -19,10 +19,13 @@ FLAGS = [
 # Translation units and their own flags.  xtc_api.hip: MFMA accumulators in
 # ordinary VGPRs (no per-iteration AGPR copies).  occ_i8.hip: the integer
 # occupied block keeps 216 accumulator registers per lane, beyond the 256
-# ordinary VGPRs, so its accumulators stay in the AGPRs.
+# ordinary VGPRs, so its accumulators stay in the AGPRs.  build_f64.hip: the
+# same for the FP64 K build's 192 (in the VGPR form it copied them between the
+# two files, and a copy is time the FP64 matrix cores stand still).
 UNITS = [
     (os.path.join(HERE, "csrc", "xtc_api.hip"), ["-mllvm", "-amdgpu-mfma-vgpr-form"]),
     (os.path.join(HERE, "csrc", "occ_i8.hip"), []),
+    (os.path.join(HERE, "csrc", "build_f64.hip"), []),
 ]
 
 

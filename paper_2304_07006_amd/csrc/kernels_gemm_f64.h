@@ -156,4 +156,23 @@ __global__ void k_reduce_M_f64(const double* __restrict__ part, int nseg, size_t
     }
 }
 
+// K[x][r][P] = sum_s part[s][x][r][P] (fixed order) for P < ldo (a multiple
+// of 4), 0 for ldo <= P < ldP.
+__global__ void k_reduce_K_f64(const double* __restrict__ part, int nseg, int rows, int ldo, int ldP,
+                               double* __restrict__ K) {
+    const size_t n4 = (size_t)3 * rows * (ldP / 4);
+    const size_t stride = (size_t)3 * rows * ldo;
+    for (size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x; t < n4; t += (size_t)gridDim.x * blockDim.x) {
+        const int P = (int)(t % (ldP / 4)) * 4;
+        const size_t xr = t / (ldP / 4);
+        d4 s = {0.0, 0.0, 0.0, 0.0};
+        if (P < ldo) {
+            const double* p = part + xr * ldo + P;
+#pragma unroll 4
+            for (int q = 0; q < nseg; ++q) s += *(const d4*)(p + q * stride);
+        }
+        *(d4*)(K + xr * ldP + P) = s;
+    }
+}
+
 }  // namespace xtc

@@ -179,7 +179,7 @@ constexpr int kI8RawBufferWord3 = 0x00020000;
 // digits against the staged rho tiles: 21 CT MFMAs per k-step.  Each stage
 // block (stages[kb][group], OccI8Stage) is copied by direct 16-byte
 // buffer-to-LDS loads one k-step ahead into the other of two statically named
-// buffers, as in k_build_K_occ.  part[seg][x][r][ldK] = the FP64 value of the
+// buffers.  part[seg][x][r][ldK] = the FP64 value of the
 // segment's sum, for pair columns 16 (blockIdx.z CT + ct) + l % 16.
 template <int KIND, int CT>
 __global__ __launch_bounds__(256, 1) void k_build_K_occ_i8(const d4* __restrict__ pos, const char* __restrict__ stages,

@@ -6,7 +6,6 @@
 //   K2[pq][rs] = A[P][R] + B[pq][R] + B[rs][P],
 //   A = sum_g rho^T F (packed pairs),  B = sum_g sum_x rhog_x^T K_x.
 #pragma once
-#include "kernels_build_k.h"
 #include "xtc_device.h"
 
 namespace xtc {
@@ -38,6 +37,9 @@ __device__ __forceinline__ double scalar_S(double r2, const JasDev& J) {
     const double v = upp + 2.0 * up * s + up * up;
     return r2 > 0.0 ? v : 0.0;
 }
+
+constexpr int kKRowsPerWave = 16;
+constexpr int kKRows = 4 * kKRowsPerWave;         // 64 grid rows per workgroup
 
 // F[g - g0][P] = sum_{g'} S(g, g') rho[g'][P] for the rows of the chunk
 // (FP64 MFMA).  Workgroup 64 rows x 16 NBLK columns; each wave owns 16 rows

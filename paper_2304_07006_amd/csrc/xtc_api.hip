@@ -6,8 +6,7 @@
 //   pos    [ngp] x 4 doubles          grid positions (x, y, z, 0)
 //   rho    [ngp][ldP] doubles         weighted pair densities, zero padded
 //   rho_lp [NS][ngp/8][ldL][8]        reduced-precision rho (k8-packed), prec != FP64
-//   rho_occ[ldO/tw][ngp][tw], colmap[ldO]  FP64 rho of the occupied-occupied pairs
-//                                     (column tiles of tw = 16 occNB pairs)
+//   rho_occ[ngp][ldO], colmap[ldO]    FP64 rho of the occupied-occupied pairs
 //   stg, amax                         digit stage blocks and per-pair largest |rho|
 //                                     of the integer occupied block (occ_i8.h)
 //   M      [ldP][ldP] doubles         FP64 accumulator of the two-body term
@@ -16,7 +15,8 @@
 //   E      [kESplit][N][N] doubles    per-split partials (one-body, exchange)
 //   S      [cap][8] doubles           per-point scalars of the current chunk
 //   D      [4][cap][ldP] doubles      A, Bx, By, Bz of the current chunk
-//   Kpart  [nsegK][3][kcap][ldL] f32  K-build segment partials of kcap rows (prec != FP64)
+//   Kpart  [nsegK][3][kcap][ldL] f32  K-build segment partials of kcap rows (prec != FP64; FP64: FP64 partials
+//          of a K build split over g', at most kKpartF64Budget bytes)
 //   CDlp   [8][NS][cap/8][ldL][8]     C and D of the chunk, k8-packed (prec != FP64)
 //   Mpart  [kMSegGroup][4][ldL][ldL] f32  two-body partials of a group of row segments
 //          (FP64: partials of a row-split product, at most kMpartF64Budget bytes)
@@ -49,7 +49,7 @@
 #include <vector>
 
 #include "../../include/xtc.h"
-#include "kernels_build_k.h"
+#include "build_f64.h"
 #include "kernels_contract.h"
 #include "kernels_fc.h"
 #include "kernels_gemm_f64.h"
@@ -114,11 +114,16 @@ constexpr int kMSegGroup = 2;                      // row segments per two-body 
 // matrix too large for two partials has tiles enough to fill the chip).
 constexpr int kTnSplitMax = 64;
 constexpr size_t kMpartF64Budget = (size_t)192 << 20;
+// FP64 K build of a grid too small to fill the chip: most segments of the sum
+// over g', and bytes of their partials.
+constexpr int kKSplitMax = 16;
+constexpr size_t kKpartF64Budget = (size_t)192 << 20;
 constexpr int kCus = 256;                          // compute units of an MI355X (launch shapes only)
 
 struct Layout {
     int N, Ng, nocc, ldP, ngp, Npair, prec;
-    int form, ns, es, ldL, ldO, nOP, occNB, nsegK, nspin, ldN, segK, segM;
+    int form, ns, es, ldL, ldO, nOP, nsegK, nspin, ldN, segK, segM;
+    KF64Plan occ64;      // column tiling of the FP64 occupied block (ldO columns)
     int nY;              // adjoint Y slots: Cbar (3), then Abar, Bbar (4) per spin channel
     OccI8Plan i8;        // column tiling of the integer occupied block
     bool i8ok;           // one column group and the grid fits its int32 segments (else the FP64 block serves)
@@ -144,24 +149,6 @@ int form_of(int prec) {
     return prec == XTC_FP32 ? 1 : prec == XTC_BF16X3 ? 3 : prec == XTC_BF16X6 ? 6 : 0;
 }
 
-
-// 16-column blocks per wave of the FP64 occupied-block kernel, in [1, 9]:
-// the count minimising padded columns x (1 + 1/(2 nb)), i.e. the MFMA work
-// plus the FP64 generation of the d tile, which each wave repeats for its
-// nb blocks.
-int occ_blocks(int nOP) {
-    int best = 1;
-    double best_cost = 1e300;
-    for (int nb = 1; nb <= 9; ++nb) {
-        const double cost = (double)align_up((size_t)nOP, (size_t)16 * nb) * (1.0 + 0.5 / nb);
-        if (cost < best_cost) {
-            best = nb;
-            best_cost = cost;
-        }
-    }
-    return best;
-}
-
 Layout make_layout(const xtc_problem* pb, int prec) {
     Layout L{};
     L.N = pb->N;
@@ -177,8 +164,8 @@ Layout make_layout(const xtc_problem* pb, int prec) {
     L.es = L.form == 1 ? 4 : 2;
     L.ldL = (int)align_up((size_t)L.ldP, kLpCols);
     L.nOP = pb->nocc * (pb->nocc + 1) / 2;
-    L.occNB = occ_blocks(L.nOP);
-    L.ldO = (int)align_up((size_t)L.nOP, (size_t)16 * L.occNB);
+    L.occ64 = kf64_columns(L.nOP, 1 << 30);
+    L.ldO = L.occ64.ncol;
     L.i8 = occ_i8_plan(L.nOP);
     // the integer block serves one column group (at most 144 occupied pairs):
     // with two, each of them regenerates d's digits, and at N=160 with 20
@@ -233,8 +220,9 @@ Layout make_layout(const xtc_problem* pb, int prec) {
     L.per_row = (size_t)L.nspin * (8 * sizeof(double) + (size_t)4 * L.ldP * sizeof(double));
     if (lp) L.per_row += (size_t)kOccSegMax * 3 * std::max(L.ldO, L.ldK8) * sizeof(double);
     if (lp) L.per_row += L.cdw * L.ns * L.es;
-    L.kpart_row = lp ? (size_t)L.nsegK * 3 * L.ldL * sizeof(float) : 0;
-    L.kcap_max = lp ? (int)std::max<size_t>(kKpartQuant, kKpartBudget / L.kpart_row / kKpartQuant * kKpartQuant) : 0;
+    L.kpart_row = lp ? (size_t)L.nsegK * 3 * L.ldL * sizeof(float) : (size_t)kKSplitMax * 3 * L.ldP * sizeof(double);
+    L.kcap_max = lp ? (int)std::max<size_t>(kKpartQuant, kKpartBudget / L.kpart_row / kKpartQuant * kKpartQuant)
+                    : (int)(kKpartF64Budget / L.kpart_row);
     if (L.tc2) L.per_row += (size_t)L.ldP * sizeof(double) + (size_t)3 * L.ldN * sizeof(double);
     if (L.bwd)
         L.per_row += (size_t)(3 + L.nY) * L.ldP * sizeof(double) + (size_t)3 * L.N * L.nocc * sizeof(double) +
@@ -268,7 +256,7 @@ void place_chunk(Layout& L, size_t bytes) {
     size_t off = L.chunk0;
     L.S = off;       off = align_up(off + (size_t)L.nspin * cap * 8 * sizeof(double), kAlign);
     L.D = off;       off = align_up(off + (size_t)L.nspin * 4 * cap * L.ldP * sizeof(double), kAlign);
-    L.Kpart = off;   off = align_up(off + (lp ? (size_t)L.kcap * L.kpart_row : 0), kAlign);
+    L.Kpart = off;   off = align_up(off + (size_t)L.kcap * L.kpart_row, kAlign);
     L.CDlp = off;    off = align_up(off + (lp ? L.cdw * L.ns * cap * L.es : 0), kAlign);
     L.Mpart = off;   off = align_up(off + L.mpart, kAlign);
     L.Kocc = off;    off = align_up(off + (lp ? (size_t)kOccSegMax * 3 * cap * std::max(L.ldO, L.ldK8) * sizeof(double) : 0),
@@ -477,48 +465,6 @@ void launch_build_lp(const Layout& L, int g0, int rows, const JasDev& J, void* w
                        L.segK, J, at<float>(ws, L.Kpart), L.kcap, L.ldP, n_ct, L.nsegK);
 }
 
-// Segments of the g' sum of the FP64 occupied block for a grid of `tiles`
-// workgroups per segment: the fewest, from 4, whose last round of workgroups
-// keeps at least 90% of the `slots` resident workgroups busy (equal-work
-// workgroups finish in rounds, and a short last round idles the rest of the
-// chip), else the best found.
-int occ_segments(long tiles, long slots) { return balanced_segments(tiles, slots, 4, kOccSegMax); }
-
-// Launch the FP64 occupied block with the segment count from the kernel's
-// occupancy on the current device; returns that count (0 on a HIP error).
-template <int KIND, int NB>
-int launch_build_occ_nb(const Layout& L, int g0, int rows, int n_rt, const JasDev& J, void* ws, hipStream_t st) {
-    int dev = 0, cus = 0, per_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)k_build_K_occ<KIND, NB>, 256, 0) !=
-            hipSuccess)
-        return 0;
-    const long tiles = (long)n_rt * (L.ldO / (16 * NB));
-    const int want = occ_segments(tiles, (long)std::max(cus, 1) * std::max(per_cu, 1));
-    const int seg_len = (int)align_up((size_t)((L.ngp + want - 1) / want), 32);   // whole 32-point stages
-    const int nseg = (L.ngp + seg_len - 1) / seg_len;   // every segment starts inside the grid
-    const dim3 grid((unsigned)tiles, nseg);
-    hipLaunchKernelGGL((k_build_K_occ<KIND, NB>), grid, dim3(256), 0, st, at<d4>(ws, L.pos), at<double>(ws, L.rho_occ),
-                       L.ldO, L.ngp, g0, rows, n_rt, J, at<double>(ws, L.Kocc), seg_len);
-    return nseg;
-}
-
-template <int KIND>
-int launch_build_occ(const Layout& L, int g0, int rows, int n_rt, const JasDev& J, void* ws, hipStream_t st) {
-    switch (L.occNB) {
-        case 1: return launch_build_occ_nb<KIND, 1>(L, g0, rows, n_rt, J, ws, st);
-        case 2: return launch_build_occ_nb<KIND, 2>(L, g0, rows, n_rt, J, ws, st);
-        case 3: return launch_build_occ_nb<KIND, 3>(L, g0, rows, n_rt, J, ws, st);
-        case 4: return launch_build_occ_nb<KIND, 4>(L, g0, rows, n_rt, J, ws, st);
-        case 5: return launch_build_occ_nb<KIND, 5>(L, g0, rows, n_rt, J, ws, st);
-        case 6: return launch_build_occ_nb<KIND, 6>(L, g0, rows, n_rt, J, ws, st);
-        case 7: return launch_build_occ_nb<KIND, 7>(L, g0, rows, n_rt, J, ws, st);
-        case 8: return launch_build_occ_nb<KIND, 8>(L, g0, rows, n_rt, J, ws, st);
-        default: return launch_build_occ_nb<KIND, 9>(L, g0, rows, n_rt, J, ws, st);
-    }
-}
-
 // The split K build of rows [g0, g0 + rows) (nc = 3: K, or nc = 1: F of the
 // TC integrals) in equal pieces (multiples of 32 rows) of at most kcap rows:
 // segment partials, then their FP64 sum into out[c][r][P] (component stride
@@ -578,11 +524,11 @@ xtc_status build_K_lp(const Layout& L, int g0, int rows, const JasDev& J, double
         }
         if ((s = launched("build_K_occ_i8")) != XTC_OK) return s;
     } else {
-        const int n_rt = (rows + kKRows - 1) / kKRows;
-        nseg = J.kind == 0 ? launch_build_occ<0>(L, g0, rows, n_rt, J, ws, st)
-                           : launch_build_occ<1>(L, g0, rows, n_rt, J, ws, st);
-        if (nseg == 0) return fail(XTC_E_HIP, "occupancy query of the occupied-block kernel failed");
-        if ((s = launched("build_K_occ_f64")) != XTC_OK) return s;
+        const KF64Plan p = kf64_segments(L.occ64, rows, L.ngp, kOccSegMax);
+        nseg = p.nseg;
+        const hipError_t e = kf64_build(at<d4>(ws, L.pos), at<double>(ws, L.rho_occ), L.ldO, L.ngp, g0, rows, J, p,
+                                        part, L.ldO, st);
+        if (e != hipSuccess) return fail(XTC_E_HIP, "build_K_occ_f64: %s", hipGetErrorString(e));
     }
     const size_t nel = (size_t)3 * rows * L.nOP;
     hipLaunchKernelGGL(k_reduce_occ, dim3((unsigned)std::min<size_t>((nel + 255) / 256, 8192)), dim3(256), 0, st, part,
@@ -784,19 +730,28 @@ xtc_status xg_group(const __bf16* X, size_t a_comp, size_t a_split, int rows, co
     return launched("gemm_xg_bf16");
 }
 
+// The FP64 K build: in one piece, or split over g' where the grid is too small
+// to fill the chip, the FP64 partials then summed into K.
+xtc_status build_K_f64(const Layout& L, const JasDev& J, int g0, int rows, double* K, void* ws, hipStream_t st) {
+    // segments whose partials fit the buffer: kcap rows of kKSplitMax segments of ldP columns
+    const size_t fit = (size_t)L.kcap * kKSplitMax / rows;
+    const KF64Plan p = kf64_plan(L.Npair, L.ldP, rows, L.ngp, (int)std::min<size_t>(fit, kKSplitMax));
+    const bool parts = p.nseg > 1;
+    double* out = parts ? at<double>(ws, L.Kpart) : K;
+    const hipError_t e = kf64_build(at<d4>(ws, L.pos), at<double>(ws, L.rho), L.ldP, L.ngp, g0, rows, J, p, out,
+                                    parts ? p.ncol : L.ldP, st);
+    if (e != hipSuccess) return fail(XTC_E_HIP, "build_K: %s", hipGetErrorString(e));
+    if (!parts) return XTC_OK;
+    const size_t n4 = (size_t)3 * rows * (L.ldP / 4);
+    hipLaunchKernelGGL(k_reduce_K_f64, dim3((unsigned)std::min<size_t>((n4 + 255) / 256, 16384)), dim3(256), 0, st, out,
+                       p.nseg, rows, p.ncol, L.ldP, K);
+    return launched("reduce_K_f64");
+}
+
 xtc_status build_K_any(const Layout& L, const JasDev& J, int g0, int rows, double* K, int occ, void* ws,
                        hipStream_t st) {
     if (L.form != 0) return build_K_lp(L, g0, rows, J, K, occ, ws, st);
-    const int n_rt = (rows + kKRows - 1) / kKRows;
-    const int n_ct = L.ldP / 128;
-    const dim3 grid(n_rt * n_ct);
-    if (J.kind == 0)
-        hipLaunchKernelGGL(k_build_K_f64<0>, grid, dim3(256), 0, st, at<d4>(ws, L.pos), at<double>(ws, L.rho),
-                           L.ldP, L.ngp, g0, rows, n_rt, J, K);
-    else
-        hipLaunchKernelGGL(k_build_K_f64<1>, grid, dim3(256), 0, st, at<d4>(ws, L.pos), at<double>(ws, L.rho),
-                           L.ldP, L.ngp, g0, rows, n_rt, J, K);
-    return launched("build_K");
+    return build_K_f64(L, J, g0, rows, K, ws, st);
 }
 
 }  // namespace
@@ -844,11 +799,11 @@ xtc_status xtc_prepare(const xtc_problem* pb, int32_t prec, int32_t chunk_rows, 
                            at<int>(ws, L.colmap), L.ldO);
         if ((s = launched("occ_pairs")) != XTC_OK) return s;
         hipLaunchKernelGGL(k_gather_occ, dim3(4096), dim3(256), 0, st, at<double>(ws, L.rho), L.ldP, L.ngp,
-                           at<int>(ws, L.colmap), L.ldO, 16 * L.occNB, at<double>(ws, L.rho_occ));
+                           at<int>(ws, L.colmap), L.ldO, L.ldO, at<double>(ws, L.rho_occ));
         if ((s = launched("gather_occ")) != XTC_OK) return s;
         if (L.i8ok) {
             if ((s = fill(at<double>(ws, L.amax), (size_t)L.ldK8, st)) != XTC_OK) return s;
-            if (occ_i8_prepare(at<double>(ws, L.rho_occ), at<d4>(ws, L.pos), L.ngp, 16 * L.occNB, L.nOP, L.i8,
+            if (occ_i8_prepare(at<double>(ws, L.rho_occ), at<d4>(ws, L.pos), L.ngp, L.ldO, L.nOP, L.i8,
                                at<unsigned long long>(ws, L.amax), at<void>(ws, L.stg), st) != hipSuccess)
                 return fail(XTC_E_HIP, "occ_i8_prepare: %s", hipGetErrorString(hipGetLastError()));
         }
