@@ -86,7 +86,7 @@ __global__ __launch_bounds__(256, 1) void k_build_K_f64(const d4* __restrict__ p
     };
     auto gen = [&](int j, ATile& W) {
         const double dx = pg.x - px[j], dy = pg.y - py[j], dz = pg.z - pz[j];
-        const double f = du_over_r<KIND>(fma(dx, dx, fma(dy, dy, dz * dz)), J);
+        const double f = du_over_r_f64<KIND>(fma(dx, dx, fma(dy, dy, dz * dz)), J);
         double* w = &W[rg][j * CW + cg][0][lane];
         w[0] = dx * f;
         w[64] = dy * f;

@@ -40,6 +40,12 @@ constexpr int kI8SegMax = 65536;      // grid points per int32 segment
 constexpr int kI8MaxCT = 9;           // 16-pair column tiles per wave
 constexpr int kI8Waves = 4;
 
+// The digit products a_i b_j kept (0-based, i + j <= 5), so ordered that
+// consecutive products share their left operand and add to different orders.
+constexpr int kI8Products = 21;
+constexpr int kI8Left[kI8Products] = {0, 0, 0, 0, 0, 0, 1, 1, 1, 1, 1, 2, 2, 2, 2, 3, 3, 3, 4, 4, 5};
+constexpr int kI8Right[kI8Products] = {0, 1, 2, 3, 4, 5, 0, 1, 2, 3, 4, 0, 1, 2, 3, 0, 1, 2, 0, 1, 0};
+
 // Power of two S > 2 m (1 for m = 0), so that |x| <= m gives |x| / S < 1/2.
 __host__ __device__ inline double i8_scale(double m) {
     if (!(m > 0.0)) return 1.0;
@@ -48,34 +54,43 @@ __host__ __device__ inline double i8_scale(double m) {
     return ldexp(1.0, e + 1);
 }
 
-// Signed 7-bit field at bit `off` of x, sign-extended.
-__device__ __forceinline__ int sfield7(int x, int off) { return (x << (25 - off)) >> 25; }
-
-// The six digits of v from h = v 2^21 (|h| <= 2^20 plus rounding):
+// The six digits of four values at once, from h = v 2^21 (|h| <= 2^20 plus
+// rounding), packed four to a register (byte b of w[s]: digit s of value b):
 // h = H + L 2^-21 + e with integers |H|, |L| <= 2^20 (+1) and |e| <= 2^-22,
 // then each of H, L = t 2^14 + m 2^7 + l with m, l in [-64, 63] and
-// t in [-64, 64].  Adding 8256 = 64 (2^7 + 1) turns m and l into the fields
-// (bits 7..13 and 0..6) with their top bit flipped; the FP64 roundings go
-// through the 1.5 2^52 shifter, whose low word is the rounded integer.
-__device__ __forceinline__ void i8_digits(double h, int d[kI8Digits]) {
-    const double kShift = 6755399441055744.0;   // 1.5 * 2^52
-    const double th = h + kShift;
-    const double hr = th - kShift;
-    const double tl = fma(h - hr, 2097152.0, kShift);
-    const int H = (int)__builtin_bit_cast(unsigned long long, th);
-    const int L = (int)__builtin_bit_cast(unsigned long long, tl);
-    const int uh = H + 8256, ul = L + 8256;
-    const int xh = uh ^ 0x2040, xl = ul ^ 0x2040;
-    d[0] = uh >> 14;
-    d[1] = sfield7(xh, 7);
-    d[2] = sfield7(xh, 0);
-    d[3] = ul >> 14;
-    d[4] = sfield7(xl, 7);
-    d[5] = sfield7(xl, 0);
+// t in [-64, 64].  The FP64 roundings go through the shifter 1.5 2^52 + 8256,
+// whose low word is the rounded integer plus 8256 = 64 (2^7 + 1); that turns m
+// and l into 64 more than themselves, in bits 7..13 and 0..6, which
+// i8_fields takes out of four values together (38 integer instructions for
+// the 24 digits of four values; one value at a time took 96).
+__device__ __forceinline__ int i8_bytes(int a, int b, int sel) {
+    return (int)__builtin_amdgcn_perm((unsigned)b, (unsigned)a, (unsigned)sel);
 }
-
-__device__ __forceinline__ int i8_pack(int a, int b, int c, int d) {
-    return (a & 255) | ((b & 255) << 8) | ((c & 255) << 16) | (d << 24);
+// bytes x in [0, 127] (bit 7 ignored) -> x - 64 as signed bytes
+__device__ __forceinline__ int i8_center(int x) {
+    const int y = (x & 0x7f7f7f7f) ^ 0x40404040;
+    return y | ((y & 0x40404040) << 1);
+}
+__device__ __forceinline__ void i8_fields(const int (&u)[4], int& t, int& m, int& l) {
+    const int w01 = i8_bytes(u[0], u[1], 0x05040100), w23 = i8_bytes(u[2], u[3], 0x05040100);   // low halves
+    l = i8_center(i8_bytes(w01, w23, 0x06040200));
+    m = i8_center(i8_bytes((int)((unsigned)w01 >> 7), (int)((unsigned)w23 >> 7), 0x06040200));
+    const int t01 = i8_bytes(u[0] >> 14, u[1] >> 14, 0x0c0c0400), t23 = i8_bytes(u[2] >> 14, u[3] >> 14, 0x04000c0c);
+    t = t01 | t23;
+}
+__device__ __forceinline__ void i8_digits4(const double (&h)[4], int (&w)[kI8Digits]) {
+    const double kShift = 6755399441055744.0 + 8256.0;   // 1.5 * 2^52 + 64 (2^7 + 1)
+    int uh[4], ul[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        const double th = h[b] + kShift;
+        const double hr = th - kShift;
+        const double tl = fma(h[b] - hr, 2097152.0, kShift);
+        uh[b] = (int)__builtin_bit_cast(unsigned long long, th);
+        ul[b] = (int)__builtin_bit_cast(unsigned long long, tl);
+    }
+    i8_fields(uh, w[0], w[1], w[2]);
+    i8_fields(ul, w[3], w[4], w[5]);
 }
 
 // Per-pair largest |rho_P(g')| of the gathered occupied pairs
@@ -136,14 +151,13 @@ __global__ __launch_bounds__(256) void k_occ_slice(const double* __restrict__ rh
         int w[kI8Digits][4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            int dg[4][kI8Digits];
+            double h[4];
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const double v = on ? col[(size_t)(gq + 4 * k + b) * tw] : 0.0;
-                i8_digits(v * hs, dg[b]);
-            }
+            for (int b = 0; b < 4; ++b) h[b] = (on ? col[(size_t)(gq + 4 * k + b) * tw] : 0.0) * hs;
+            int d[kI8Digits];
+            i8_digits4(h, d);
 #pragma unroll
-            for (int s = 0; s < kI8Digits; ++s) w[s][k] = i8_pack(dg[0][s], dg[1][s], dg[2][s], dg[3][s]);
+            for (int s = 0; s < kI8Digits; ++s) w[s][k] = d[s];
         }
         char* blk = stages + (kb * groups + ct8 / CT) * S::kBlockB + (size_t)(ct8 % CT) * kI8Digits * kI8TileB;
 #pragma unroll
@@ -219,24 +233,31 @@ __global__ __launch_bounds__(256, 1) void k_build_K_occ_i8(const d4* __restrict_
                                                      1024 * (wave + kI8Waves * i), 0, 0);
     };
 
-    // digits of d^comp for this lane's row and points 16 q + e of the k-step
-    // whose positions are at p64 (LDS)
-    auto gen = [&](const char* p64, i4 A[kI8Digits]) {
+    // positions 16 q + 4 k + b, b = 0..3, of the k-step whose 64 points are at
+    // p64 (LDS), with the wave's component last
+    struct Pos4 {
+        double x[4], y[4], z[4], c[4];
+    };
+    auto read_pos = [&](const char* p64, int k, Pos4& p) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            int dg[4][kI8Digits];
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const double* cq = (const double*)(p64 + 32 * (16 * q + 4 * k + b));
-                const double cx = cq[0], cy = cq[1], cz = cq[2], cc = cq[comp];
-                const double dx = pg.x - cx, dy = pg.y - cy, dz = pg.z - cz;
-                const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-                const double f = du_over_r<KIND>(r2, J);
-                i8_digits((pc - cc) * (f * hs), dg[b]);
-            }
-#pragma unroll
-            for (int s = 0; s < kI8Digits; ++s) A[s][k] = i8_pack(dg[0][s], dg[1][s], dg[2][s], dg[3][s]);
+        for (int b = 0; b < 4; ++b) {
+            const double* cq = (const double*)(p64 + 32 * (16 * q + 4 * k + b));
+            p.x[b] = cq[0];
+            p.y[b] = cq[1];
+            p.z[b] = cq[2];
+            p.c[b] = cq[comp];
         }
+    };
+    // digits of d^comp for this lane's row and those four points
+    auto gen4 = [&](const Pos4& p, int (&d)[kI8Digits]) {
+        double h[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const double dx = pg.x - p.x[b], dy = pg.y - p.y[b], dz = pg.z - p.z[b];
+            const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, kR2FloorF64)));
+            h[b] = (pc - p.c[b]) * du_over_r_nz_f64<KIND>(r2, J, hs);
+        }
+        i8_digits4(h, d);
     };
 
     i4 acc[CT][kI8Orders];
@@ -248,22 +269,72 @@ __global__ __launch_bounds__(256, 1) void k_build_K_occ_i8(const d4* __restrict_
 
     // one k-step from `buf`: the next k-step's digits, the products of this
     // one, then the wait for this wave's loads of the next stage and the
-    // barrier that publishes everyone's (and ends all reads of this one)
+    // barrier that publishes everyone's (and ends all reads of this one).  With
+    // two waves per SIMD (CT <= 5) one wave's MFMAs cover the other's generation
+    // (78 pairs, 5000 rows, 100 000 points, power Jastrow: 4.9 -> 4.2 ms with the
+    // shorter digit code).  With one (CT > 5), left to itself the compiler issues
+    // the two one after the other: the k-step then runs in four fenced quarters,
+    // each with a quarter of the MFMAs and the digits of four points, issued as
+    // one MFMA and its share of the VALU work in turn (136 pairs, 7500 rows,
+    // 150 000 points: 13.0 -> 11.2 ms).
     auto stage = [&](const char* buf) {
         if (live) {
-            i4 An[kI8Digits];
-            gen(buf + S::kDigitB, An);
-#pragma unroll
-            for (int c = 0; c < CT; ++c) {
-                i4 b[kI8Digits];
+            auto read_b = [&](int c, i4 (&b)[kI8Digits]) {
 #pragma unroll
                 for (int s = 0; s < kI8Digits; ++s)
                     b[s] = *(const i4*)(buf + ((c * kI8Digits + s) * 64 + lane) * 16);
+            };
+            i4 An[kI8Digits];
+            auto digits4 = [&](const Pos4& p, int k) {
+                int d[kI8Digits];
+                gen4(p, d);
 #pragma unroll
-                for (int o = 0; o < kI8Orders; ++o)
+                for (int s = 0; s < kI8Digits; ++s) An[s][k] = d[s];
+            };
+            if constexpr (CT <= 5) {
 #pragma unroll
-                    for (int i = 0; i <= o; ++i)
-                        acc[c][o] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[i], b[o - i], acc[c][o], 0, 0, 0);
+                for (int k = 0; k < 4; ++k) {
+                    Pos4 p;
+                    read_pos(buf + S::kDigitB, k, p);
+                    digits4(p, k);
+                }
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    i4 b[kI8Digits];
+                    read_b(c, b);
+#pragma unroll
+                    for (int j = 0; j < kI8Products; ++j)
+                        acc[c][kI8Left[j] + kI8Right[j]] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+                            A[kI8Left[j]], b[kI8Right[j]], acc[c][kI8Left[j] + kI8Right[j]], 0, 0, 0);
+                }
+            } else {
+                constexpr int kMfma = kI8Products * CT;
+                constexpr int kValu = KIND == 0 ? 144 : 212;   // VALU instructions of a quarter
+                constexpr int kPer = (4 * kValu + kMfma - 1) / kMfma;
+                i4 b[2][kI8Digits];
+                Pos4 p[2];
+                read_b(0, b[0]);
+                read_pos(buf + S::kDigitB, 0, p[0]);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (k < 3) read_pos(buf + S::kDigitB, k + 1, p[(k + 1) & 1]);
+                    digits4(p[k & 1], k);
+#pragma unroll
+                    for (int m = kMfma * k / 4; m < kMfma * (k + 1) / 4; ++m) {
+                        const int c = m / kI8Products, j = m % kI8Products;
+                        if (j == 0 && c + 1 < CT) read_b(c + 1, b[(c + 1) & 1]);
+                        acc[c][kI8Left[j] + kI8Right[j]] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+                            A[kI8Left[j]], b[c & 1][kI8Right[j]], acc[c][kI8Left[j] + kI8Right[j]], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int m = kMfma * k / 4; m < kMfma * (k + 1) / 4; ++m) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // MFMA
+                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // LDS read
+                        __builtin_amdgcn_sched_group_barrier(0x002, kPer, 0);   // VALU
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
             for (int s = 0; s < kI8Digits; ++s) A[s] = An[s];
@@ -281,7 +352,17 @@ __global__ __launch_bounds__(256, 1) void k_build_K_occ_i8(const d4* __restrict_
         issue(0, sm0);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        if (live) gen(smp, A);
+        if (live) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                Pos4 p;
+                int d[kI8Digits];
+                read_pos(smp, k, p);
+                gen4(p, d);
+#pragma unroll
+                for (int s = 0; s < kI8Digits; ++s) A[s][k] = d[s];
+            }
+        }
     }
     int t = 0;
     for (; t + 1 < nst; t += 2) {

@@ -46,26 +46,36 @@ __device__ __forceinline__ double rcp_f64(double x) {
     return fma(y, fma(e, e, e), y);
 }
 
-// u'(r)/r for the electron-electron Jastrow, from r^2; exactly 0 at r^2 == 0
-// (coincident points: the gradient of an isotropic function is taken as 0).
+// scale u'(r)/r for the electron-electron Jastrow, from r^2 > 0.  For
+// d^x = (x - x') u'(r)/r the caller adds kR2FloorF64 to r^2: the value stays
+// finite at coincident points, where the difference vector it multiplies is
+// exactly zero (the gradient of an isotropic function is taken as 0 there), and
+// the floor is below the last bit of r^2 for every r above 1e-137.  (The value
+// at the floor is about 1e145 scale u': `scale` has to keep that finite.)
 //   Pade : u = r/(2(1+br))      -> u'/r = 1 / (2 r (1+br)^2)
 //   power: u = sum c_k t^k      -> u'/r = (sum k c_k t^(k-1)) / (r (1+r)^2)
+constexpr double kR2FloorF64 = 1e-290;
 template <int KIND>
-__device__ __forceinline__ double du_over_r(double r2, const JasDev& J) {
-    const double s = rsq_f64(r2);                 // 1/r (not finite at r2 == 0: selected away)
+__device__ __forceinline__ double du_over_r_nz_f64(double r2, const JasDev& J, double scale = 1.0) {
+    const double s = rsq_f64(r2);                 // 1/r
     const double r = r2 * s;
-    double f;
     if constexpr (KIND == 0) {
         const double it = rcp_f64(fma(J.b, r, 1.0));
-        f = 0.5 * s * it * it;
+        return (0.5 * scale * s) * (it * it);
     } else {
         const double q = rcp_f64(1.0 + r);
         const double t = r * q;
         double p = J.dcoef[15];
 #pragma unroll
         for (int k = 14; k >= 0; --k) p = fma(p, t, J.dcoef[k]);
-        f = p * q * q * s;
+        return (p * (scale * s)) * (q * q);
     }
+}
+
+// u'(r)/r for r^2 >= 0, exactly 0 at r^2 == 0, for any finite coefficients.
+template <int KIND>
+__device__ __forceinline__ double du_over_r_f64(double r2, const JasDev& J) {
+    const double f = du_over_r_nz_f64<KIND>(r2, J);   // not finite at r2 == 0: selected away
     return r2 > 0.0 ? f : 0.0;
 }
 
