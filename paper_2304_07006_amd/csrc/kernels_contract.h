@@ -29,14 +29,20 @@ struct OccList {
 // Intermediates.  One workgroup handles one grid point at a time (grid-stride
 // over the rows of the chunk).  The occupied columns (rho_rk, K_rk) of that
 // point are gathered into LDS as [nocc][N][4] (each thread's loads of up to
-// kIGather entries issued together); each thread then owns 4x4
+// kIGather entries issued together); each thread then owns kITile x kITile
 // output blocks (r-block <= s-block) of the upper triangle and accumulates
-// Zt and Z over k with register blocking.
+// Zt and Z over k with register blocking.  The kernel waits on its loads and
+// barriers, so what matters is how many workgroups a CU holds and that K is
+// loaded before the sums: 2 x 2 blocks (149 registers; 4 x 4 took 254 and had
+// none left for K), in workgroups of as many waves as the blocks fill.  N=128,
+// 7500 rows: 1572 -> 1075 us (8 reads and writes of 62.5 M pair values: 4.0 GB);
+// N=160, 5000 rows: 2068 -> 1690; N=64, 20 000 rows: 1084 -> 575; N=8, 2000
+// rows: 33 -> 9 us.
 // One spin channel s per launch: Z~ and Z carry the occupations n_k of that
 // spin, W and W~ those of the total density.  Per-point scalars
 // S[g] = (W~/2, W/2 (3), sum_k n_k A_kk, sum_k n_k B_kk (3)) feed the one-body
 // reduction.
-constexpr int kIGather = 4;
+constexpr int kIGather = 4, kITile = 2;
 // Staged entry e of the intermediates' LDS array: 32 bytes, and with PAD 16
 // more bytes after every 4 entries, so that the 16 lanes of a b128 read phase
 // that fetch entries 4 apart (consecutive 4x4 tiles) hit distinct banks.
@@ -65,17 +71,18 @@ __global__ __launch_bounds__(256) void k_intermediates(const double* __restrict_
     __shared__ double sW[4];                       // Wx, Wy, Wz, Wt
     const int n = occ.n;
     const size_t kstride = (size_t)rows * ldP;
-    const int nb = (N + 3) / 4;
+    const int nb = (N + kITile - 1) / kITile;
     const int ntiles = nb * (nb + 1) / 2;
+    const int nt = blockDim.x;
     for (int g = blockIdx.x; g < rows; g += gridDim.x) {
         const double* rg = rho_rows + (size_t)g * ldP;
         const double* kg = K + (size_t)g * ldP;
         // every thread issues the loads of up to kIGather entries before storing
-        for (int base = threadIdx.x; base < n * N; base += kIGather * 256) {
+        for (int base = threadIdx.x; base < n * N; base += kIGather * nt) {
             d4 e[kIGather];
 #pragma unroll
             for (int u = 0; u < kIGather; ++u) {
-                const int idx = base + 256 * u;
+                const int idx = base + nt * u;
                 if (idx < n * N) {
                     const int kk = idx / N, r = idx % N;
                     const int P = pair_sym(r, occ.k[kk], N);
@@ -84,7 +91,7 @@ __global__ __launch_bounds__(256) void k_intermediates(const double* __restrict_
             }
 #pragma unroll
             for (int u = 0; u < kIGather; ++u)
-                if (base + 256 * u < n * N) st_staged<PAD>(lraw, base + 256 * u, e[u]);
+                if (base + nt * u < n * N) st_staged<PAD>(lraw, base + nt * u, e[u]);
         }
         __syncthreads();
         if (threadIdx.x < 64) {
@@ -132,34 +139,43 @@ __global__ __launch_bounds__(256) void k_intermediates(const double* __restrict_
         }
         __syncthreads();
         const double W0 = sW[0], W1 = sW[1], W2 = sW[2], hWt = 0.5 * sW[3];
-        for (int t = threadIdx.x; t < ntiles; t += blockDim.x) {
-            int bi = 0, rem = t;
-            while (rem >= nb - bi) { rem -= nb - bi; ++bi; }
-            const int bj = bi + rem;
-            double zt[4][4], z0[4][4], z1[4][4], z2[4][4];
+        for (int t = threadIdx.x; t < ntiles; t += nt) {
+            int bi, bj;
+            pair_split(t, nb, bi, bj);
+            double zt[kITile][kITile], z0[kITile][kITile], z1[kITile][kITile], z2[kITile][kITile];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < kITile; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) zt[i][j] = z0[i][j] = z1[i][j] = z2[i][j] = 0.0;
-            int ri[4], sj[4];
+                for (int j = 0; j < kITile; ++j) zt[i][j] = z0[i][j] = z1[i][j] = z2[i][j] = 0.0;
+            int ri[kITile], sj[kITile];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                ri[i] = min(4 * bi + i, N - 1);
-                sj[i] = min(4 * bj + i, N - 1);
+            for (int i = 0; i < kITile; ++i) {
+                ri[i] = min(kITile * bi + i, N - 1);
+                sj[i] = min(kITile * bj + i, N - 1);
             }
+            double kv[kITile][kITile][3];                      // K of the block
+#pragma unroll
+            for (int i = 0; i < kITile; ++i)
+#pragma unroll
+                for (int j = 0; j < kITile; ++j) {
+                    const int P = pair_sym(ri[i], sj[j], N);
+                    kv[i][j][0] = kg[P];
+                    kv[i][j][1] = kg[kstride + P];
+                    kv[i][j][2] = kg[2 * kstride + P];
+                }
             for (int kk = 0; kk < n; ++kk) {
                 const int row = kk * N;
                 const double nk = occ.w[kk];
-                d4 a[4], b[4];
+                d4 a[kITile], b[kITile];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int i = 0; i < kITile; ++i) {
                     a[i] = ld_staged<PAD>(lraw, row + ri[i]);
                     b[i] = nk * ld_staged<PAD>(lraw, row + sj[i]);
                 }
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < kITile; ++i)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
+                    for (int j = 0; j < kITile; ++j) {
                         zt[i][j] = fma(a[i].y, b[j].y, fma(a[i].z, b[j].z, fma(a[i].w, b[j].w, zt[i][j])));
                         z0[i][j] = fma(a[i].x, b[j].y, fma(a[i].y, b[j].x, z0[i][j]));
                         z1[i][j] = fma(a[i].x, b[j].z, fma(a[i].z, b[j].x, z1[i][j]));
@@ -167,13 +183,13 @@ __global__ __launch_bounds__(256) void k_intermediates(const double* __restrict_
                     }
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < kITile; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int r = 4 * bi + i, s = 4 * bj + j;
+                for (int j = 0; j < kITile; ++j) {
+                    const int r = kITile * bi + i, s = kITile * bj + j;
                     if (r < N && s < N && r <= s) {
                         const int P = pair_index(r, s, N);
-                        const double k0 = kg[P], k1 = kg[kstride + P], k2 = kg[2 * kstride + P];
+                        const double k0 = kv[i][j][0], k1 = kv[i][j][1], k2 = kv[i][j][2];
                         double* dg = D + (size_t)g * ldP + P;
                         dg[0] = fma(W0, k0, fma(W1, k1, W2 * k2)) - zt[i][j];
                         dg[dstride] = hWt * k0 - z0[i][j];
@@ -240,90 +256,146 @@ __global__ __launch_bounds__(256) void k_onebody_T1(const double* __restrict__ r
 
 // One-body reduction, exchange term, partial over grid splits:
 //   E[split][p][q] = sum_{g in split} sum_k n_k sum_c C_c[g][pair(p,k)] D_c[g][pair(k,q)]
-// Workgroup: a 64 x 64 block of (p,q), 4 x 4 per thread (strided by 16); the occupied columns
-// of C and rows of D for that block are staged in LDS per grid point.
-constexpr int kEBlk = 64;
-__global__ __launch_bounds__(256) void k_onebody_E(const double* __restrict__ rho_rows,
+// on FP64 MFMA, the sum over k in groups of 4 as the MFMA's inner index and
+// the sums over g and c in sequence.  Four waves share the rows of one tile of
+// 16 TB x 16 TB outputs (wave w takes g = w, w + 4, ...) and meet in LDS in a
+// fixed order.  For a fixed k the pairs (p, k) of 16 consecutive p are (almost
+// always) 16 consecutive columns, so each lane loads its operand straight from
+// the rows; the columns are found once per group of k, outside the loop over
+// g.  The next component's operands are in flight while one is multiplied.
+// N=128, 16 occupied, 7500 rows: 1000 -> 408 us; N=64, 20, 5000 rows: 621 -> 98;
+// N=24, 6, 4001 rows: 148 -> 12.5; N=8, 2, 2000 rows: 37 -> 4.3 (a thread per
+// 4 x 4 outputs over columns staged in LDS per point and component before).
+template <int TB>
+__global__ __launch_bounds__(256, 2) void k_onebody_E(const double* __restrict__ rho_rows,
                                                    const double* __restrict__ K,
                                                    const double* __restrict__ D, size_t dstride,
                                                    int rows, int ldP, int N, OccList occ,
                                                    double* __restrict__ E) {
-    extern __shared__ double sh[];                 // cs[nocc][64], ds[nocc][64]
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = occ.n;
-    double* cs = sh;
-    double* ds = sh + n * kEBlk;
-    const int nbk = (N + kEBlk - 1) / kEBlk;
-    const int pb = blockIdx.x % nbk, qb = blockIdx.x / nbk;
+    const int nt = (N + 16 * TB - 1) / (16 * TB);
+    const int p0 = (blockIdx.x % nt) * 16 * TB, q0 = (blockIdx.x / nt) * 16 * TB;
     const int split = blockIdx.y, nsplit = gridDim.y;
     const int gb = (int)(((long)rows * split) / nsplit), ge = (int)(((long)rows * (split + 1)) / nsplit);
-    // 16 x 16 threads, 4 x 4 each: p = 64 pb + ti + 16 i, q = 64 qb + tj + 16 j
-    // (the 16 lanes of a row read 16 consecutive staged values: no LDS bank
-    // conflicts, where 4 consecutive values per thread conflicted)
-    const int ti = threadIdx.x & 15, tj = threadIdx.x >> 4;
     const size_t kstride = (size_t)rows * ldP;
-    double acc[4][4];
+    const int l16 = lane & 15, kq = lane >> 4;
+    d4 acc[TB][TB];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TB; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
-    for (int g = gb; g < ge; ++g) {
-        for (int comp = 0; comp < 4; ++comp) {
-            const double* Cg = (comp == 0 ? rho_rows : K + (size_t)(comp - 1) * kstride) + (size_t)g * ldP;
-            const double* Dg = D + (size_t)comp * dstride + (size_t)g * ldP;
-            __syncthreads();
-            for (int idx = threadIdx.x; idx < n * kEBlk; idx += blockDim.x) {
-                const int kk = idx / kEBlk, j = idx % kEBlk;
-                const int k = occ.k[kk];
-                const int p = pb * kEBlk + j, q = qb * kEBlk + j;
-                cs[idx] = p < N ? Cg[pair_sym(p, k, N)] : 0.0;
-                ds[idx] = q < N ? occ.w[kk] * Dg[pair_sym(k, q, N)] : 0.0;
+        for (int j = 0; j < TB; ++j) acc[i][j] = (d4){0.0, 0.0, 0.0, 0.0};
+    for (int k0 = 0; k0 < n; k0 += 4) {
+        const int kk = min(k0 + kq, n - 1), k = occ.k[kk];
+        const bool on = k0 + kq < n;
+        const double nk = occ.w[kk];
+        int cp[TB], cq[TB];                            // this lane's columns (clamped past N)
+#pragma unroll
+        for (int i = 0; i < TB; ++i) {
+            cp[i] = pair_sym(min(p0 + 16 * i + l16, N - 1), k, N);
+            cq[i] = pair_sym(min(q0 + 16 * i + l16, N - 1), k, N);
+        }
+        double a[2][TB], b[2][TB];
+        auto load = [&](int s, int g, int c) {
+            const size_t o = (size_t)g * ldP;
+            const double* C = c == 0 ? rho_rows + o : K + (size_t)(c - 1) * kstride + o;
+            const double* Dg = D + (size_t)c * dstride + o;
+#pragma unroll
+            for (int i = 0; i < TB; ++i) {
+                a[s][i] = C[cp[i]];
+                b[s][i] = Dg[cq[i]];
             }
-            __syncthreads();
-            for (int kk = 0; kk < n; ++kk) {
-                double a[4], b[4];
+        };
+        int g = gb + wave;
+        if (g < ge) load(0, g, 0);
+        for (; g < ge; g += 4) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    a[i] = cs[kk * kEBlk + ti + 16 * i];
-                    b[i] = ds[kk * kEBlk + tj + 16 * i];
+            for (int c = 0; c < 4; ++c) {
+                double av[TB], bv[TB];
+#pragma unroll
+                for (int i = 0; i < TB; ++i) {
+                    av[i] = on ? a[c & 1][i] : 0.0;
+                    bv[i] = on ? nk * b[c & 1][i] : 0.0;
                 }
+                if (c < 3) load((c + 1) & 1, g, c + 1);
+                else load(0, min(g + 4, ge - 1), 0);
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < TB; ++i)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] = fma(a[i], b[j], acc[i][j]);
+                    for (int j = 0; j < TB; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i], bv[j], acc[i][j], 0, 0, 0);
             }
         }
     }
-    const size_t NN = (size_t)N * N;
+    // waves 2, 3 onto 0, 1, then 1 onto 0
+    __shared__ double red[2][4 * TB * TB][64];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int step = 2; step >= 1; step >>= 1) {
+        if (wave >= step && wave < 2 * step)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int p = pb * kEBlk + ti + 16 * i, q = qb * kEBlk + tj + 16 * j;
-            if (p < N && q < N) E[split * NN + (size_t)p * N + q] = acc[i][j];
+            for (int i = 0; i < TB; ++i)
+#pragma unroll
+                for (int j = 0; j < TB; ++j)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) red[wave - step][4 * (TB * i + j) + v][lane] = acc[i][j][v];
+        __syncthreads();
+        if (wave < step)
+#pragma unroll
+            for (int i = 0; i < TB; ++i)
+#pragma unroll
+                for (int j = 0; j < TB; ++j)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[i][j][v] += red[wave][4 * (TB * i + j) + v][lane];
+        __syncthreads();
+    }
+    if (wave != 0) return;
+    double* out = E + (size_t)split * N * N;
+#pragma unroll
+    for (int i = 0; i < TB; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int p = p0 + 16 * i + kq + 4 * v;    // logical row l/16 + 4v
+#pragma unroll
+            for (int j = 0; j < TB; ++j) {
+                const int q = q0 + 16 * j + l16;
+                if (p < N && q < N) out[(size_t)p * N + q] = acc[i][j][v];
+            }
         }
 }
 
 // Fold the split partials of one chunk into the packed FP64 accumulator:
 //   h1acc[pair(p,q)] (+)= sum_s T1[s][P] - 1/2 (sum_s E[s][p][q] + sum_s E[s][q][p])
-__global__ void k_onebody_accumulate(const double* __restrict__ T1, int nsplit_t1,
-                                     const double* __restrict__ E, int nsplit_e, int ldP, int N,
-                                     double* __restrict__ h1acc, int accumulate) {
-    const int P = blockIdx.x * blockDim.x + threadIdx.x;
+// 32 pairs per workgroup, the partials of each shared by kAccSlices threads
+// (slice t takes s = t, t + kAccSlices, ...) whose sums meet in a fixed order:
+// one thread per pair took 84-115 us of load latency, this takes 6-8.
+constexpr int kAccSlices = 8;
+__global__ __launch_bounds__(256) void k_onebody_accumulate(const double* __restrict__ T1, int nsplit_t1,
+                                                            const double* __restrict__ E, int nsplit_e, int ldP, int N,
+                                                            double* __restrict__ h1acc, int accumulate) {
+    __shared__ double red[kAccSlices][32];
+    const int j = threadIdx.x & 31, slice = threadIdx.x >> 5;
+    const int P = blockIdx.x * 32 + j;
     const int Npair = N * (N + 1) / 2;
-    if (P >= Npair) return;
-    int p = 0, rem = P;
-    while (rem >= N - p) { rem -= N - p; ++p; }
-    const int q = p + rem;
-    double t = 0.0;
-    for (int s = 0; s < nsplit_t1; ++s) t += T1[(size_t)s * ldP + P];
-    const size_t NN = (size_t)N * N;
-    double epq = 0.0, eqp = 0.0;
-    for (int s = 0; s < nsplit_e; ++s) {
-        epq += E[s * NN + (size_t)p * N + q];
-        eqp += E[s * NN + (size_t)q * N + p];
+    double v = 0.0;
+    if (P < Npair) {
+        int p, q;
+        pair_split(P, N, p, q);
+        double t = 0.0, e = 0.0;
+#pragma unroll 4
+        for (int s = slice; s < nsplit_t1; s += kAccSlices) t += T1[(size_t)s * ldP + P];
+        const size_t NN = (size_t)N * N;
+#pragma unroll 4
+        for (int s = slice; s < nsplit_e; s += kAccSlices) e += E[s * NN + (size_t)p * N + q] + E[s * NN + (size_t)q * N + p];
+        v = t - 0.5 * e;
     }
-    const double v = t - 0.5 * (epq + eqp);
-    h1acc[P] = accumulate ? h1acc[P] + v : v;
+    red[slice][j] = v;
+    __syncthreads();
+    if (slice == 0 && P < Npair) {
+#pragma unroll
+        for (int s = 1; s < kAccSlices; ++s) v += red[s][j];
+        h1acc[P] = accumulate ? h1acc[P] + v : v;
+    }
 }
 
 // h1[p][q] = h1acc[pair(p,q)] (symmetric bitwise) for one spin channel, or for

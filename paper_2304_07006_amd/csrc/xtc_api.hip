@@ -11,7 +11,7 @@
 //                                     of the integer occupied block (occ_i8.h)
 //   M      [ldP][ldP] doubles         FP64 accumulator of the two-body term
 //   h1acc  [ldP] doubles              FP64 accumulator of the one-body term
-//   T1     [kT1Split][ldP] doubles    per-split partials (one-body, term 1)
+//   T1     [kT1SplitMax][ldP] doubles per-split partials (one-body, term 1)
 //   E      [kESplit][N][N] doubles    per-split partials (one-body, exchange)
 //   S      [cap][8] doubles           per-point scalars of the current chunk
 //   D      [4][cap][ldP] doubles      A, Bx, By, Bz of the current chunk
@@ -77,7 +77,7 @@ xtc_status fail(xtc_status st, const char* fmt, ...) {
     return st;
 }
 
-constexpr int kT1Split = 64;
+constexpr int kT1Split = 64, kT1SplitMax = 256;
 constexpr int kESplitMax = 256;
 constexpr size_t kAlign = 256;
 constexpr int kMaxN = 256;
@@ -191,7 +191,7 @@ Layout make_layout(const xtc_problem* pb, int prec) {
     L.amax = off;    off = align_up(off + (i8 ? (size_t)L.ldK8 * sizeof(double) : 0), kAlign);
     L.M = off;       off = align_up(off + (size_t)L.nspin * L.ldP * L.ldP * sizeof(double), kAlign);
     L.h1acc = off;   off = align_up(off + (size_t)L.nspin * L.ldP * sizeof(double), kAlign);
-    L.T1 = off;      off = align_up(off + (size_t)kT1Split * L.ldP * sizeof(double), kAlign);
+    L.T1 = off;      off = align_up(off + (size_t)kT1SplitMax * L.ldP * sizeof(double), kAlign);
     L.E = off;       off = align_up(off + (size_t)kESplitMax * L.N * L.N * sizeof(double), kAlign);
     L.gacc = off;    off = align_up(off + (L.bwd ? kGradMax * sizeof(double) : 0), kAlign);
     L.occw = off;    off = align_up(off + (L.bwd ? (size_t)3 * L.N * sizeof(double) : 0), kAlign);
@@ -410,26 +410,25 @@ xtc_status run_intermediates(const Layout& L, const xtc_problem* pb, const doubl
     const int rows = g1 - g0;
     const double* rho_rows = at<double>(ws, L.rho) + (size_t)g0 * L.ldP;
     const size_t dstride = (size_t)L.cap * L.ldP;
-    const int blocks = std::min(rows, 4096);
     const size_t lds = lds_intermediates(L);
     const bool pad = intermediates_padded(L);
+    const int nb = (L.N + kITile - 1) / kITile, tiles = nb * (nb + 1) / 2;
+    const int threads = std::min(256, (int)align_up((size_t)tiles, 64));
+    const int blocks = std::min(rows, 16384);
+    const void* fn = pad ? (const void*)k_intermediates<true> : (const void*)k_intermediates<false>;
     if (lds > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(pad ? (const void*)k_intermediates<true> : (const void*)k_intermediates<false>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) {
             (void)hipGetLastError();   // do not leave the error for the caller's next HIP call
             return fail(XTC_E_HIP, "intermediates LDS attribute: %s", hipGetErrorString(e));
         }
     }
     for (int sp = 0; sp < L.nspin; ++sp) {
-        if (pad)
-            hipLaunchKernelGGL(k_intermediates<true>, dim3(blocks), dim3(256), lds, st, rho_rows, K, rows, L.ldP, L.N,
-                               make_occ(pb, sp), at<double>(ws, L.D) + (size_t)sp * 4 * dstride, dstride,
-                               at<double>(ws, L.S) + (size_t)sp * L.cap * 8);
-        else
-            hipLaunchKernelGGL(k_intermediates<false>, dim3(blocks), dim3(256), lds, st, rho_rows, K, rows, L.ldP,
-                               L.N, make_occ(pb, sp), at<double>(ws, L.D) + (size_t)sp * 4 * dstride, dstride,
-                               at<double>(ws, L.S) + (size_t)sp * L.cap * 8);
+        const OccList occ = make_occ(pb, sp);
+        double* D = at<double>(ws, L.D) + (size_t)sp * 4 * dstride;
+        double* S = at<double>(ws, L.S) + (size_t)sp * L.cap * 8;
+        hipLaunchKernelGGL((pad ? k_intermediates<true> : k_intermediates<false>), dim3(blocks), dim3(threads), lds, st,
+                           rho_rows, K, rows, L.ldP, L.N, occ, D, dstride, S);
         xtc_status s;
         if ((s = launched("intermediates")) != XTC_OK) return s;
     }
@@ -921,19 +920,15 @@ xtc_status xtc_contract_1body_0body(const xtc_problem* pb, const double* K, int3
     const int rows = g1 - g0;
     const double* rho_rows = at<double>(ws, L.rho) + (size_t)g0 * L.ldP;
     const size_t dstride = (size_t)L.cap * L.ldP;
-    const int nsplit_t1 = std::min(kT1Split, rows);
-    const int nbk = (L.N + kEBlk - 1) / kEBlk;
-    int nsplit_e = std::max(1, std::min(kESplitMax, 1024 / (nbk * nbk)));
-    nsplit_e = std::min(nsplit_e, rows);
-    const size_t lds = (size_t)2 * L.nocc * kEBlk * sizeof(double);
-    if (lds > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute((const void*)k_onebody_E,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            return fail(XTC_E_HIP, "onebody_E LDS attribute: %s", hipGetErrorString(e));
-        }
-    }
+    // term 1: kT1Split row splits, more where few pairs leave the chip idle
+    const int t1_blocks = (L.Npair + 255) / 256;
+    const int nsplit_t1 = std::min(rows, std::max(kT1Split, std::min(kT1SplitMax, 1024 / t1_blocks)));
+    // exchange term: tiles of 64 outputs a side (16, 32 for smaller N), and row
+    // splits until the four-wave workgroups fill the chip about twice
+    const int tb = L.N <= 16 ? 1 : L.N <= 32 ? 2 : 4;
+    const int n_t = (L.N + 16 * tb - 1) / (16 * tb);
+    int nsplit_e = std::max(1, std::min(kESplitMax, 1024 / (n_t * n_t)));
+    nsplit_e = std::min(nsplit_e, (rows + 7) / 8);
     const double* S = at<double>(ws, L.S);
     const size_t sstride = (size_t)L.cap * 8;
     // per spin channel (T1 and E are scratch of one channel at a time)
@@ -943,10 +938,15 @@ xtc_status xtc_contract_1body_0body(const xtc_problem* pb, const double* K, int3
                            dstride, S + sp * sstride, L.nspin == 2 ? S + (1 - sp) * sstride : nullptr, rows, L.ldP,
                            L.Npair, at<double>(ws, L.T1));
         if ((s = launched("onebody_T1")) != XTC_OK) return s;
-        hipLaunchKernelGGL(k_onebody_E, dim3(nbk * nbk, nsplit_e), dim3(256), lds, st, rho_rows, K, Ds, dstride,
-                           rows, L.ldP, L.N, make_occ(pb, sp), at<double>(ws, L.E));
+        const auto exchange = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(n_t * n_t, nsplit_e), dim3(256), 0, st, rho_rows, K, Ds, dstride, rows,
+                               L.ldP, L.N, make_occ(pb, sp), at<double>(ws, L.E));
+        };
+        if (tb == 1) exchange(k_onebody_E<1>);
+        else if (tb == 2) exchange(k_onebody_E<2>);
+        else exchange(k_onebody_E<4>);
         if ((s = launched("onebody_E")) != XTC_OK) return s;
-        hipLaunchKernelGGL(k_onebody_accumulate, dim3((L.Npair + 255) / 256), dim3(256), 0, st,
+        hipLaunchKernelGGL(k_onebody_accumulate, dim3((L.Npair + 31) / 32), dim3(256), 0, st,
                            at<double>(ws, L.T1), nsplit_t1, at<double>(ws, L.E), nsplit_e, L.ldP, L.N,
                            at<double>(ws, L.h1acc) + (size_t)sp * L.ldP, (flags & XTC_RESET) ? 0 : 1);
         if ((s = launched("onebody_accumulate")) != XTC_OK) return s;

@@ -88,4 +88,14 @@ __device__ __forceinline__ int pair_sym(int p, int q, int N) {
     return p <= q ? pair_index(p, q, N) : pair_index(q, p, N);
 }
 
+// The pair (p, q), p <= q < N, of packed index P: pair_index inverted, from the
+// root of its quadratic in FP32 (exact integers below 2^24), corrected.
+__device__ __forceinline__ void pair_split(int P, int N, int& p, int& q) {
+    const float b = 2.0f * N + 1.0f;
+    p = min(max((int)(0.5f * (b - sqrtf(fmaxf(b * b - 8.0f * P, 0.0f)))), 0), N - 1);
+    while (p > 0 && pair_index(p, p, N) > P) --p;
+    while (p + 1 < N && pair_index(p + 1, p + 1, N) <= P) ++p;
+    q = p + P - pair_index(p, p, N);
+}
+
 }  // namespace xtc
