@@ -1136,16 +1136,26 @@ xtc_status xtc_backward(const xtc_problem* pb, const xtc_jastrow* jas, int32_t p
 namespace {
 constexpr int kLowdinSeg = 4096;
 constexpr int kJacobiMaxSweeps = 40;
+// Points per partial of S: at most kLowdinSeg, and short enough that the tiles
+// of a mid-size grid fill the chip, while the partials stay within 32 MiB.
+constexpr size_t kLowdinPartBudget = (size_t)32 << 20;
 struct LowdinLayout {
-    int ldS, nseg;
-    size_t part, S, U, X, sweeps, status, total;
+    int ldS, nseg, seg;
+    size_t part, S, U, X, rot, sweeps, status, total;
 };
 LowdinLayout lowdin_layout(int N, int Ng) {
     LowdinLayout L{};
     L.ldS = (int)align_up((size_t)N, 64);
-    L.nseg = (Ng + kLowdinSeg - 1) / kLowdinSeg;
+    const size_t psize = (size_t)L.ldS * L.ldS * sizeof(double);
+    const int want = (int)std::min<size_t>(256, kLowdinPartBudget / psize);
+    L.seg = std::min(kLowdinSeg, std::max(64, (int)align_up((size_t)((Ng + want - 1) / want), 16)));
+    L.nseg = (Ng + L.seg - 1) / L.seg;
+    // the rotations (c, s) of every round the eigensolver may take go where the
+    // partials were
+    const size_t rot = (size_t)kJacobiMaxSweeps * (N + 1) * ((N + 1) / 2) * 2 * sizeof(double);
     size_t off = 0;
-    L.part = off;   off = align_up(off + (size_t)L.nseg * L.ldS * L.ldS * sizeof(double), kAlign);
+    L.part = L.rot = off;
+    off = align_up(off + std::max((size_t)L.nseg * psize, rot), kAlign);
     L.S = off;      off = align_up(off + (size_t)N * N * sizeof(double), kAlign);
     L.U = off;      off = align_up(off + (size_t)N * N * sizeof(double), kAlign);
     L.X = off;      off = align_up(off + (size_t)N * N * sizeof(double), kAlign);
@@ -1360,16 +1370,28 @@ xtc_status run_lowdin(const LowdinLayout& L, int N, int Ng, const double* chi, c
                       double* lambda, void* ws, hipStream_t st) {
     xtc_status s;
     const int n_t = L.ldS / 64;
-    hipLaunchKernelGGL(k_syrk_w_part, dim3(n_t * n_t, L.nseg), dim3(256), 0, st, chi, w, N, Ng, L.ldS, n_t,
-                       kLowdinSeg, at<double>(ws, L.part));
+    hipLaunchKernelGGL(k_syrk_w_part, dim3(n_t * (n_t + 1) / 2, L.nseg), dim3(256), 0, st, chi, w, N, Ng, L.ldS, n_t,
+                       L.seg, at<double>(ws, L.part));
     if ((s = launched("syrk_w")) != XTC_OK) return s;
     const int NN = N * N;
     hipLaunchKernelGGL(k_syrk_reduce, dim3((NN + 255) / 256), dim3(256), 0, st, at<double>(ws, L.part), L.nseg, N,
-                       L.ldS, at<double>(ws, L.S), at<double>(ws, L.U));
+                       L.ldS, at<double>(ws, L.S));
     if ((s = launched("syrk_reduce")) != XTC_OK) return s;
-    hipLaunchKernelGGL(k_jacobi, dim3(1), dim3(kJacobiThreads), 0, st, at<double>(ws, L.S), at<double>(ws, L.U), N,
-                       kJacobiMaxSweeps, at<int>(ws, L.sweeps));
+    const size_t lds = N <= kJacobiLdsN ? (size_t)N * N * sizeof(double) : 0;
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void*)k_jacobi<true>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(XTC_E_HIP, "jacobi LDS attribute: %s", hipGetErrorString(e));
+        }
+    }
+    hipLaunchKernelGGL((lds ? k_jacobi<true> : k_jacobi<false>), dim3(1), dim3(kJacobiThreads), lds, st,
+                       at<double>(ws, L.S), N, kJacobiMaxSweeps, at<double>(ws, L.rot), at<int>(ws, L.sweeps));
     if ((s = launched("jacobi")) != XTC_OK) return s;
+    hipLaunchKernelGGL(k_jacobi_vectors, dim3(N), dim3(64), 0, st, at<double>(ws, L.rot), at<int>(ws, L.sweeps), N,
+                       at<double>(ws, L.U));
+    if ((s = launched("jacobi_vectors")) != XTC_OK) return s;
     // convergence and positive definiteness are checked before anything is
     // written to phi or lambda (one synchronisation of the stream)
     hipLaunchKernelGGL(k_lowdin_status, dim3(1), dim3(64), 0, st, at<double>(ws, L.S), N, at<int>(ws, L.sweeps),
@@ -1387,7 +1409,15 @@ xtc_status run_lowdin(const LowdinLayout& L, int N, int Ng, const double* chi, c
     hipLaunchKernelGGL(k_inv_sqrt, dim3((NN + 255) / 256), dim3(256), 0, st, at<double>(ws, L.S), at<double>(ws, L.U),
                        N, at<double>(ws, L.X));
     if ((s = launched("inv_sqrt")) != XTC_OK) return s;
-    hipLaunchKernelGGL(k_apply_X, dim3((Ng + 255) / 256, N), dim3(256), (size_t)N * sizeof(double), st,
+    const size_t xlds = align_up((size_t)N, 4) * 64 * sizeof(double);
+    if (xlds > 64 * 1024) {
+        e = hipFuncSetAttribute((const void*)k_apply_X, hipFuncAttributeMaxDynamicSharedMemorySize, (int)xlds);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(XTC_E_HIP, "apply_X LDS attribute: %s", hipGetErrorString(e));
+        }
+    }
+    hipLaunchKernelGGL(k_apply_X, dim3((Ng + kApplyPoints - 1) / kApplyPoints, (N + 63) / 64), dim3(256), xlds, st,
                        at<double>(ws, L.X), chi, N, Ng, phi);
     if ((s = launched("apply_X")) != XTC_OK) return s;
     if (lambda) {

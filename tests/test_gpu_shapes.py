@@ -40,3 +40,26 @@ def test_fp64_forward_at_split_and_tile_edges(torch_cuda, N, nocc, Ng, chunk, ce
     assert abs(float(E0.cpu()[0]) - E0o) < TOL * max(1.0, abs(E0o))
     again = xtc.forward(p, prec="fp64", chunk_rows=chunk)
     assert torch_cuda.equal(V2, again[0]) and torch_cuda.equal(h1, again[1]) and torch_cuda.equal(E0, again[2])
+
+
+# matrix in LDS (N <= 140) and beyond, odd N (dummy partner), one function,
+# one 64-row tile and one row more, fewer points than a wave's 64
+@pytest.mark.parametrize("N,Ng", [(1, 40), (3, 50), (37, 1500), (64, 700), (65, 2100), (140, 3000), (141, 3000),
+                                  (160, 4133)])
+def test_lowdin_at_matrix_and_tile_edges(torch_cuda, N, Ng):
+    from oracle import lowdin as ol
+    from paper_2304_07006_amd import xtc
+    print(f"case: lowdin N={N} Ng={Ng}", flush=True)
+    nc = max(1, (N + 3) // 4)
+    rng = np.random.default_rng(70 + N)
+    centres = inputs.chain_centres(nc, rng)
+    xyz, w = inputs.sample_grid(centres, Ng, rng)
+    chi = np.ascontiguousarray(inputs.basis_values(xyz, centres, 4, rng)[0][:N])
+    phi_o, _, lam_o = ol.lowdin(chi, w)
+    phi, lam = xtc.lowdin(chi, w)
+    # S is formed to a few ulp of its largest entry, S^{-1/2} to cond(S) times that
+    tol = 50 * np.finfo(float).eps * lam_o.max() / lam_o.min() * max(1, N / 8)
+    assert np.abs(np.sort(lam.cpu().numpy()) - np.sort(lam_o)).max() < 50 * N * np.finfo(float).eps * lam_o.max()
+    assert np.abs(phi.cpu().numpy() - phi_o).max() < tol * max(1.0, np.abs(phi_o).max())
+    again = xtc.lowdin(chi, w)
+    assert torch_cuda.equal(phi, again[0]) and torch_cuda.equal(lam, again[1])
