@@ -204,19 +204,62 @@ __global__ __launch_bounds__(256) void k_intermediates(const double* __restrict_
 
 // --------------------------------------------------------------------------
 // V2[p][q][r][s] = -(M2[P][R] + M1[R][P]).  Closed shell: M1 = M2 = M, and all
-// eight index symmetries hold bitwise because both terms are read for every
-// ordering.  Open shell, spins (s, t) of (pq, rs): M2 = M^t, M1 = M^s
+// eight index symmetries hold bitwise because the sum does not depend on the
+// order of its terms.  Open shell, spins (s, t) of (pq, rs): M2 = M^t, M1 = M^s
 // (Appendix A, [Delta U]^{st}[pq, rs] = -(f^t(pq, rs) + f^s(rs, pq))).
-__global__ __launch_bounds__(256) void k_finalize_V2(const double* __restrict__ M1, const double* __restrict__ M2,
-                                                     int ldP, int N, double* __restrict__ V2) {
-    const int p = blockIdx.y, q = blockIdx.z;
-    const int pq = p * N + q;
-    const int P = pair_sym(p, q, N);
-    const int NN = N * N;
-    for (int rs = blockIdx.x * blockDim.x + threadIdx.x; rs < NN; rs += gridDim.x * blockDim.x) {
-        const int r = rs / N, s = rs % N;
-        const int R = pair_sym(r, s, N);
-        V2[(size_t)pq * NN + rs] = -(M2[(size_t)P * ldP + R] + M1[(size_t)R * ldP + P]);
+// Bound by the write of V2 (2.1 GB at N=128).  Two steps over slabs of rows P:
+// the packed sums W[P - P0][R] in 32 x 32 tiles, the transposed term through
+// LDS, and then row P of W written to (p, q) and (q, p).  N=128: 4.01 ms with
+// every element reading M[R][P] down a column, 0.35 + 0.85 ms now.
+__global__ __launch_bounds__(256) void k_sym_sum(const double* __restrict__ M1, const double* __restrict__ M2, int ldP,
+                                                 int P0, double* __restrict__ W) {
+    __shared__ double t[32][33];
+    const int Rt = blockIdx.x * 32, Pt = P0 + blockIdx.y * 32;
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+#pragma unroll
+    for (int i = 0; i < 32; i += 8) t[ty + i][tx] = M1[(size_t)(Rt + ty + i) * ldP + Pt + tx];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 32; i += 8)
+        W[(size_t)(Pt - P0 + ty + i) * ldP + Rt + tx] = -(M2[(size_t)(Pt + ty + i) * ldP + Rt + tx] + t[tx][ty + i]);
+}
+
+// One workgroup: rows r of a tile of kExpandRows, all s, of one P.  The values
+// with s >= r are read along s; those with s < r, whose packed index runs along
+// r, come 16 consecutive r at a time through LDS.
+constexpr int kExpandRows = 16;
+__global__ __launch_bounds__(256) void k_expand_V2(const double* __restrict__ W, int ldP, int P0, int N,
+                                                   double* __restrict__ V2) {
+    __shared__ double t[kExpandRows][257];
+    const int P = P0 + blockIdx.y, r0 = blockIdx.x * kExpandRows;
+    int p, q;
+    pair_split(P, N, p, q);
+    const double* row = W + (size_t)blockIdx.y * ldP;
+    const int rj = threadIdx.x & (kExpandRows - 1);
+    for (int s = threadIdx.x / kExpandRows; s < min(N, r0 + kExpandRows); s += 256 / kExpandRows) {
+        const int r = r0 + rj;
+        if (r < N && s < r) t[rj][s] = row[pair_index(s, r, N)];
+    }
+    __syncthreads();
+    const size_t NN = (size_t)N * N;
+    double* pq = V2 + ((size_t)p * N + q) * NN;
+    double* qp = V2 + ((size_t)q * N + p) * NN;
+    const int rows = min(kExpandRows, N - r0);
+    int r = 0, s = threadIdx.x;
+    while (s >= N) {
+        s -= N;
+        ++r;
+    }
+    while (r < rows) {
+        const double v = s < r0 + r ? t[r][s] : row[pair_index(r0 + r, s, N)];
+        const size_t o = (size_t)(r0 + r) * N + s;
+        pq[o] = v;
+        if (p != q) qp[o] = v;
+        s += 256;
+        while (s >= N) {
+            s -= N;
+            ++r;
+        }
     }
 }
 

@@ -117,11 +117,18 @@ __device__ __forceinline__ void xcd_strip_tile(int id, int n_rt, int nstrip, boo
 // --------------------------------------------------------------------------
 // Pack an FP64 row-major array src[nrows][ld_src] (columns < ncols valid) into
 // the k8-packed operand format dst[s][n8][ld_dst][8]; rows >= nrows and
-// columns >= ncols become 0.
+// columns >= ncols become 0.  blockIdx.z: array z of `srcs`, packed comp_stride
+// elements after array z - 1 (one launch for the components of an operand).
+constexpr int kPackMax = 4;
+struct PackSrc {
+    const double* p[kPackMax];
+};
 template <int FORM>
-__global__ __launch_bounds__(256) void k_pack_lp(const double* __restrict__ src, int nrows, int ld_src,
-                                                 int ncols, int ld_dst, void* __restrict__ dst,
-                                                 size_t split_stride) {
+__global__ __launch_bounds__(256) void k_pack_lp(PackSrc srcs, int nrows, int ld_src, int ncols, int ld_dst,
+                                                 void* __restrict__ dst0, size_t split_stride, size_t comp_stride) {
+    const double* __restrict__ src = srcs.p[blockIdx.z];
+    void* dst = FORM == 1 ? (void*)((float*)dst0 + blockIdx.z * comp_stride)
+                          : (void*)((__bf16*)dst0 + blockIdx.z * comp_stride);
     const int P = blockIdx.x * blockDim.x + threadIdx.x;
     const int g8 = blockIdx.y;
     if (P >= ld_dst) return;

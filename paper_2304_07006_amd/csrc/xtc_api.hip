@@ -436,21 +436,20 @@ xtc_status run_intermediates(const Layout& L, const xtc_problem* pb, const doubl
 }
 
 // ---------------------------------------------------------------- reduced precision
-template <int FORM>
-xtc_status pack_lp(const double* src, int nrows, int ld_src, int ncols, int n8, int ld_dst, void* dst,
-                   size_t split_stride, hipStream_t st) {
-    hipLaunchKernelGGL((k_pack_lp<FORM>), dim3((ld_dst + 255) / 256, n8), dim3(256), 0, st, src, nrows, ld_src, ncols,
-                       ld_dst, dst, split_stride);
+// Pack up to kPackMax FP64 row-major arrays [nrows][ld_src] into consecutive
+// components (comp_stride elements apart) of the k8-packed operand format.
+xtc_status pack_many(int form, const PackSrc& src, int ncomp, int nrows, int ld_src, int ncols, int n8, int ld_dst,
+                     void* dst, size_t split_stride, size_t comp_stride, hipStream_t st) {
+    const dim3 grid((ld_dst + 255) / 256, n8, ncomp);
+    const auto kernel = form == 1 ? k_pack_lp<1> : form == 3 ? k_pack_lp<3> : k_pack_lp<6>;
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, src, nrows, ld_src, ncols, ld_dst, dst, split_stride,
+                       comp_stride);
     return launched("pack_lp");
 }
 
 xtc_status pack_any(int form, const double* src, int nrows, int ld_src, int ncols, int n8, int ld_dst, void* dst,
                     size_t split_stride, hipStream_t st) {
-    switch (form) {
-        case 1: return pack_lp<1>(src, nrows, ld_src, ncols, n8, ld_dst, dst, split_stride, st);
-        case 3: return pack_lp<3>(src, nrows, ld_src, ncols, n8, ld_dst, dst, split_stride, st);
-        default: return pack_lp<6>(src, nrows, ld_src, ncols, n8, ld_dst, dst, split_stride, st);
-    }
+    return pack_many(form, PackSrc{{src}}, 1, nrows, ld_src, ncols, n8, ld_dst, dst, split_stride, 0, st);
 }
 
 template <int KIND, int FORM, int NC = 3>
@@ -608,19 +607,16 @@ xtc_status gemm2b_lp(const Layout& L, const double* K, int g0, int rows, int acc
     const size_t comp_bytes = (size_t)L.ns * split_stride * L.es;
     char* cd = at<char>(ws, L.CDlp);
     const double* rho_rows = at<double>(ws, L.rho) + (size_t)g0 * L.ldP;
-    for (int c = 0; c < 4; ++c) {
-        const double* src = c == 0 ? rho_rows : K + (size_t)(c - 1) * rows * L.ldP;
-        if ((s = pack_any(L.form, src, rows, L.ldP, L.ldP, n8, L.ldL, cd + c * comp_bytes, split_stride, st)) != XTC_OK)
-            return s;
-    }
+    const size_t ks = (size_t)rows * L.ldP, ds = (size_t)L.cap * L.ldP, comp = (size_t)L.ns * split_stride;
+    if ((s = pack_many(L.form, PackSrc{{rho_rows, K, K + ks, K + 2 * ks}}, 4, rows, L.ldP, L.ldP, n8, L.ldL, cd,
+                       split_stride, comp, st)) != XTC_OK)
+        return s;
     // one spin channel at a time: its D into the operand buffer, GEMM, reduction into M^s
     for (int sp = 0; sp < L.nspin; ++sp) {
         const double* D = at<double>(ws, L.D) + (size_t)sp * 4 * L.cap * L.ldP;
-        for (int c = 0; c < 4; ++c) {
-            if ((s = pack_any(L.form, D + (size_t)c * L.cap * L.ldP, rows, L.ldP, L.ldP, n8, L.ldL,
-                              cd + (4 + c) * comp_bytes, split_stride, st)) != XTC_OK)
-                return s;
-        }
+        if ((s = pack_many(L.form, PackSrc{{D, D + ds, D + 2 * ds, D + 3 * ds}}, 4, rows, L.ldP, L.ldP, n8, L.ldL,
+                           cd + 4 * comp_bytes, split_stride, comp, st)) != XTC_OK)
+            return s;
         if ((s = gemm_tn_grouped(L, cd, L.ldL, split_stride, cd + 4 * comp_bytes, L.ldL, split_stride, rows32, L.ldP,
                                  L.ldP, 4, 1, at<double>(ws, L.M) + (size_t)sp * L.ldP * L.ldP, L.ldP, accumulate,
                                  ws, st)) != XTC_OK)
@@ -711,6 +707,23 @@ xtc_status gemm_tn_f64(const Layout& L, const TnOperand& A, const TnOperand& B, 
     hipLaunchKernelGGL(k_reduce_M_f64, dim3((unsigned)std::min<size_t>((n4 + 255) / 256, 16384)), dim3(256), 0, st, out,
                        p.nseg, msize, ldm, imax, jmax4, M, accumulate);
     return launched("reduce_M_f64");
+}
+
+// One spin block of V2 from the accumulators, in slabs of rows P whose packed
+// sums fit the two-body partial buffer (free by then).
+xtc_status finalize_V2(const Layout& L, const double* M1, const double* M2, double* V2, void* ws, hipStream_t st) {
+    xtc_status s;
+    double* W = at<double>(ws, L.Mpart);
+    const int slab = (int)std::min<size_t>(L.ldP, L.mpart / (L.ldP * sizeof(double)) / 32 * 32);
+    for (int P0 = 0; P0 < L.Npair; P0 += slab) {
+        const int np = std::min(slab, L.Npair - P0);
+        hipLaunchKernelGGL(k_sym_sum, dim3(L.ldP / 32, (np + 31) / 32), dim3(256), 0, st, M1, M2, L.ldP, P0, W);
+        if ((s = launched("sym_sum")) != XTC_OK) return s;
+        hipLaunchKernelGGL(k_expand_V2, dim3((L.N + kExpandRows - 1) / kExpandRows, np), dim3(256), 0, st, W, L.ldP, P0,
+                           L.N, V2);
+        if ((s = launched("expand_V2")) != XTC_OK) return s;
+    }
+    return XTC_OK;
 }
 
 // The adjoint's X Gbar products in the split-BF16 3-product form (k_nt_bf16,
@@ -880,19 +893,14 @@ xtc_status xtc_contract_2body(const xtc_problem* pb, const double* K, int32_t g0
         }
     }
     if (flags & XTC_FINALIZE) {
-        const int NN = L.N * L.N;
-        const size_t N4 = (size_t)NN * NN;
+        const size_t N4 = (size_t)L.N * L.N * L.N * L.N;
         const double* Ma = at<double>(ws, L.M);
         const double* Mb = Ma + (size_t)L.ldP * L.ldP;
-        const dim3 grid((NN + 255) / 256, L.N, L.N);
         // closed shell: V2 = block (a, a); open shell: blocks (a, a), (a, b), (b, b)
-        hipLaunchKernelGGL(k_finalize_V2, grid, dim3(256), 0, st, Ma, Ma, L.ldP, L.N, V2);
-        if ((s = launched("finalize_V2")) != XTC_OK) return s;
+        if ((s = finalize_V2(L, Ma, Ma, V2, ws, st)) != XTC_OK) return s;
         if (L.nspin == 2) {
-            hipLaunchKernelGGL(k_finalize_V2, grid, dim3(256), 0, st, Ma, Mb, L.ldP, L.N, V2 + N4);
-            if ((s = launched("finalize_V2")) != XTC_OK) return s;
-            hipLaunchKernelGGL(k_finalize_V2, grid, dim3(256), 0, st, Mb, Mb, L.ldP, L.N, V2 + 2 * N4);
-            if ((s = launched("finalize_V2")) != XTC_OK) return s;
+            if ((s = finalize_V2(L, Ma, Mb, V2 + N4, ws, st)) != XTC_OK) return s;
+            if ((s = finalize_V2(L, Mb, Mb, V2 + 2 * N4, ws, st)) != XTC_OK) return s;
         }
     }
     return XTC_OK;
@@ -1279,13 +1287,12 @@ xtc_status xtc_tc_2body(const xtc_problem* pb, const xtc_jastrow* jas, const dou
                                  st)) != XTC_OK)
             return s;
         char* kd = cd + 3 * cN;
-        for (int x = 0; x < 3; ++x) {
-            if ((s = pack_any(L.form, Rg + x * xs, rows, L.ldN, L.ldN, n8, L.ldN, cd + x * cN, sN, st)) != XTC_OK)
-                return s;
-            if ((s = pack_any(L.form, K + (size_t)x * rows * L.ldP, rows, L.ldP, L.ldP, n8, L.ldL, kd + x * cL, sL,
-                              st)) != XTC_OK)
-                return s;
-        }
+        const size_t ks = (size_t)rows * L.ldP;
+        if ((s = pack_many(L.form, PackSrc{{Rg, Rg + xs, Rg + 2 * xs}}, 3, rows, L.ldN, L.ldN, n8, L.ldN, cd, sN,
+                           L.ns * sN, st)) != XTC_OK ||
+            (s = pack_many(L.form, PackSrc{{K, K + ks, K + 2 * ks}}, 3, rows, L.ldP, L.ldP, n8, L.ldL, kd, sL,
+                           L.ns * sL, st)) != XTC_OK)
+            return s;
         // the three components of rhog_pq . K_R summed inside each workgroup
         if ((s = gemm_tn_grouped(L, cd, L.ldN, sN, kd, L.ldL, sL, rows32, L.N * L.N, L.ldP, 3, 3, Btc, L.ldP, acc, ws,
                                  st)) != XTC_OK)
@@ -1321,15 +1328,10 @@ xtc_status xtc_frozen_core(int32_t N, const double* V2, const double* h1, const 
         else a.k[i - ncore] = k;
     }
     hipStream_t st = (hipStream_t)stream;
-    xtc_status s;
-    hipLaunchKernelGGL(k_fc_onebody, dim3((nact * nact + 255) / 256), dim3(256), 0, st, V2, h1, N, c, a, h1_act);
-    if ((s = launched("fc_onebody")) != XTC_OK) return s;
-    hipLaunchKernelGGL(k_fc_energy, dim3(1), dim3(64), 0, st, V2, h1, E0, N, c, E_fc);
-    if ((s = launched("fc_energy")) != XTC_OK) return s;
-    const size_t total = (size_t)nact * nact * nact * nact;
-    hipLaunchKernelGGL(k_fc_gather, dim3((unsigned)std::min<size_t>((total + 255) / 256, 65536)), dim3(256), 0, st, V2,
-                       N, a, V2_act);
-    return launched("fc_gather");
+    const int n_h = (nact * nact + 255) / 256;
+    hipLaunchKernelGGL(k_frozen_core, dim3(1 + n_h + nact * nact), dim3(256), 0, st, V2, h1, E0, N, c, a, n_h, V2_act,
+                       h1_act, E_fc);
+    return launched("frozen_core");
 }
 
 size_t xtc_lowdin_workspace_size(int32_t N, int32_t Ng) {
