@@ -248,31 +248,34 @@ __device__ __forceinline__ float scalar_S_fast(float r2, const JasDev& J) {
 // NC = 1 builds F = S rho instead (the scalar kernel of the two-body TC
 // integrals, one component), with the same tiling.
 constexpr int kLpThreads = 512;
-// Column blocks of 16 per wave and pair columns per workgroup.  The
-// one-component build (F) generates as much per k-step as the three-component
-// one but multiplies a third as much, so in the 3-product form each wave takes
-// twice the columns (8 blocks), halving the generation per MFMA (Pade
-// Jastrow: the power series' two polynomials leave no registers for it).
+// Tile variants: NW waves (4 NW grid rows) and NB 16-column blocks per wave.
+// The standard one is 8 waves of 4 blocks.  The one-component build (F)
+// generates as much per k-step as the three-component one but multiplies a
+// third as much, so in the 3-product form each wave takes twice the columns (8
+// blocks), halving the generation per MFMA (Pade Jastrow: the power series' two
+// polynomials leave no registers for it).  The smaller tiles fill the chip where
+// the standard one leaves most of it idle (lp_tile in the host code); every
+// accumulator sees the same products in the same order in all of them.
 template <int KIND, int FORM, int NC> struct LpTile {
+    static constexpr int NW = 8;
     static constexpr int NB = (NC == 1 && FORM == 3 && KIND == 0) ? 8 : 4;
-    static constexpr int cols = (kLpThreads / 64) * 16 * NB;
 };
-static_assert(LpTile<0, 3, 3>::cols == kLpCols && LpTile<1, 3, 3>::cols == kLpCols,
+static_assert(LpTile<0, 3, 3>::NW * 16 * LpTile<0, 3, 3>::NB == kLpCols &&
+                  LpTile<1, 3, 3>::NW * 16 * LpTile<1, 3, 3>::NB == kLpCols,
               "the K build tiles ldL = a multiple of kLpCols");
-template <int KIND, int FORM, int NC = 3>
-__global__ __launch_bounds__(kLpThreads) void k_build_K_lp(const d4* __restrict__ pos,
+template <int KIND, int FORM, int NC, int NW, int NB>
+__global__ __launch_bounds__(64 * NW) void k_build_K_lp(const d4* __restrict__ pos,
                                                            const void* __restrict__ rho_lp, size_t split_stride,
                                                            int ldL, int ngp, int g0, int rows, int n_rt,
                                                            int seg_len, JasDev J, float* __restrict__ part,
                                                            int cap, int ncol, int n_ct, int nseg) {
     typedef typename Lp<FORM>::T T;
     constexpr int NS = Lp<FORM>::NS;
-    constexpr int NB = LpTile<KIND, FORM, NC>::NB;       // 16-column blocks per wave
-    constexpr int kWgCols = LpTile<KIND, FORM, NC>::cols;
+    constexpr int kWgCols = NW * 16 * NB, kRows = 4 * NW, H = NW / 4;   // H 16-row halves per wave
     // two generation buffers as distinct arrays, so the compiler can prove the
     // writes of the next k-step do not alias the reads of the current one
     constexpr int kARow = LpARow<FORM>::v;
-    typedef T ATile[NC][NS][kLpRows][kARow];
+    typedef T ATile[NC][NS][kRows][kARow];
     __shared__ __attribute__((aligned(16))) ATile sA0;
     __shared__ __attribute__((aligned(16))) ATile sA1;
     // positions of the 32 g' of one k-step as x[], y[], z[], pad[] (double
@@ -286,8 +289,8 @@ __global__ __launch_bounds__(kLpThreads) void k_build_K_lp(const d4* __restrict_
     // operands keep 2^-24, takes the differences in FP64 and rounds them once.
     typedef typename std::conditional<FORM == 1, double, float>::type PosT;
     typedef PosT PTile[4][kLpK];
-    __shared__ __attribute__((aligned(16))) PTile sP0[kLpThreads / 64];
-    __shared__ __attribute__((aligned(16))) PTile sP1[kLpThreads / 64];
+    __shared__ __attribute__((aligned(16))) PTile sP0[NW];
+    __shared__ __attribute__((aligned(16))) PTile sP1[NW];
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     // Flat grid over strips (column tile, segment of g') x row tiles, in the
@@ -296,7 +299,7 @@ __global__ __launch_bounds__(kLpThreads) void k_build_K_lp(const d4* __restrict_
     // advance through g' together.  Column tiles with idle waves finish early
     // and would stagger every later workgroup (and break that sharing), so
     // they are dispatched last, after all full tiles of all segments.
-    const int n_full = ((n_ct - 1) * kWgCols + 7 * 16 * NB < ncol) ? n_ct : n_ct - 1;
+    const int n_full = ((n_ct - 1) * kWgCols + (NW - 1) * 16 * NB < ncol) ? n_ct : n_ct - 1;
     int rt, ct, seg;
     {
         const int id = blockIdx.x, nf = n_rt * n_full * nseg;
@@ -319,7 +322,7 @@ __global__ __launch_bounds__(kLpThreads) void k_build_K_lp(const d4* __restrict_
     // that the 32 lanes of a half-wave store to 32 distinct LDS banks.
     const int grow = 4 * (threadIdx.x >> 6) + 2 * ((threadIdx.x >> 4) & 1) + ((threadIdx.x >> 5) & 1);
     const int gk = 2 * (threadIdx.x & 15);
-    const d4 pr = pos[g0 + min(rt * kLpRows + grow, rows - 1)];
+    const d4 pr = pos[g0 + min(rt * kRows + grow, rows - 1)];
     const PosT prx = (PosT)pr.x, pry = (PosT)pr.y, prz = (PosT)pr.z;
     // MFMA role
     const int l16 = lane & 15, lk = lane >> 4;
@@ -328,11 +331,11 @@ __global__ __launch_bounds__(kLpThreads) void k_build_K_lp(const d4* __restrict_
     // to generate the shared tiles: no operand loads, MFMAs or stores
     const bool active = ct * kWgCols + wave * 16 * NB < ncol;
 
-    f4 acc[NC][2][NB];
+    f4 acc[NC][H][NB];
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < H; ++h)
 #pragma unroll
             for (int b = 0; b < NB; ++b) acc[c][h][b] = (f4){0.f, 0.f, 0.f, 0.f};
 
@@ -436,7 +439,7 @@ __global__ __launch_bounds__(kLpThreads) void k_build_K_lp(const d4* __restrict_
         if constexpr (FORM == 1) {
             gen(PR, W);
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
+            for (int h = 0; h < H; ++h) {
                 float av[NC][8];
 #pragma unroll
                 for (int c = 0; c < NC; ++c) {
@@ -458,7 +461,7 @@ __global__ __launch_bounds__(kLpThreads) void k_build_K_lp(const d4* __restrict_
         } else {
             gen(PR, W);
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
+            for (int h = 0; h < H; ++h) {
                 bf8 av[NC][NS];
 #pragma unroll
                 for (int c = 0; c < NC; ++c)
@@ -483,7 +486,7 @@ __global__ __launch_bounds__(kLpThreads) void k_build_K_lp(const d4* __restrict_
         constexpr int kValuPer = FORM == 1 ? 1 : 2;
         __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int h = 0; h < H; ++h) {
             __builtin_amdgcn_sched_group_barrier(0x100, NC * NS * (FORM == 1 ? 2 : 1), 0);
 #pragma unroll
             for (int i = 0; i < kMfmaHalf; ++i) {
@@ -528,10 +531,10 @@ __global__ __launch_bounds__(kLpThreads) void k_build_K_lp(const d4* __restrict_
     const size_t cstride = (size_t)cap * ldL;
     float* out = part + (size_t)seg * NC * cstride;
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < H; ++h)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int r = rt * kLpRows + 16 * h + 4 * lk + v;
+            const int r = rt * kRows + 16 * h + 4 * lk + v;
             if (r < rows) {
 #pragma unroll
                 for (int c = 0; c < NC; ++c)
@@ -542,9 +545,9 @@ __global__ __launch_bounds__(kLpThreads) void k_build_K_lp(const d4* __restrict_
         }
 }
 
-// K[c][r][P] = sum_s part[s][c][r][P] in FP64 (fixed order), for c < nc, r < rows, P < ldP;
-// K's components are krows rows apart (a piece of a longer chunk).
-__global__ void k_reduce_K(const float* __restrict__ part, int nseg, int cap, int ldL, int rows, int ldP,
+// K[c][r][P] = sum_s part[s][c][r][P] in FP64 (fixed order), for c < nc, r < rows, P < ldP
+// (0 from P >= ncol on); K's components are krows rows apart (a piece of a longer chunk).
+__global__ void k_reduce_K(const float* __restrict__ part, int nseg, int cap, int ldL, int rows, int ldP, int ncol,
                            double* __restrict__ K, int krows, int nc) {
     // four consecutive pairs per thread (ldP, ldL and the component strides are
     // multiples of 4): 16-byte partial loads, 32-byte stores, same summation order
@@ -556,7 +559,7 @@ __global__ void k_reduce_K(const float* __restrict__ part, int nseg, int cap, in
         const int r = (int)(cr % rows), c = (int)(cr / rows);
         const size_t o = c * cstride + (size_t)r * ldL + P;
         d4 s = (d4){0.0, 0.0, 0.0, 0.0};
-        for (int q = 0; q < nseg; ++q) {
+        for (int q = 0; q < (P < ncol ? nseg : 0); ++q) {
             const f4 v = *(const f4*)(part + (size_t)q * nc * cstride + o);
             s += (d4){(double)v[0], (double)v[1], (double)v[2], (double)v[3]};
         }
@@ -661,6 +664,84 @@ __global__ __launch_bounds__(256) void k_gemm_tn_lp(const void* __restrict__ Clp
 #pragma unroll
             for (int j = 0; j < 8; ++j) out[(size_t)P * ldD + R0 + 16 * j] = acc[i][j][v];
         }
+}
+
+// The same product for matrices of few tiles: four waves as 2 x 2 of 16 IB x
+// 16 JB outputs each, so that a small matrix still spreads over the chip, the
+// next k-step's operands in flight while one is multiplied.  Every accumulator
+// sees the same products in the same order as in the kernels around it.
+template <int FORM, int IB, int JB>
+__global__ __launch_bounds__(256) void k_gemm_tn_small(const void* __restrict__ Clp, int ldC, size_t c_split,
+                                                       const void* __restrict__ Dlp, int ldD, size_t d_split,
+                                                       int rows32, int n_pt, int cpw, int seg_len, int nseg_r,
+                                                       float* __restrict__ part) {
+    constexpr int NS = Lp<FORM>::NS;
+    constexpr int NV = FORM == 1 ? 2 : NS;             // 16-byte vectors per operand block and k-step
+    typedef typename std::conditional<FORM == 1, f4, bf8>::type vec;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int pt = blockIdx.x % n_pt, rt = blockIdx.x / n_pt;
+    const int c0 = (blockIdx.y / nseg_r) * cpw, sg = blockIdx.y % nseg_r;
+    const int gs = sg * seg_len, ge = min(rows32, gs + seg_len);
+    const int l16 = lane & 15, lk = lane >> 4;
+    const int P0 = pt * 32 * IB + 16 * IB * (wave & 1), R0 = rt * 32 * JB + 16 * JB * (wave >> 1);
+    f4 acc[IB][JB];
+#pragma unroll
+    for (int i = 0; i < IB; ++i)
+#pragma unroll
+        for (int j = 0; j < JB; ++j) acc[i][j] = (f4){0.f, 0.f, 0.f, 0.f};
+    const int nk = (ge - gs) / kLpK, nq = nk * cpw;
+    vec a[2][IB][NV], b[2][JB][NV];
+    auto load = [&](int q, vec (&av)[IB][NV], vec (&bv)[JB][NV]) {
+        const int qq = min(q, nq - 1), comp = c0 + qq / nk;
+        const size_t g8 = (gs + kLpK * (qq % nk)) / 8 + lk;
+        constexpr int kEs = FORM == 1 ? 4 : 2;
+        const char* C = (const char*)Clp + ((size_t)comp * NS * c_split + (g8 * ldC + P0 + l16) * 8) * kEs;
+        const char* D = (const char*)Dlp + ((size_t)comp * NS * d_split + (g8 * ldD + R0 + l16) * 8) * kEs;
+#pragma unroll
+        for (int s = 0; s < NV; ++s) {
+#pragma unroll
+            for (int i = 0; i < IB; ++i)
+                av[i][s] = *(const vec*)(C + (FORM == 1 ? 16 * s : s * c_split * kEs) + 128 * i * kEs);
+#pragma unroll
+            for (int j = 0; j < JB; ++j)
+                bv[j][s] = *(const vec*)(D + (FORM == 1 ? 16 * s : s * d_split * kEs) + 128 * j * kEs);
+        }
+    };
+    auto multiply = [&](const vec (&av)[IB][NV], const vec (&bv)[JB][NV]) {
+        if constexpr (FORM == 1) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+#pragma unroll
+                for (int j = 0; j < JB; ++j)
+#pragma unroll
+                    for (int i = 0; i < IB; ++i)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i][e / 4][e % 4], bv[j][e / 4][e % 4],
+                                                                         acc[i][j], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int t = 0; t < Terms<FORM>::n; ++t)
+#pragma unroll
+                for (int j = 0; j < JB; ++j)
+#pragma unroll
+                    for (int i = 0; i < IB; ++i)
+                        acc[i][j] = mma_bf16(av[i][Terms<FORM>::a[t]], bv[j][Terms<FORM>::b[t]], acc[i][j]);
+        }
+    };
+    load(0, a[0], b[0]);
+    for (int q = 0; q < nq; q += 2) {
+        load(q + 1, a[1], b[1]);
+        multiply(a[0], b[0]);
+        load(q + 2, a[0], b[0]);
+        if (q + 1 < nq) multiply(a[1], b[1]);
+    }
+    float* out = part + (size_t)blockIdx.y * ldC * ldD;
+#pragma unroll
+    for (int i = 0; i < IB; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int j = 0; j < JB; ++j)
+                out[(size_t)(P0 + 16 * i + 4 * lk + v) * ldD + R0 + 16 * j + l16] = acc[i][j][v];
 }
 
 // The same product in split BF16 with both operands staged in LDS.

@@ -18,7 +18,7 @@
 //   Kpart  [nsegK][3][kcap][ldL] f32  K-build segment partials of kcap rows (prec != FP64; FP64: FP64 partials
 //          of a K build split over g', at most kKpartF64Budget bytes)
 //   CDlp   [8][NS][cap/8][ldL][8]     C and D of the chunk, k8-packed (prec != FP64)
-//   Mpart  [kMSegGroup][4][ldL][ldL] f32  two-body partials of a group of row segments
+//   Mpart  [group][4][ldL][ldL] f32   two-body partials of a group of row segments
 //          (FP64: partials of a row-split product, at most kMpartF64Budget bytes)
 // and with XTC_WITH_BACKWARD in prec (the adjoint reuses M for Gbar):
 //   Kc [3][cap][ldP], Y [7][cap][ldP], T [cap][3][N][nocc], Wbar [cap][3],
@@ -36,7 +36,7 @@
 // forms are bounded: the K build runs over a chunk in equal row pieces of at
 // most kcap rows (kcap = min(cap, the multiple of 1024 rows whose partials
 // fit kKpartBudget bytes, at least 1024)), and the two-body GEMM over groups of
-// kMSegGroup row segments, each piece reduced into its FP64 result before the
+// row segments, each piece reduced into its FP64 result before the
 // next one reuses the partial buffer.
 #include <hip/hip_runtime.h>
 
@@ -109,7 +109,13 @@ constexpr int kRowQuant = 32;
 constexpr int kOccSegMax = 32;  // most segments of the FP64 occupied-block sum over g'
 constexpr size_t kKpartBudget = (size_t)16 << 30;  // bytes of K-build segment partials
 constexpr int kKpartQuant = 1024;                  // rows: 32 row tiles, one XCD's resident set
-constexpr int kMSegGroup = 2;                      // row segments per two-body GEMM launch
+// Row segments per two-body GEMM launch: two, and for smaller matrices as many
+// (up to kMSegGroupMax) as fit kMpartBudget bytes of partials, so that a launch
+// has rounds enough of workgroups (N=48 in FP32, 4000 rows: four launches of 400
+// workgroups, the second round of each half empty, 173 us each; one of 1600
+// takes 654).
+constexpr int kMSegGroup = 2, kMSegGroupMax = 16;
+constexpr size_t kMpartBudget = (size_t)512 << 20;
 // Row-split FP64 products: most row segments, and bytes of their partials (a
 // matrix too large for two partials has tiles enough to fill the chip).
 constexpr int kTnSplitMax = 64;
@@ -213,7 +219,7 @@ Layout make_layout(const xtc_problem* pb, int prec) {
     // packed operands: C and D of the two-body GEMM (8 components of ldL), or
     // w phi grad phi (3 of ldN) and K (3 of ldL) of the TC integrals
     L.cdw = std::max((size_t)8 * L.ldL, L.tc2 ? (size_t)3 * L.ldN + (size_t)3 * L.ldL : 0);
-    L.mpart = lp ? (size_t)kMSegGroup * L.mslab
+    L.mpart = lp ? L.mslab * std::min<size_t>(kMSegGroupMax, std::max<size_t>(kMSegGroup, kMpartBudget / L.mslab))
                  : std::min(kMpartF64Budget, (size_t)kTnSplitMax * std::max(L.ldP, L.tc2 ? L.ldN : 0) * L.ldP * sizeof(double));
     L.chunk0 = off;
     L.fixed = off + L.mpart + (L.bwd ? gslab : 0) + 16 * kAlign;
@@ -452,15 +458,56 @@ xtc_status pack_any(int form, const double* src, int nrows, int ld_src, int ncol
     return pack_many(form, PackSrc{{src}}, 1, nrows, ld_src, ncols, n8, ld_dst, dst, split_stride, 0, st);
 }
 
-template <int KIND, int FORM, int NC = 3>
-void launch_build_lp(const Layout& L, int g0, int rows, const JasDev& J, void* ws, hipStream_t st) {
-    const int n_rt = (rows + kLpRows - 1) / kLpRows;
-    // ldL is a multiple of 512; a 1024-column tile past it has only inactive waves there
-    constexpr int cols = LpTile<KIND, FORM, NC>::cols;
-    const int n_ct = (L.ldL + cols - 1) / cols;
-    hipLaunchKernelGGL((k_build_K_lp<KIND, FORM, NC>), dim3(n_rt * n_ct * L.nsegK), dim3(kLpThreads), 0, st,
+// Tile variant of the reduced K build over `rows` rows: the one whose busiest
+// CU needs the fewest cycles per k-step, a workgroup costing its active waves'
+// MFMAs and generation on four SIMDs (about 350 cycles of generation per wave;
+// at least 900 in all, the latency of a step).  0 is the standard tile, which
+// every grid of more than a few rounds takes; N=21 on 1501 rows is 47 workgroups
+// of it (91 us) and 188 of 16 x 128 columns (53 us).
+struct LpVariant {
+    int waves, blocks;
+};
+constexpr LpVariant kLpVariants[] = {{8, 0}, {8, 2}, {4, 2}, {4, 1}};   // blocks 0: LpTile's
+int lp_tile(const Layout& L, int rows, int nc, int std_blocks) {
+    int best = 0;
+    double best_cycles = 1e300;
+    for (int i = 0; i < 4; ++i) {
+        const int w = kLpVariants[i].waves, nb = i ? kLpVariants[i].blocks : std_blocks;
+        const int cols = w * 16 * nb;
+        const int n_ct = (L.Npair + cols - 1) / cols;
+        const long wgs = (long)((rows + 4 * w - 1) / (4 * w)) * n_ct * L.nsegK;
+        const double mfma = (w / 4) * nb * nc * (L.form == 1 ? 8 * 32.0 : L.form * 16.0);
+        const double step = std::max(900.0, (w / 4) * (mfma + 350.0));
+        // co-resident workgroups of the small tiles share the step's latency
+        const double per_cu = (double)((wgs + kCus - 1) / kCus);
+        const double cycles = std::max(step, per_cu * (w / 4) * (mfma + 350.0));
+        if (cycles < 0.85 * best_cycles) {
+            best = i;
+            best_cycles = cycles;
+        }
+    }
+    return best;
+}
+
+template <int KIND, int FORM, int NC, int W, int NB>
+void launch_build_lp_tile(const Layout& L, int g0, int rows, const JasDev& J, void* ws, hipStream_t st) {
+    constexpr int cols = W * 16 * NB;
+    const int n_rt = (rows + 4 * W - 1) / (4 * W);
+    const int n_ct = (L.Npair + cols - 1) / cols;      // columns from Npair on are not read
+    hipLaunchKernelGGL((k_build_K_lp<KIND, FORM, NC, W, NB>), dim3(n_rt * n_ct * L.nsegK), dim3(64 * W), 0, st,
                        at<d4>(ws, L.pos), at<void>(ws, L.rho_lp), (size_t)L.ngp * L.ldL, L.ldL, L.ngp, g0, rows, n_rt,
-                       L.segK, J, at<float>(ws, L.Kpart), L.kcap, L.ldP, n_ct, L.nsegK);
+                       L.segK, J, at<float>(ws, L.Kpart), L.kcap, L.Npair, n_ct, L.nsegK);
+}
+
+template <int KIND, int FORM, int NC>
+void launch_build_lp(const Layout& L, int g0, int rows, const JasDev& J, void* ws, hipStream_t st) {
+    typedef LpTile<KIND, FORM, NC> Std;
+    switch (lp_tile(L, rows, NC, Std::NB)) {
+        case 0: return launch_build_lp_tile<KIND, FORM, NC, Std::NW, Std::NB>(L, g0, rows, J, ws, st);
+        case 1: return launch_build_lp_tile<KIND, FORM, NC, 8, 2>(L, g0, rows, J, ws, st);
+        case 2: return launch_build_lp_tile<KIND, FORM, NC, 4, 2>(L, g0, rows, J, ws, st);
+        default: return launch_build_lp_tile<KIND, FORM, NC, 4, 1>(L, g0, rows, J, ws, st);
+    }
 }
 
 // The split K build of rows [g0, g0 + rows) (nc = 3: K, or nc = 1: F of the
@@ -488,7 +535,7 @@ xtc_status build_lp_pieces(const Layout& L, int g0, int rows, const JasDev& J, d
         const size_t n4 = (size_t)NC * nr * L.ldP / 4;   // k_reduce_K: four pairs per thread
         const unsigned blocks = (unsigned)std::min<size_t>((n4 + 255) / 256, 16384);
         hipLaunchKernelGGL(k_reduce_K, dim3(blocks), dim3(256), 0, st, at<float>(ws, L.Kpart), L.nsegK, L.kcap,
-                           L.ldL, nr, L.ldP, out + (size_t)r0 * L.ldP, rows, NC);
+                           L.ldL, nr, L.ldP, L.Npair, out + (size_t)r0 * L.ldP, rows, NC);
         if ((s = launched("reduce_K")) != XTC_OK) return s;
     }
     return XTC_OK;
@@ -541,19 +588,33 @@ xtc_status gemm_tn_lp(int form, const void* C, int ldC, size_t c_split, const vo
                       int rows32, int pmax, int rmax, int ncomp, int cpw, int seg_len, float* part, int* nparts,
                       hipStream_t st) {
     const int nseg_r = (rows32 + seg_len - 1) / seg_len;
+    const int ny = (ncomp / cpw) * nseg_r;
+    *nparts = ny;
+    // few tiles: 64 x 64 outputs per workgroup, or 32 x 32 if those are still
+    // fewer than CUs (N=21, 1501 rows, is one 256 x 256 tile per component: 95 -> 28 us)
+    const long big = (long)((pmax + (form == 3 ? 255 : 127)) / (form == 3 ? 256 : 128)) * ((rmax + 255) / 256);
+    if (big * ny < kCus / 2) {
+        const int b = (long)((pmax + 63) / 64) * ((rmax + 63) / 64) * ny >= kCus ? 2 : 1;
+        const int n_pt = (pmax + 32 * b - 1) / (32 * b), n_rt = (rmax + 32 * b - 1) / (32 * b);
+        const auto kernel = form == 1 ? (b == 2 ? k_gemm_tn_small<1, 2, 2> : k_gemm_tn_small<1, 1, 1>)
+                          : form == 3 ? (b == 2 ? k_gemm_tn_small<3, 2, 2> : k_gemm_tn_small<3, 1, 1>)
+                                      : (b == 2 ? k_gemm_tn_small<6, 2, 2> : k_gemm_tn_small<6, 1, 1>);
+        hipLaunchKernelGGL(kernel, dim3(n_pt * n_rt, ny), dim3(256), 0, st, C, ldC, c_split, D, ldD, d_split, rows32,
+                           n_pt, cpw, seg_len, nseg_r, part);
+        return launched("gemm_tn_small");
+    }
     if (form == 3 && ldC % 256 == 0 && ldD % 256 == 0) {
         // both operands staged in LDS (256 x 256 tiles over [0, pmax) x [0, rmax)),
         // dealt to the 8 XCDs in ranges of per_xcd tiles
         const int n_pt = (pmax + 255) / 256, n_rt = (rmax + 255) / 256;
         const int per_xcd = (n_pt * n_rt + 7) / 8;
-        const dim3 grid(8 * per_xcd, (ncomp / cpw) * nseg_r);
+        const dim3 grid(8 * per_xcd, ny);
         hipLaunchKernelGGL((k_gemm_tn_lds<3>), grid, dim3(kTnThreads), 0, st, C, ldC, c_split, D, ldD, d_split, rows32,
                            n_pt, n_rt, per_xcd, pmax, rmax, cpw, seg_len, nseg_r, part);
-        *nparts = (int)grid.y;
         return launched("gemm_tn_lds");
     }
     const int n_pt = ldC / 128, n_rt = ldD / 256;
-    const dim3 grid(n_pt * n_rt, (ncomp / cpw) * nseg_r);
+    const dim3 grid(n_pt * n_rt, ny);
     if (form == 1)
         hipLaunchKernelGGL((k_gemm_tn_lp<1>), grid, dim3(256), 0, st, C, ldC, c_split, D, ldD, d_split, rows32, n_pt,
                            pmax, rmax, cpw, seg_len, nseg_r, part);
@@ -563,7 +624,6 @@ xtc_status gemm_tn_lp(int form, const void* C, int ldC, size_t c_split, const vo
     else
         hipLaunchKernelGGL((k_gemm_tn_lp<6>), grid, dim3(256), 0, st, C, ldC, c_split, D, ldD, d_split, rows32, n_pt,
                            pmax, rmax, cpw, seg_len, nseg_r, part);
-    *nparts = (int)grid.y;
     return launched("gemm_tn_lp");
 }
 
@@ -578,14 +638,14 @@ xtc_status reduce_parts(const float* part, int nparts, int ldC, int ldD, int pma
 }
 
 // M (+)= C^T D over rows32 packed operand rows (reduced forms), launched in
-// groups of kMSegGroup row segments of segM rows: each group's FP32 partials
+// groups of row segments of segM rows that fit the partial buffer: each group's FP32 partials
 // are summed in FP64 into M before the next group reuses the partial buffer.
 xtc_status gemm_tn_grouped(const Layout& L, const char* C, int ldC, size_t c_split, const char* D, int ldD,
                            size_t d_split, int rows32, int pmax, int rmax, int ncomp, int cpw, double* M, int ldM,
                            int accumulate, void* ws, hipStream_t st) {
     xtc_status s;
     float* part = at<float>(ws, L.Mpart);
-    const int group = kMSegGroup * L.segM;
+    const int group = (int)(L.mpart / L.mslab) * L.segM;
     for (int q0 = 0; q0 < rows32; q0 += group) {
         const int nr = std::min(group, rows32 - q0);
         const size_t shift = (size_t)(q0 / 8) * 8 * L.es;   // bytes per packed row group and column

@@ -63,3 +63,22 @@ def test_lowdin_at_matrix_and_tile_edges(torch_cuda, N, Ng):
     assert np.abs(phi.cpu().numpy() - phi_o).max() < tol * max(1.0, np.abs(phi_o).max())
     again = xtc.lowdin(chi, w)
     assert torch_cuda.equal(phi, again[0]) and torch_cuda.equal(lam, again[1])
+
+
+# the reduced forms' small K-build tiles and small transposed products, and the
+# sizes around them (one row tile, one column tile, one k-step; many tiles)
+@pytest.mark.parametrize("prec", ["fp32", "bf16x3", "bf16x6"])
+@pytest.mark.parametrize("N,nocc,Ng,chunk,centres", [
+    (4, 1, 33, 33, 1), (8, 2, 2000, 2000, 2), (20, 5, 1501, 700, 5), (28, 6, 1024, 1024, 7), (40, 6, 3000, 1500, 5)])
+def test_reduced_forward_at_tile_edges(torch_cuda, prec, N, nocc, Ng, chunk, centres):
+    from paper_2304_07006_amd import xtc
+    print(f"case: {prec} forward N={N} nocc={nocc} Ng={Ng} chunk={chunk}", flush=True)
+    p = inputs.make_problem(N, nocc, Ng, centres, "chain", "power16", seed=300 + N + Ng)
+    V2o, h1o, E0o = factorised.closed_shell(p.xyz, p.w, p.phi, p.occ, p.jastrow)
+    V2, h1, E0 = xtc.forward(p, prec=prec, chunk_rows=chunk)
+    # 1e-6 is the bar of the forms on outputs of order one; it scales with the output
+    assert np.abs(V2.cpu().numpy() - V2o).max() < 1e-6 * max(1.0, np.abs(V2o).max())
+    assert np.abs(h1.cpu().numpy() - h1o).max() < 1e-6 * max(1.0, np.abs(h1o).max())
+    assert abs(float(E0.cpu()[0]) - E0o) < 1e-8 * max(1.0, abs(E0o))
+    again = xtc.forward(p, prec=prec, chunk_rows=chunk)
+    assert torch_cuda.equal(V2, again[0]) and torch_cuda.equal(h1, again[1]) and torch_cuda.equal(E0, again[2])
