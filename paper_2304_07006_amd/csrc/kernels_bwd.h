@@ -32,10 +32,6 @@
 
 namespace xtc {
 
-// occupied orbitals whose T columns one thread of k_adj_T keeps in registers
-// at a time (larger sets are taken in groups of this many)
-constexpr int kAdjOccGroup = 24;
-
 // ---------------------------------------------------------------- seeds --
 // Effective seed Gt[a,b,c,d] (see the header comment); occw[p] = n_p, 0 for
 // orbitals outside the density.
@@ -167,14 +163,27 @@ __global__ __launch_bounds__(256) void k_make_gbar_open(const double* __restrict
 }
 
 // ------------------------------------------------------- NT GEMM (FP64) --
-// Y[i][j] (+)= sum_k X[i][k] Gm[j][k] for i < rows, j < ldP, k < ldP, i.e.
-// X Gm^T (closed shell: Gm = Gbar, symmetric).  Workgroup 4 waves as 2 x 2, wave tile 32 (i) x 64 (j).
-// Each lane loads 4 consecutive k of one row per operand block (32-byte
-// vectors); MFMA e of a 16-k step uses element e, i.e. the k index inside the
-// step is permuted as 4 (l/16) + e identically for both operands.
-__global__ __launch_bounds__(256) void k_gemm_xg_f64(const double* __restrict__ X, size_t ldx, int rows,
-                                                     const double* __restrict__ Gm, int ldP, int n_jt,
-                                                     double* __restrict__ Y, size_t ldy, int accumulate) {
+// Y[i][j] (+)= sum_k X[i][k] Gm[j][k] for i < rows, j < ldP, k < kmax (a
+// multiple of 16: the pairs, both operands are zero past them), i.e. X Gm^T
+// (closed shell: Gm = Gbar, symmetric).  blockIdx.y is one of the products of
+// a spin channel: they share their launch, so that a small matrix fills the
+// chip (N=24, 4001 rows: seven launches of 39 us -> one of 176).  Workgroup 4
+// waves as 2 x 2, wave tile 32 (i) x 64 (j).  Each lane loads 4 consecutive k of one row per operand block (32-byte
+// vectors), one 16-k step ahead; MFMA e of a step uses element e, i.e. the k
+// index inside the step is permuted as 4 (l/16) + e identically for both
+// operands.
+constexpr int kXgMax = 7;
+struct XgProducts {
+    const double* X[kXgMax];
+    const double* G[kXgMax];
+    double* Y[kXgMax];
+    int accumulate[kXgMax];
+};
+__global__ __launch_bounds__(256, 2) void k_gemm_xg_f64(XgProducts prod, int rows, int ldP, int kmax, int n_jt) {
+    const double* __restrict__ X = prod.X[blockIdx.y];
+    const double* __restrict__ Gm = prod.G[blockIdx.y];
+    double* __restrict__ Y = prod.Y[blockIdx.y];
+    const int accumulate = prod.accumulate[blockIdx.y];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int it = blockIdx.x / n_jt, jt = blockIdx.x % n_jt;
     const int i0 = it * 64 + 32 * (wave & 1), j0 = jt * 128 + 64 * (wave >> 1);
@@ -186,16 +195,26 @@ __global__ __launch_bounds__(256) void k_gemm_xg_f64(const double* __restrict__ 
         for (int b = 0; b < 4; ++b) acc[a][b] = (d4){0.0, 0.0, 0.0, 0.0};
     const double* xr[2];
 #pragma unroll
-    for (int a = 0; a < 2; ++a) xr[a] = X + (size_t)min(i0 + 16 * a + l16, rows - 1) * ldx + kq;
+    for (int a = 0; a < 2; ++a) xr[a] = X + (size_t)min(i0 + 16 * a + l16, rows - 1) * ldP + kq;
     const double* gr[4];
 #pragma unroll
     for (int b = 0; b < 4; ++b) gr[b] = Gm + (size_t)(j0 + 16 * b + l16) * ldP + kq;
-    for (int k = 0; k < ldP; k += 16) {
+    d4 xn[2], gn[4];
+    auto load = [&](int k) {
+        const int kk = min(k, kmax - 16);
+#pragma unroll
+        for (int a = 0; a < 2; ++a) xn[a] = *(const d4*)(xr[a] + kk);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) gn[b] = *(const d4*)(gr[b] + kk);
+    };
+    load(0);
+    for (int k = 0; k < kmax; k += 16) {
         d4 xa[2], gb[4];
 #pragma unroll
-        for (int a = 0; a < 2; ++a) xa[a] = *(const d4*)(xr[a] + k);
+        for (int a = 0; a < 2; ++a) xa[a] = xn[a];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) gb[b] = *(const d4*)(gr[b] + k);
+        for (int b = 0; b < 4; ++b) gb[b] = gn[b];
+        load(k + 16);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -212,7 +231,7 @@ __global__ __launch_bounds__(256) void k_gemm_xg_f64(const double* __restrict__ 
             if (i < rows) {
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
-                    double* y = Y + (size_t)i * ldy + j0 + 16 * b + l16;
+                    double* y = Y + (size_t)i * ldP + j0 + 16 * b + l16;
                     *y = accumulate ? *y + acc[a][b][v] : acc[a][b][v];
                 }
             }
@@ -225,6 +244,8 @@ __global__ __launch_bounds__(256) void k_gemm_xg_f64(const double* __restrict__ 
 // (off-diagonal packed entries counted half in each full-matrix slot),
 //   T^x[r][k] = -2 n_k sum_s (Abar'[r][s] X^x[s][k] + Bbar'^x[r][s] rho_o[s][k])
 // and Wbar^x = sum_R Abar_R K^x_R.  T goes to scratch [rows][3][N][nocc].
+// The sum over s runs on FP64 MFMA (N=96, 12 occupied, 5000 rows: 1500 -> 510 us,
+// N=24, 4001 rows: 193 -> 30 us; one thread per (r, columns) walked s alone).
 // Open shell: one launch per spin channel (its Abar, Bbar slots and
 // occupations), the second adding into T and Wbar (accumulate).
 __global__ __launch_bounds__(256) void k_adj_T(const double* __restrict__ rho_rows, const double* __restrict__ K,
@@ -234,6 +255,7 @@ __global__ __launch_bounds__(256) void k_adj_T(const double* __restrict__ rho_ro
     extern __shared__ d4 locc[];                    // [nocc][N] of (rho, Kx, Ky, Kz)
     __shared__ double red[3][4];
     const int n = occ.n;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
     const size_t kstride = (size_t)rows * ldP;
     const double* Abar = Y + 3 * ystride;           // Y slots: 0..2 Kbar direct, 3 Abar, 4..6 Bbar
     for (int g = blockIdx.x; g < rows; g += gridDim.x) {
@@ -260,49 +282,63 @@ __global__ __launch_bounds__(256) void k_adj_T(const double* __restrict__ rho_ro
             w1 += __shfl_xor(w1, m);
             w2 += __shfl_xor(w2, m);
         }
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
         if (lane == 0) { red[0][wave] = w0; red[1][wave] = w1; red[2][wave] = w2; }
         __syncthreads();
         if (threadIdx.x == 0) {
             for (int x = 0; x < 3; ++x) {
-                const double v = red[x][0] + red[x][1] + red[x][2] + red[x][3];
+                double v = red[x][0];
+                for (int u = 1; u < nw; ++u) v += red[x][u];
                 Wbar[(size_t)g * 3 + x] = accumulate ? Wbar[(size_t)g * 3 + x] + v : v;
             }
         }
-        // T rows: one thread per (r, group of kAdjOccGroup occupied columns),
-        // the group's columns in registers
-        const int ngrp = (n + kAdjOccGroup - 1) / kAdjOccGroup;
-        for (int rq = threadIdx.x; rq < N * ngrp; rq += blockDim.x) {
-            const int r = rq % N, k0 = (rq / N) * kAdjOccGroup;
-            double t0[kAdjOccGroup], t1[kAdjOccGroup], t2[kAdjOccGroup];
-#pragma unroll
-            for (int kk = 0; kk < kAdjOccGroup; ++kk) t0[kk] = t1[kk] = t2[kk] = 0.0;
-            const double* bx = Y + 4 * ystride + (size_t)g * ldP;
-            const double* by = Y + 5 * ystride + (size_t)g * ldP;
-            const double* bz = Y + 6 * ystride + (size_t)g * ldP;
-            for (int s = 0; s < N; ++s) {
+        // T rows: one wave per block of 16 r (its lanes' l/16 the inner index s
+        // of the MFMA), 16 occupied columns at a time from LDS; the next four
+        // s of Abar and Bbar are in flight while four are multiplied
+        const double* bg = Y + 4 * ystride + (size_t)g * ldP;
+        const int l16 = lane & 15, kq = lane >> 4;
+        for (int r0 = 16 * wave; r0 < N; r0 += 16 * nw) {
+            const int r = min(r0 + l16, N - 1);
+            double nx[4];
+            auto load = [&](int s0) {
+                const int s = min(s0 + kq, N - 1);
                 const int R = pair_sym(r, s, N);
-                const double h = r == s ? 1.0 : 0.5;
-                const double a = h * ag[R], b0 = h * bx[R], b1 = h * by[R], b2 = h * bz[R];
-#pragma unroll
-                for (int kk = 0; kk < kAdjOccGroup; ++kk) {
-                    if (k0 + kk < n) {
-                        const d4 e = locc[(k0 + kk) * N + s];      // (rho_sk, K_sk)
-                        t0[kk] = fma(a, e.y, fma(b0, e.x, t0[kk]));
-                        t1[kk] = fma(a, e.z, fma(b1, e.x, t1[kk]));
-                        t2[kk] = fma(a, e.w, fma(b2, e.x, t2[kk]));
-                    }
+                const double h = s0 + kq < N ? (r == s ? 1.0 : 0.5) : 0.0;
+                const double va = ag[R], v0 = bg[R], v1 = bg[ystride + R], v2 = bg[2 * ystride + R];
+                nx[0] = h > 0.0 ? h * va : 0.0;
+                nx[1] = h > 0.0 ? h * v0 : 0.0;
+                nx[2] = h > 0.0 ? h * v1 : 0.0;
+                nx[3] = h > 0.0 ? h * v2 : 0.0;
+            };
+            for (int k0 = 0; k0 < n; k0 += 16) {
+                const int kk = min(k0 + l16, n - 1);
+                const d4* col = locc + (size_t)kk * N;
+                d4 t0 = {0.0, 0.0, 0.0, 0.0}, t1 = t0, t2 = t0;
+                load(0);
+                for (int s0 = 0; s0 < N; s0 += 4) {
+                    const double va = nx[0], v0 = nx[1], v1 = nx[2], v2 = nx[3];
+                    const d4 e = col[min(s0 + kq, N - 1)];        // (rho_sk, K_sk)
+                    load(s0 + 4);
+                    t0 = __builtin_amdgcn_mfma_f64_16x16x4f64(va, e.y, t0, 0, 0, 0);
+                    t1 = __builtin_amdgcn_mfma_f64_16x16x4f64(va, e.z, t1, 0, 0, 0);
+                    t2 = __builtin_amdgcn_mfma_f64_16x16x4f64(va, e.w, t2, 0, 0, 0);
+                    t0 = __builtin_amdgcn_mfma_f64_16x16x4f64(v0, e.x, t0, 0, 0, 0);
+                    t1 = __builtin_amdgcn_mfma_f64_16x16x4f64(v1, e.x, t1, 0, 0, 0);
+                    t2 = __builtin_amdgcn_mfma_f64_16x16x4f64(v2, e.x, t2, 0, 0, 0);
                 }
-            }
-            double* tg = T + (size_t)g * 3 * N * n;
+                if (k0 + l16 < n) {
+                    const double m2n = -2.0 * occ.w[kk];
+                    double* tg = T + (size_t)g * 3 * N * n + kk;
 #pragma unroll
-            for (int kk = 0; kk < kAdjOccGroup; ++kk) {
-                if (k0 + kk < n) {
-                    const double m2n = -2.0 * occ.w[k0 + kk];
-                    double* t = tg + r * n + k0 + kk;
-                    t[(size_t)0 * N * n] = (accumulate ? t[(size_t)0 * N * n] : 0.0) + m2n * t0[kk];
-                    t[(size_t)1 * N * n] = (accumulate ? t[(size_t)1 * N * n] : 0.0) + m2n * t1[kk];
-                    t[(size_t)2 * N * n] = (accumulate ? t[(size_t)2 * N * n] : 0.0) + m2n * t2[kk];
+                    for (int v = 0; v < 4; ++v) {
+                        const int ro = r0 + kq + 4 * v;            // logical row l/16 + 4v
+                        if (ro < N) {
+                            double* t = tg + (size_t)ro * n;
+                            const size_t xs = (size_t)N * n;
+                            t[0] = (accumulate ? t[0] : 0.0) + m2n * t0[v];
+                            t[xs] = (accumulate ? t[xs] : 0.0) + m2n * t1[v];
+                            t[2 * xs] = (accumulate ? t[2 * xs] : 0.0) + m2n * t2[v];
+                        }
+                    }
                 }
             }
         }
@@ -399,22 +435,10 @@ __global__ __launch_bounds__(256) void k_pi_grad(const double* __restrict__ Kbar
         for (int b = 0; b < 4; ++b) {
             const int jg = j0 + 16 * b + l16;
             if (jg >= ngp) continue;
-            const d4 pj = pos[jg];
-            const double dx = pi.x - pj.x, dy = pi.y - pj.y, dz = pi.z - pj.z;
-            const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-            if (!(r2 > 0.0)) continue;
-            const double r = sqrt(r2);
-            const double q = 1.0 / (1.0 + r);
-            const double t = r * q;
-            const double s = (dx * acc[0][b][v] + dy * acc[1][b][v] + dz * acc[2][b][v]) * q * q / r;
-            double tp = s;
-#pragma unroll
-            for (int j = 0; j < kGradMax; ++j) {
-                gsum[j] = fma((double)(j + 1), tp, gsum[j]);
-                tp *= t;
-            }
+            pi_grad_point(pi, pos[jg], acc[0][b][v], acc[1][b][v], acc[2][b][v], gsum);
         }
     }
+    pi_grad_factors(gsum);
     __shared__ double red[4][kGradMax];
 #pragma unroll
     for (int j = 0; j < kGradMax; ++j) {

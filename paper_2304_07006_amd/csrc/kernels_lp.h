@@ -988,25 +988,6 @@ __global__ __launch_bounds__(256) void k_pack_kmajor(const double* __restrict__ 
     }
 }
 
-// Gradient epilogue of one Pi value: dL/dc_j gains j t^(j-1) q^2 / r times
-// (r_g - r_g') . Pi(g,g') (power Jastrow, u' = sum_j j c_j t^(j-1) q^2 with
-// t = r q, q = 1/(1+r)); FP64, coincident points skipped.
-__device__ __forceinline__ void pi_grad_point(const d4& pi, const d4& pj, float px, float py, float pz,
-                                              double (&gsum)[16]) {
-    const double dx = pi.x - pj.x, dy = pi.y - pj.y, dz = pi.z - pj.z;
-    const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-    if (!(r2 > 0.0)) return;
-    const double r = sqrt(r2);
-    const double q = 1.0 / (1.0 + r);
-    const double t = r * q;
-    double tp = (dx * (double)px + dy * (double)py + dz * (double)pz) * q * q / r;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        gsum[j] = fma((double)(j + 1), tp, gsum[j]);
-        tp *= t;
-    }
-}
-
 // FP32 Pi tiles with the gradient epilogue (see k_pi_grad):
 // Pi^x(g,g') = sum_P Kbar^x[g][P] rho[g'][P] with FP32 accumulation over all
 // pairs; workgroup 4 waves as 2 (g) x 2 (g'), wave tile 16 g x 128 g' x 3.
@@ -1070,6 +1051,7 @@ __global__ __launch_bounds__(256) void k_pi_grad_lp(const void* __restrict__ Kb,
             pi_grad_point(pi, pos[jg], acc[0][b][v], acc[1][b][v], acc[2][b][v], gsum);
         }
     }
+    pi_grad_factors(gsum);
     __shared__ double red[4][16];
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
@@ -1324,6 +1306,7 @@ __global__ __launch_bounds__(kPiThreads) void k_nt_bf16(const __bf16* __restrict
                     pi_grad_point(pi, pos[jg], acc[0][h][b][v], acc[1][h][b][v], acc[2][h][b][v], gsum);
                 }
             }
+        pi_grad_factors(gsum);
         __shared__ double red[kPiThreads / 64][16];
 #pragma unroll
         for (int j = 0; j < 16; ++j) {

@@ -1120,13 +1120,16 @@ xtc_status xtc_backward(const xtc_problem* pb, const xtc_jastrow* jas, int32_t p
                     return s;
             } else {
                 const int n_it = (rows + 63) / 64, n_jt = L.ldP / 128;
-                for (int y = 0; y < 7; ++y) {
-                    const double* X = y < 3 ? dsrc[y] : rk[y - 3];
-                    double* Yy = y < 3 ? Y + (size_t)y * ystride : Yab + (size_t)(y - 3) * ystride;
-                    hipLaunchKernelGGL(k_gemm_xg_f64, dim3(n_it * n_jt), dim3(256), 0, st, X, (size_t)L.ldP, rows,
-                                       Gm[y < 3 ? t : 2 + t], L.ldP, n_jt, Yy, (size_t)L.ldP, y < 3 ? t : 0);
-                    if ((s = launched("gemm_xg")) != XTC_OK) return s;
+                XgProducts prod;
+                for (int y = 0; y < kXgMax; ++y) {
+                    prod.X[y] = y < 3 ? dsrc[y] : rk[y - 3];
+                    prod.Y[y] = y < 3 ? Y + (size_t)y * ystride : Yab + (size_t)(y - 3) * ystride;
+                    prod.G[y] = Gm[y < 3 ? t : 2 + t];
+                    prod.accumulate[y] = y < 3 ? t : 0;
                 }
+                hipLaunchKernelGGL(k_gemm_xg_f64, dim3(n_it * n_jt, kXgMax), dim3(256), 0, st, prod, rows, L.ldP,
+                                   (int)align_up((size_t)L.Npair, 16), n_jt);
+                if ((s = launched("gemm_xg")) != XTC_OK) return s;
             }
         }
         const size_t lds = (size_t)L.nocc * L.N * 4 * sizeof(double);
@@ -1139,7 +1142,7 @@ xtc_status xtc_backward(const xtc_problem* pb, const xtc_jastrow* jas, int32_t p
             }
         }
         for (int t = 0; t < L.nspin; ++t) {
-            hipLaunchKernelGGL(k_adj_T, dim3(std::min(rows, 4096)), dim3(256), lds, st, rho_rows, Kc,
+            hipLaunchKernelGGL(k_adj_T, dim3(std::min(rows, 16384)), dim3(64 * std::min(4, (L.N + 15) / 16)), lds, st, rho_rows, Kc,
                                Y + (size_t)4 * t * ystride, ystride, rows, L.ldP, L.N, make_occ(pb, t),
                                at<double>(ws, L.T), at<double>(ws, L.Wbar), t);
             if ((s = launched("adj_T")) != XTC_OK) return s;
@@ -1154,7 +1157,7 @@ xtc_status xtc_backward(const xtc_problem* pb, const xtc_jastrow* jas, int32_t p
         if (L.form == 0) {
             nblk_pi = n_it_pi * n_jt_pi;
             hipLaunchKernelGGL(k_pi_grad, dim3(nblk_pi), dim3(256), 0, st, Y, ystride, rows, at<double>(ws, L.rho),
-                               L.ldP, L.ldP, at<d4>(ws, L.pos), g0, L.ngp, n_jt_pi, J.ncoef, at<double>(ws, L.gpart));
+                               L.ldP, (int)align_up((size_t)L.Npair, 16), at<d4>(ws, L.pos), g0, L.ngp, n_jt_pi, J.ncoef, at<double>(ws, L.gpart));
             if ((s = launched("pi_grad")) != XTC_OK) return s;
         } else {
             // Kbar of the chunk to split operands (FP32: row-major; split BF16:

@@ -79,6 +79,33 @@ __device__ __forceinline__ double du_over_r_f64(double r2, const JasDev& J) {
     return r2 > 0.0 ? f : 0.0;
 }
 
+// Gradient epilogue of one Pi value: dL/dc_j gains j t^(j-1) q^2 / r times
+// (r_g - r_g') . Pi(g,g') (power Jastrow, u' = sum_j j c_j t^(j-1) q^2 with
+// t = r q, q = 1/(1+r)); FP64, nothing from coincident points.  gsum[j - 1]
+// collects the terms without their factor j (pi_grad_factors).  Half of
+// the epilogue's instructions were the correctly rounded square root and two
+// divisions.
+__device__ __forceinline__ void pi_grad_point(const d4& pi, const d4& pj, double px, double py, double pz,
+                                              double (&gsum)[16]) {
+    const double dx = pi.x - pj.x, dy = pi.y - pj.y, dz = pi.z - pj.z;
+    const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
+    if (!(r2 > 0.0)) return;
+    const double s = rsq_f64(r2);                 // 1/r
+    const double r = r2 * s;
+    const double q = rcp_f64(1.0 + r);
+    const double t = r * q;
+    double tp = fma(dx, px, fma(dy, py, dz * pz)) * (q * q) * s;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        gsum[j] += tp;
+        tp *= t;
+    }
+}
+__device__ __forceinline__ void pi_grad_factors(double (&gsum)[16]) {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) gsum[j] *= (double)(j + 1);
+}
+
 __device__ __forceinline__ int pair_index(int p, int q, int N) {
     // p <= q
     return p * N - (p * (p - 1)) / 2 + (q - p);
