@@ -168,10 +168,12 @@ __global__ __launch_bounds__(256) void k_make_gbar_open(const double* __restrict
 // (closed shell: Gm = Gbar, symmetric).  blockIdx.y is one of the products of
 // a spin channel: they share their launch, so that a small matrix fills the
 // chip (N=24, 4001 rows: seven launches of 39 us -> one of 176).  Workgroup 4
-// waves as 2 x 2, wave tile 32 (i) x 64 (j).  Each lane loads 4 consecutive k of one row per operand block (32-byte
-// vectors), one 16-k step ahead; MFMA e of a step uses element e, i.e. the k
-// index inside the step is permuted as 4 (l/16) + e identically for both
-// operands.
+// waves as 2 x 2, wave tile 32 (i) x 64 (j).  Each lane loads 4 consecutive k of
+// one row per operand block (32-byte vectors); MFMA e of a 16-k step uses
+// element e, i.e. the k index inside the step is permuted as 4 (l/16) + e
+// identically for both operands.  Three waves per SIMD hide the loads; with
+// registers for four the workgroups in flight outgrow the caches (adjoint N=128,
+// 8000 points, x6: 203 -> 258 ms).
 constexpr int kXgMax = 7;
 struct XgProducts {
     const double* X[kXgMax];
@@ -179,7 +181,7 @@ struct XgProducts {
     double* Y[kXgMax];
     int accumulate[kXgMax];
 };
-__global__ __launch_bounds__(256, 2) void k_gemm_xg_f64(XgProducts prod, int rows, int ldP, int kmax, int n_jt) {
+__global__ __launch_bounds__(256) void k_gemm_xg_f64(XgProducts prod, int rows, int ldP, int kmax, int n_jt) {
     const double* __restrict__ X = prod.X[blockIdx.y];
     const double* __restrict__ Gm = prod.G[blockIdx.y];
     double* __restrict__ Y = prod.Y[blockIdx.y];
@@ -199,22 +201,12 @@ __global__ __launch_bounds__(256, 2) void k_gemm_xg_f64(XgProducts prod, int row
     const double* gr[4];
 #pragma unroll
     for (int b = 0; b < 4; ++b) gr[b] = Gm + (size_t)(j0 + 16 * b + l16) * ldP + kq;
-    d4 xn[2], gn[4];
-    auto load = [&](int k) {
-        const int kk = min(k, kmax - 16);
-#pragma unroll
-        for (int a = 0; a < 2; ++a) xn[a] = *(const d4*)(xr[a] + kk);
-#pragma unroll
-        for (int b = 0; b < 4; ++b) gn[b] = *(const d4*)(gr[b] + kk);
-    };
-    load(0);
     for (int k = 0; k < kmax; k += 16) {
         d4 xa[2], gb[4];
 #pragma unroll
-        for (int a = 0; a < 2; ++a) xa[a] = xn[a];
+        for (int a = 0; a < 2; ++a) xa[a] = *(const d4*)(xr[a] + k);
 #pragma unroll
-        for (int b = 0; b < 4; ++b) gb[b] = gn[b];
-        load(k + 16);
+        for (int b = 0; b < 4; ++b) gb[b] = *(const d4*)(gr[b] + k);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll

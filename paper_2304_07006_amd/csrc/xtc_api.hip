@@ -458,30 +458,38 @@ xtc_status pack_any(int form, const double* src, int nrows, int ld_src, int ncol
     return pack_many(form, PackSrc{{src}}, 1, nrows, ld_src, ncols, n8, ld_dst, dst, split_stride, 0, st);
 }
 
+// Cycles per k-step of a workgroup of `waves` waves of which those that own some
+// of `cols` columns multiply (`blocks` 16-column blocks of `block` MFMA cycles
+// each per 16 rows), on four SIMDs: the active waves' MFMAs, and about 350
+// cycles of generation per wave.
+double lp_step_cycles(int waves, int blocks, int cols, double block) {
+    const int active = std::min(waves, (cols + 16 * blocks - 1) / (16 * blocks));
+    return ((active + 3) / 4) * (waves / 4) * blocks * block + (waves / 4) * 350.0;
+}
+
 // Tile variant of the reduced K build over `rows` rows: the one whose busiest
-// CU needs the fewest cycles per k-step, a workgroup costing its active waves'
-// MFMAs and generation on four SIMDs (about 350 cycles of generation per wave;
-// at least 900 in all, the latency of a step).  0 is the standard tile, which
-// every grid of more than a few rounds takes; N=21 on 1501 rows is 47 workgroups
-// of it (91 us) and 188 of 16 x 128 columns (53 us).
+// CU needs the fewest cycles per k-step (at least 900, the latency of a step).
+// 0 is the standard tile, which every grid of more than a few rounds takes; N=21
+// on 1501 rows is 47 workgroups of it (91 us) and 188 of 16 x 128 columns (53
+// us).
 struct LpVariant {
     int waves, blocks;
 };
 constexpr LpVariant kLpVariants[] = {{8, 0}, {8, 2}, {4, 2}, {4, 1}};   // blocks 0: LpTile's
 int lp_tile(const Layout& L, int rows, int nc, int std_blocks) {
+    const double block = nc * (L.form == 1 ? 8 * 32.0 : L.form * 16.0);   // MFMA cycles of 16 rows x 16 columns
     int best = 0;
     double best_cycles = 1e300;
     for (int i = 0; i < 4; ++i) {
         const int w = kLpVariants[i].waves, nb = i ? kLpVariants[i].blocks : std_blocks;
         const int cols = w * 16 * nb;
-        const int n_ct = (L.Npair + cols - 1) / cols;
-        const long wgs = (long)((rows + 4 * w - 1) / (4 * w)) * n_ct * L.nsegK;
-        const double mfma = (w / 4) * nb * nc * (L.form == 1 ? 8 * 32.0 : L.form * 16.0);
-        const double step = std::max(900.0, (w / 4) * (mfma + 350.0));
-        // co-resident workgroups of the small tiles share the step's latency
-        const double per_cu = (double)((wgs + kCus - 1) / kCus);
-        const double cycles = std::max(step, per_cu * (w / 4) * (mfma + 350.0));
-        if (cycles < 0.85 * best_cycles) {
+        const int full = L.Npair / cols, rem = L.Npair - full * cols;
+        const double tiles = (double)((rows + 4 * w - 1) / (4 * w)) * L.nsegK;   // workgroups per column tile
+        const double step = lp_step_cycles(w, nb, cols, block), last = rem ? lp_step_cycles(w, nb, rem, block) : 0.0;
+        const double busiest = std::ceil(tiles * (full + (rem ? 1 : 0)) / kCus) * (full ? step : last);
+        const double cycles = std::max({900.0, std::min(busiest, tiles * (full * step + last) / kCus + step),
+                                        full ? step : last});
+        if (cycles < 0.8 * best_cycles) {
             best = i;
             best_cycles = cycles;
         }
@@ -489,25 +497,59 @@ int lp_tile(const Layout& L, int rows, int nc, int std_blocks) {
     return best;
 }
 
-template <int KIND, int FORM, int NC, int W, int NB>
-void launch_build_lp_tile(const Layout& L, int g0, int rows, const JasDev& J, void* ws, hipStream_t st) {
-    constexpr int cols = W * 16 * NB;
-    const int n_rt = (rows + 4 * W - 1) / (4 * W);
-    const int n_ct = (L.Npair + cols - 1) / cols;      // columns from Npair on are not read
-    hipLaunchKernelGGL((k_build_K_lp<KIND, FORM, NC, W, NB>), dim3(n_rt * n_ct * L.nsegK), dim3(64 * W), 0, st,
+// The pair columns [coff, ncol) in tiles of one variant.
+template <int KIND, int FORM, int NC, int NW, int NB>
+void launch_build_lp_tile(const Layout& L, int coff, int ncol, int g0, int rows, const JasDev& J, void* ws,
+                          hipStream_t st) {
+    constexpr int cols = NW * 16 * NB;
+    const int n_rt = (rows + 4 * NW - 1) / (4 * NW);
+    const int n_ct = (ncol - coff + cols - 1) / cols;
+    hipLaunchKernelGGL((k_build_K_lp<KIND, FORM, NC, NW, NB>), dim3(n_rt * n_ct * L.nsegK), dim3(64 * NW), 0, st,
                        at<d4>(ws, L.pos), at<void>(ws, L.rho_lp), (size_t)L.ngp * L.ldL, L.ldL, L.ngp, g0, rows, n_rt,
-                       L.segK, J, at<float>(ws, L.Kpart), L.kcap, L.Npair, n_ct, L.nsegK);
+                       L.segK, J, at<float>(ws, L.Kpart), L.kcap, coff, ncol, n_ct, L.nsegK);
+}
+
+// Variant (0: standard) for a last column tile of `cols` < standard columns, by
+// cycles per 32 rows and k-step: its active waves' MFMAs four waves at a time
+// plus everyone's generation, against small tiles whose four waves are all
+// busy.  N=64 ends in 32 pairs of a 512-column tile, N=96 in 48: 5.81 -> 5.53
+// ms for 5000 rows and 40 000 points, 31.8 -> 30.8 ms for 100 000.
+int lp_remainder(const Layout& L, int cols, int nc, int std_blocks) {
+    const double block = nc * (L.form == 1 ? 8 * 32.0 : L.form * 16.0);   // MFMA cycles of 16 rows x 16 columns
+    const int active = (cols + 16 * std_blocks - 1) / (16 * std_blocks);
+    double best_cycles = 0.85 * (((active + 3) / 4) * 2 * std_blocks * block + 700.0);
+    int best = 0;
+    for (int i = 2; i < 4; ++i) {
+        const int nb = kLpVariants[i].blocks;
+        const double c = 2.0 * ((cols + 64 * nb - 1) / (64 * nb)) * (nb * block + 350.0);
+        if (c < best_cycles) {
+            best = i;
+            best_cycles = c;
+        }
+    }
+    return best;
 }
 
 template <int KIND, int FORM, int NC>
 void launch_build_lp(const Layout& L, int g0, int rows, const JasDev& J, void* ws, hipStream_t st) {
     typedef LpTile<KIND, FORM, NC> Std;
-    switch (lp_tile(L, rows, NC, Std::NB)) {
-        case 0: return launch_build_lp_tile<KIND, FORM, NC, Std::NW, Std::NB>(L, g0, rows, J, ws, st);
-        case 1: return launch_build_lp_tile<KIND, FORM, NC, 8, 2>(L, g0, rows, J, ws, st);
-        case 2: return launch_build_lp_tile<KIND, FORM, NC, 4, 2>(L, g0, rows, J, ws, st);
-        default: return launch_build_lp_tile<KIND, FORM, NC, 4, 1>(L, g0, rows, J, ws, st);
-    }
+    constexpr int cols = Std::NW * 16 * Std::NB;
+    const auto part = [&](int variant, int coff, int ncol) {   // columns from Npair on are not read
+        switch (variant) {
+            case 0: return launch_build_lp_tile<KIND, FORM, NC, Std::NW, Std::NB>(L, coff, ncol, g0, rows, J, ws, st);
+            case 1: return launch_build_lp_tile<KIND, FORM, NC, 8, 2>(L, coff, ncol, g0, rows, J, ws, st);
+            case 2: return launch_build_lp_tile<KIND, FORM, NC, 4, 2>(L, coff, ncol, g0, rows, J, ws, st);
+            default: return launch_build_lp_tile<KIND, FORM, NC, 4, 1>(L, coff, ncol, g0, rows, J, ws, st);
+        }
+    };
+    const int variant = lp_tile(L, rows, NC, Std::NB);
+    const int full = L.Npair / cols * cols, rem = L.Npair - full;
+    // (a second launch runs after the first: not worth it within a few rounds)
+    const long wgs = (long)((rows + 4 * Std::NW - 1) / (4 * Std::NW)) * (full / cols) * L.nsegK;
+    const int last = variant == 0 && rem > 0 && wgs >= 4 * kCus ? lp_remainder(L, rem, NC, Std::NB) : 0;
+    if (last == 0) return part(variant, 0, L.Npair);
+    part(0, 0, full);
+    part(last, full, L.Npair);
 }
 
 // The split K build of rows [g0, g0 + rows) (nc = 3: K, or nc = 1: F of the
