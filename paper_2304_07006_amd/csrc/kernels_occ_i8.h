@@ -38,7 +38,9 @@ constexpr int kI8Kb = 64;             // grid points per MFMA k-step
 constexpr int kI8TileB = 64 * 16;     // bytes of one digit tile (64 lanes x 16 bytes)
 constexpr int kI8SegMax = 65536;      // grid points per int32 segment
 constexpr int kI8MaxCT = 9;           // 16-pair column tiles per wave
-constexpr int kI8Waves = 4;
+// Waves per workgroup of a kernel with CT column tiles: eight (two per SIMD)
+// while their accumulators leave registers for that, else four.
+constexpr int i8_waves(int ct) { return ct <= 5 ? 8 : 4; }
 
 // The digit products a_i b_j kept (0-based, i + j <= 5), so ordered that
 // consecutive products share their left operand and add to different orders.
@@ -120,14 +122,14 @@ __global__ __launch_bounds__(256) void k_occ_absmax(const double* __restrict__ r
 // Stage blocks of the main kernel, one per k-step kb and column group:
 // the digit tiles of rho for the group's CT column tiles, [ct][s][lane]
 // (16 bytes each; pairs >= nOP are zero), then the positions (x, y, z, 0)
-// of the 64 points of k-step kb + 1 (zero past the grid), padded to whole
-// 4 KB (one 1 KB chunk per wave and round; the padding is loaded, never
-// read), so that each stage is one contiguous block of kBlockB bytes.
+// of the 64 points of k-steps kb + 1 and kb + 2 (zero past the grid), padded to
+// whole 4 KB (the padding is loaded, never read), so that each stage is one
+// contiguous block of kBlockB bytes.
 template <int CT> struct OccI8Stage {
     static constexpr int kDigitB = CT * kI8Digits * kI8TileB;
-    static constexpr int kUsedB = kDigitB + kI8Kb * 32;
+    static constexpr int kUsedB = kDigitB + 2 * kI8Kb * 32;
     static constexpr int kBlockB = (kUsedB + 4095) / 4096 * 4096;
-    static constexpr int kPerWave = kBlockB / 1024 / kI8Waves;               // 1 KB direct-load chunks
+    static constexpr int kChunks = kBlockB / 1024;                           // 1 KB direct-load chunks
 };
 
 // Digits: one thread per (kb, column tile ct8 of nct8 = groups x CT, lane).
@@ -166,15 +168,15 @@ __global__ __launch_bounds__(256) void k_occ_slice(const double* __restrict__ rh
     }
 }
 
-// Positions: one thread per (kb, group, point).
+// Positions: one thread per (kb, group, point of the two k-steps).
 template <int CT>
 __global__ __launch_bounds__(256) void k_occ_stage_pos(const d4* __restrict__ pos, int ngp, int groups,
                                                        char* __restrict__ stages) {
     typedef OccI8Stage<CT> S;
-    const size_t n = (size_t)(ngp / kI8Kb) * groups * kI8Kb;
+    const size_t n = (size_t)(ngp / kI8Kb) * groups * 2 * kI8Kb;
     for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += (size_t)gridDim.x * blockDim.x) {
-        const int p = (int)(idx % kI8Kb);
-        const size_t kg = idx / kI8Kb;   // kb * groups + group
+        const int p = (int)(idx % (2 * kI8Kb));
+        const size_t kg = idx / (2 * kI8Kb);   // kb * groups + group
         const size_t g = (kg / groups + 1) * kI8Kb + p;
         *(d4*)(stages + kg * S::kBlockB + S::kDigitB + 32 * p) = g < (size_t)ngp ? pos[g] : (d4){0.0, 0.0, 0.0, 0.0};
     }
@@ -186,38 +188,50 @@ constexpr int kI8RawBufferWord3 = 0x00020000;
 // The block for rows [g0, g0 + rows).  Each wave owns one task: 16 rows
 // (row block rb) and one component x of d, for the CT column tiles of column
 // group blockIdx.z, so its accumulators are CT x 6 orders x 4 registers; task
-// 4 blockIdx.x + wave is row block task / 3, component task % 3 (waves past
-// the last task only help load).  blockIdx.y is the segment of seg_kb k-steps.
-// Per k-step a wave generates its 16 rows' d^x for the next 64 points (FP64,
-// then digits; 16 values per lane), while its MFMAs consume the current
-// digits against the staged rho tiles: 21 CT MFMAs per k-step.  Each stage
-// block (stages[kb][group], OccI8Stage) is copied by direct 16-byte
+// W blockIdx.x + wave is row block task / 3, component task % 3 (waves past
+// the last task only help).  blockIdx.y is the segment of seg_kb k-steps.
+// A pipeline of three stages, one barrier per k-step: while the MFMAs consume
+// the digits of k-step t (21 CT of them), the wave makes the digits of its d^x
+// for k-step t + 1 (16 values per lane) from S u'(r)/r, which the workgroup
+// computed together into LDS one k-step before, each value once for its row
+// block's components, and shares in computing that for k-step t + 2.  (Each
+// component's wave computing its own u'/r, half of the VALU work that bounds the
+// kernel, took 11.2 ms for 136 pairs, 7500 rows, 150 000 points and 4.2 ms for 78
+// pairs, 5000 rows, 100 000 points, power Jastrow; now 10.2 and 3.4.)
+// Each stage block (stages[kb][group], OccI8Stage) is copied by direct 16-byte
 // buffer-to-LDS loads one k-step ahead into the other of two statically named
-// buffers.  part[seg][x][r][ldK] = the FP64 value of the
-// segment's sum, for pair columns 16 (blockIdx.z CT + ct) + l % 16.
+// buffers.  part[seg][x][r][ldK] = the FP64 value of the segment's sum, for
+// pair columns 16 (blockIdx.z CT + ct) + l % 16.
 template <int KIND, int CT>
-__global__ __launch_bounds__(256, 1) void k_build_K_occ_i8(const d4* __restrict__ pos, const char* __restrict__ stages,
-                                                           int groups, int ngp, int g0, int rows, int n_rb, JasDev J,
-                                                           double sd, const unsigned long long* __restrict__ amax,
-                                                           double* __restrict__ part, int ldK, int seg_kb) {
+__global__ __launch_bounds__(64 * i8_waves(CT), 1) void k_build_K_occ_i8(
+    const d4* __restrict__ pos, const char* __restrict__ stages, int groups, int ngp, int g0, int rows, int n_rb,
+    JasDev J, double sd, const unsigned long long* __restrict__ amax, double* __restrict__ part, int ldK, int seg_kb) {
     typedef OccI8Stage<CT> S;
     typedef __attribute__((address_space(3))) void* lds_ptr;
+    constexpr int W = i8_waves(CT);
+    constexpr int kSlots = W == 8 ? 4 : 2;               // row blocks that W consecutive tasks can touch
+    constexpr int kPairs = kSlots * 512 / (64 * W);      // pairs of u'/r values per thread and k-step
+    // u'/r of a k-step: [row block][point / 16][pair of points][row][2]
+    typedef double FTile[kSlots][4][8][16][2];
     __shared__ __attribute__((aligned(1024))) char sm0[S::kBlockB];
     __shared__ __attribute__((aligned(1024))) char sm1[S::kBlockB];
-    __shared__ __attribute__((aligned(1024))) char smp[kI8Kb * 32];
+    __shared__ __attribute__((aligned(1024))) char smp[2 * kI8Kb * 32];
+    __shared__ __attribute__((aligned(16))) FTile sF0;
+    __shared__ __attribute__((aligned(16))) FTile sF1;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int task = kI8Waves * blockIdx.x + wave;
+    const int task0 = W * blockIdx.x, task = task0 + wave;
     const int live = __builtin_amdgcn_readfirstlane(task < 3 * n_rb ? 1 : 0);
-    const int rb = live ? task / 3 : 0;
+    const int rb0 = task0 / 3;
+    const int nslots = min(task0 + W - 1, 3 * n_rb - 1) / 3 - rb0 + 1;
+    const int rb = live ? task / 3 : rb0;
     const int comp = live ? task % 3 : 0;
     const int cg = blockIdx.z;
     const int nkb = ngp / kI8Kb;
     const int kb0 = blockIdx.y * seg_kb;
     const int nst = min(seg_kb, nkb - kb0);
-    const int q = lane >> 4;
-    const int my = min(rb * 16 + (lane & 15), rows - 1);
-    const d4 pg = pos[g0 + my];
+    const int q = lane >> 4, l16 = lane & 15;
+    const d4 pg = pos[g0 + min(rb * 16 + l16, rows - 1)];
     const double pc = comp == 0 ? pg.x : comp == 1 ? pg.y : pg.z;
     const double hs = 2097152.0 / sd;   // digits of d / sd from d 2^21 / sd
     const uint32_t loff = 16 * lane;
@@ -228,36 +242,52 @@ __global__ __launch_bounds__(256, 1) void k_build_K_occ_i8(const d4* __restrict_
             (void*)(stages + ((size_t)(kb0 + t) * groups + cg) * S::kBlockB), (short)0, S::kBlockB,
             kI8RawBufferWord3);
 #pragma unroll
-        for (int i = 0; i < S::kPerWave; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(buf + 1024 * (wave + kI8Waves * i)), 16, loff,
-                                                     1024 * (wave + kI8Waves * i), 0, 0);
+        for (int i = 0; i < (S::kChunks + W - 1) / W; ++i)
+            if (S::kChunks % W == 0 || wave + W * i < S::kChunks)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(buf + 1024 * (wave + W * i)), 16, loff,
+                                                         1024 * (wave + W * i), 0, 0);
     };
 
-    // positions 16 q + 4 k + b, b = 0..3, of the k-step whose 64 points are at
-    // p64 (LDS), with the wave's component last
-    struct Pos4 {
-        double x[4], y[4], z[4], c[4];
-    };
-    auto read_pos = [&](const char* p64, int k, Pos4& p) {
+    // u'/r role: pair i of this thread is row block i * W / 8 .., points 16 fq +
+    // 2 fe, + 1, row threadIdx % 16
+    double rx[kSlots], ry[kSlots], rz[kSlots];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const double* cq = (const double*)(p64 + 32 * (16 * q + 4 * k + b));
-            p.x[b] = cq[0];
-            p.y[b] = cq[1];
-            p.z[b] = cq[2];
-            p.c[b] = cq[comp];
+    for (int s = 0; s < kSlots; ++s) {
+        const d4 p = pos[g0 + min((rb0 + s) * 16 + l16, rows - 1)];
+        rx[s] = p.x;
+        ry[s] = p.y;
+        rz[s] = p.z;
+    }
+    auto share = [&](int i, const char* p64, FTile& F) {
+        const int idx = threadIdx.x + 64 * W * i;
+        const int slot = (64 * W * i) / 512;             // uniform: 512 pairs per row block
+        const int fe = (idx >> 4) & 7, fq = (idx >> 7) & 3;
+        const double* c = (const double*)(p64 + 32 * (16 * fq + 2 * fe));
+        double* o = F[slot][fq][fe][l16];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const double dx = rx[slot] - c[4 * b], dy = ry[slot] - c[4 * b + 1], dz = rz[slot] - c[4 * b + 2];
+            const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, kR2FloorF64)));
+            o[b] = du_over_r_nz_f64<KIND>(r2, J, hs);
         }
     };
-    // digits of d^comp for this lane's row and those four points
-    auto gen4 = [&](const Pos4& p, int (&d)[kI8Digits]) {
+    auto share_all = [&](const char* p64, FTile& F) {
+#pragma unroll
+        for (int i = 0; i < kPairs; ++i)
+            if ((64 * W * i) / 512 < nslots) share(i, p64, F);
+    };
+    // digits of d^comp for this lane's row and points 16 q + 4 k + b, b = 0..3,
+    // of the k-step whose positions are at p64 and u'/r in F
+    auto digits4 = [&](const char* p64, const FTile& F, int k, i4 (&A)[kI8Digits]) {
         double h[4];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const double dx = pg.x - p.x[b], dy = pg.y - p.y[b], dz = pg.z - p.z[b];
-            const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, kR2FloorF64)));
-            h[b] = (pc - p.c[b]) * du_over_r_nz_f64<KIND>(r2, J, hs);
-        }
+        for (int b = 0; b < 4; ++b)
+            h[b] = (pc - ((const double*)(p64 + 32 * (16 * q + 4 * k + b)))[comp]) *
+                   F[rb - rb0][q][2 * k + b / 2][l16][b % 2];
+        int d[kI8Digits];
         i8_digits4(h, d);
+#pragma unroll
+        for (int s = 0; s < kI8Digits; ++s) A[s][k] = d[s];
     };
 
     i4 acc[CT][kI8Orders];
@@ -267,37 +297,27 @@ __global__ __launch_bounds__(256, 1) void k_build_K_occ_i8(const d4* __restrict_
         for (int o = 0; o < kI8Orders; ++o) acc[c][o] = (i4){0, 0, 0, 0};
     i4 A[kI8Digits];
 
-    // one k-step from `buf`: the next k-step's digits, the products of this
-    // one, then the wait for this wave's loads of the next stage and the
-    // barrier that publishes everyone's (and ends all reads of this one).  With
-    // two waves per SIMD (CT <= 5) one wave's MFMAs cover the other's generation
-    // (78 pairs, 5000 rows, 100 000 points, power Jastrow: 4.9 -> 4.2 ms with the
-    // shorter digit code).  With one (CT > 5), left to itself the compiler issues
-    // the two one after the other: the k-step then runs in four fenced quarters,
-    // each with a quarter of the MFMAs and the digits of four points, issued as
-    // one MFMA and its share of the VALU work in turn (136 pairs, 7500 rows,
-    // 150 000 points: 13.0 -> 11.2 ms).
-    auto stage = [&](const char* buf) {
+    // one k-step from `buf`, then the wait for this wave's loads of the next
+    // stage and the barrier that publishes everyone's (and ends all reads of
+    // this one).  With two waves per SIMD one wave's MFMAs cover the other's
+    // generation.  With one (CT > 5), left to itself the compiler issues the
+    // two one after the other: the k-step then runs in four fenced quarters,
+    // each with a quarter of the MFMAs and the VALU work, issued as one MFMA
+    // and its share of that work in turn.
+    auto stage = [&](const char* buf, const FTile& R, FTile& F) {
+        const char* pos1 = buf + S::kDigitB;             // positions of k-step t + 1
+        const char* pos2 = pos1 + 32 * kI8Kb;            // and t + 2
+        auto read_b = [&](int c, i4 (&b)[kI8Digits]) {
+#pragma unroll
+            for (int s = 0; s < kI8Digits; ++s)
+                b[s] = *(const i4*)(buf + ((c * kI8Digits + s) * 64 + lane) * 16);
+        };
+        if (!live || CT <= 5) share_all(pos2, F);
         if (live) {
-            auto read_b = [&](int c, i4 (&b)[kI8Digits]) {
-#pragma unroll
-                for (int s = 0; s < kI8Digits; ++s)
-                    b[s] = *(const i4*)(buf + ((c * kI8Digits + s) * 64 + lane) * 16);
-            };
             i4 An[kI8Digits];
-            auto digits4 = [&](const Pos4& p, int k) {
-                int d[kI8Digits];
-                gen4(p, d);
-#pragma unroll
-                for (int s = 0; s < kI8Digits; ++s) An[s][k] = d[s];
-            };
             if constexpr (CT <= 5) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    Pos4 p;
-                    read_pos(buf + S::kDigitB, k, p);
-                    digits4(p, k);
-                }
+                for (int k = 0; k < 4; ++k) digits4(pos1, R, k, An);
 #pragma unroll
                 for (int c = 0; c < CT; ++c) {
                     i4 b[kI8Digits];
@@ -308,18 +328,17 @@ __global__ __launch_bounds__(256, 1) void k_build_K_occ_i8(const d4* __restrict_
                             A[kI8Left[j]], b[kI8Right[j]], acc[c][kI8Left[j] + kI8Right[j]], 0, 0, 0);
                 }
             } else {
+                static_assert(CT <= 5 || kPairs == 4, "one pair of u'/r values per quarter");
                 constexpr int kMfma = kI8Products * CT;
-                constexpr int kValu = KIND == 0 ? 144 : 212;   // VALU instructions of a quarter
+                constexpr int kValu = KIND == 0 ? 112 : 144;   // VALU instructions of a quarter
                 constexpr int kPer = (4 * kValu + kMfma - 1) / kMfma;
                 i4 b[2][kI8Digits];
-                Pos4 p[2];
                 read_b(0, b[0]);
-                read_pos(buf + S::kDigitB, 0, p[0]);
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     __builtin_amdgcn_sched_barrier(0);
-                    if (k < 3) read_pos(buf + S::kDigitB, k + 1, p[(k + 1) & 1]);
-                    digits4(p[k & 1], k);
+                    digits4(pos1, R, k, An);
+                    share(k, pos2, F);
 #pragma unroll
                     for (int m = kMfma * k / 4; m < kMfma * (k + 1) / 4; ++m) {
                         const int c = m / kI8Products, j = m % kI8Products;
@@ -327,6 +346,7 @@ __global__ __launch_bounds__(256, 1) void k_build_K_occ_i8(const d4* __restrict_
                         acc[c][kI8Left[j] + kI8Right[j]] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
                             A[kI8Left[j]], b[c & 1][kI8Right[j]], acc[c][kI8Left[j] + kI8Right[j]], 0, 0, 0);
                     }
+                    __builtin_amdgcn_sched_group_barrier(0x100, 10, 0);         // LDS reads
 #pragma unroll
                     for (int m = kMfma * k / 4; m < kMfma * (k + 1) / 4; ++m) {
                         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // MFMA
@@ -344,34 +364,33 @@ __global__ __launch_bounds__(256, 1) void k_build_K_occ_i8(const d4* __restrict_
     };
 
     if (nst > 0) {
-        // positions of the first k-step (inside the grid), then its stage
+        // positions of the first two k-steps (zero past the grid), then the
+        // first one's stage, u'/r of both and the digits of the first
+        const int left = min(2 * kI8Kb, ngp - kb0 * kI8Kb);
         const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
-            (void*)(pos + (size_t)kb0 * kI8Kb), (short)0, kI8Kb * 32, kI8RawBufferWord3);
-        if (wave < 2)
+            (void*)(pos + (size_t)kb0 * kI8Kb), (short)0, left * 32, kI8RawBufferWord3);
+        if (wave < 4)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rp, (lds_ptr)(smp + 1024 * wave), 16, loff, 1024 * wave, 0, 0);
         issue(0, sm0);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
+        share_all(smp, sF0);
+        share_all(smp + 32 * kI8Kb, sF1);
+        __syncthreads();
         if (live) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                Pos4 p;
-                int d[kI8Digits];
-                read_pos(smp, k, p);
-                gen4(p, d);
-#pragma unroll
-                for (int s = 0; s < kI8Digits; ++s) A[s][k] = d[s];
-            }
+            for (int k = 0; k < 4; ++k) digits4(smp, sF0, k, A);
         }
+        __syncthreads();                                  // before stage 0 writes sF0
     }
     int t = 0;
     for (; t + 1 < nst; t += 2) {
         issue(t + 1, sm1);
-        stage(sm0);
+        stage(sm0, sF1, sF0);
         if (t + 2 < nst) issue(t + 2, sm0);
-        stage(sm1);
+        stage(sm1, sF0, sF1);
     }
-    if (t < nst) stage(sm0);
+    if (t < nst) stage(sm0, sF1, sF0);
 
     if (!live) return;
     double* out = part + (size_t)blockIdx.y * 3 * rows * ldK;

@@ -57,7 +57,7 @@ int balanced_segments(long tiles, long slots, int lo, int hi) {
 }
 
 size_t occ_i8_stage_bytes(const OccI8Plan& plan, int ngp) {
-    const size_t used = (size_t)plan.ct * kI8Digits * kI8TileB + kI8Kb * 32;
+    const size_t used = (size_t)plan.ct * kI8Digits * kI8TileB + 2 * kI8Kb * 32;
     return (size_t)(ngp / kI8Kb) * plan.groups * ((used + 4095) / 4096 * 4096);   // OccI8Stage<ct>::kBlockB
 }
 
@@ -71,7 +71,7 @@ hipError_t prepare_ct(const double* rho_occ, const d4* pos, int ngp, int tw, int
                        rho_occ, ngp, tw, nOP, groups, amax, stages);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const size_t np = (size_t)(ngp / kI8Kb) * groups * kI8Kb;
+    const size_t np = (size_t)(ngp / kI8Kb) * groups * 2 * kI8Kb;
     hipLaunchKernelGGL(k_occ_stage_pos<CT>, dim3((unsigned)std::min<size_t>((np + 255) / 256, 16384)), dim3(256), 0,
                        st, pos, ngp, groups, stages);
     return hipGetLastError();
@@ -110,7 +110,8 @@ int build_ct(const d4* pos, const void* stages, const OccI8Plan& plan, int ngp, 
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)k_build_K_occ_i8<KIND, CT>, 256, 0) !=
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)k_build_K_occ_i8<KIND, CT>, 64 * i8_waves(CT),
+                                                     0) !=
             hipSuccess)
         return 0;
     const int nkb = ngp / kI8Kb;
@@ -118,13 +119,13 @@ int build_ct(const d4* pos, const void* stages, const OccI8Plan& plan, int ngp, 
     const int lo = std::max(4, (nkb + kb_max - 1) / kb_max);
     if (lo > max_seg) return 0;
     const int n_rb = (rows + 15) / 16;
-    const int n_wg = (3 * n_rb + kI8Waves - 1) / kI8Waves;
+    const int n_wg = (3 * n_rb + i8_waves(CT) - 1) / i8_waves(CT);
     const long tiles = (long)n_wg * plan.groups;
     const int want = balanced_segments(tiles, (long)cus * std::max(per_cu, 1), lo, max_seg);
     const int seg_kb = (nkb + want - 1) / want;
     const int nseg = (nkb + seg_kb - 1) / seg_kb;   // every segment starts inside the grid
     hipLaunchKernelGGL((k_build_K_occ_i8<KIND, CT>), dim3((unsigned)n_wg, (unsigned)nseg, (unsigned)plan.groups),
-                       dim3(256), 0, st, pos, (const char*)stages, plan.groups, ngp, g0, rows, n_rb, J,
+                       dim3(64 * i8_waves(CT)), 0, st, pos, (const char*)stages, plan.groups, ngp, g0, rows, n_rb, J,
                        occ_i8_dscale(J), amax, part, ldK, seg_kb);
     return hipGetLastError() == hipSuccess ? nseg : 0;
 }
