@@ -29,7 +29,7 @@
 //   split Gbar, [2][ldP/8][ldP][8])
 // and with XTC_WITH_TC2 (two-body TC integrals; ldN = N^2 rounded up to 128):
 //   Atc [ldP][ldP], Btc [ldN][ldP] FP64 accumulators, Ftc [cap][ldP],
-//   Rg [3][cap][ldN] (w phi grad phi of the chunk)
+//   Rg [3][cap][ldN] (w phi grad phi of the chunk, FP64 form)
 // ldL = ldP rounded up to 512.  The chunk capacity `cap` is the largest
 // multiple of 32 rows that fits in the bytes the caller passes, so every call
 // with the same ws_bytes agrees on it.  The segment partials of the reduced
@@ -229,7 +229,7 @@ Layout make_layout(const xtc_problem* pb, int prec) {
     L.kpart_row = lp ? (size_t)L.nsegK * 3 * L.ldL * sizeof(float) : (size_t)kKSplitMax * 3 * L.ldP * sizeof(double);
     L.kcap_max = lp ? (int)std::max<size_t>(kKpartQuant, kKpartBudget / L.kpart_row / kKpartQuant * kKpartQuant)
                     : (int)(kKpartF64Budget / L.kpart_row);
-    if (L.tc2) L.per_row += (size_t)L.ldP * sizeof(double) + (size_t)3 * L.ldN * sizeof(double);
+    if (L.tc2) L.per_row += (size_t)L.ldP * sizeof(double) + (lp ? 0 : (size_t)3 * L.ldN * sizeof(double));
     if (L.bwd)
         L.per_row += (size_t)(3 + L.nY) * L.ldP * sizeof(double) + (size_t)3 * L.N * L.nocc * sizeof(double) +
                      3 * sizeof(double) + (gslab + 31) / 32 + (lp ? (size_t)7 * L.ns * L.ldP * L.es : 0);
@@ -275,7 +275,7 @@ void place_chunk(Layout& L, size_t bytes) {
     L.gpart = off;   off = align_up(off + (b ? (size_t)((cap + 31) / 32) * gslab : 0), kAlign);
     L.KbL = off;     off = align_up(off + (b && lp ? (size_t)7 * L.ns * cap * L.ldP * L.es : 0), kAlign);
     L.Ftc = off;     off = align_up(off + (L.tc2 ? (size_t)cap * L.ldP * sizeof(double) : 0), kAlign);
-    L.Rg = off;      off = align_up(off + (L.tc2 ? (size_t)3 * cap * L.ldN * sizeof(double) : 0), kAlign);
+    L.Rg = off;      off = align_up(off + (L.tc2 && !lp ? (size_t)3 * cap * L.ldN * sizeof(double) : 0), kAlign);
     L.end = off;
     if (L.end > bytes) L.cap = 0;   // cannot happen by construction; refuse rather than overrun
 }
@@ -1360,17 +1360,17 @@ xtc_status xtc_tc_2body(const xtc_problem* pb, const xtc_jastrow* jas, const dou
         return s;
     }
     if ((s = launched("build_F")) != XTC_OK) return s;
-    double* Rg = at<double>(ws, L.Rg);
-    const size_t xs = (size_t)L.cap * L.ldN;
-    const size_t nrg = (size_t)rows * L.ldN;
-    hipLaunchKernelGGL(k_rhog, dim3((unsigned)std::min<size_t>((nrg + 255) / 256, 16384)), dim3(256), 0, st, pb->w,
-                       pb->phi, dphi, L.N, L.Ng, g0, rows, L.ldN, xs, Rg);
-    if ((s = launched("rhog")) != XTC_OK) return s;
     const int acc = (flags & XTC_RESET) ? 0 : 1;
     const double* rho_rows = at<double>(ws, L.rho) + (size_t)g0 * L.ldP;
     double* Atc = at<double>(ws, L.Atc);
     double* Btc = at<double>(ws, L.Btc);
     if (L.form == 0) {
+        double* Rg = at<double>(ws, L.Rg);
+        const size_t xs = (size_t)L.cap * L.ldN;
+        const size_t nrg = (size_t)rows * L.ldN;
+        hipLaunchKernelGGL(k_rhog, dim3((unsigned)std::min<size_t>((nrg + 255) / 256, 16384)), dim3(256), 0, st, pb->w,
+                           pb->phi, dphi, L.N, L.Ng, g0, rows, L.ldN, xs, Rg);
+        if ((s = launched("rhog")) != XTC_OK) return s;
         if ((s = gemm_tn_f64(L, TnOperand{rho_rows, rho_rows, 0, L.ldP}, TnOperand{F, F, 0, L.ldP}, 1, rows, L.Npair,
                              L.Npair, Atc, L.ldP, acc, ws, st)) != XTC_OK)
             return s;
@@ -1393,8 +1393,10 @@ xtc_status xtc_tc_2body(const xtc_problem* pb, const xtc_jastrow* jas, const dou
             return s;
         char* kd = cd + 3 * cN;
         const size_t ks = (size_t)rows * L.ldP;
-        if ((s = pack_many(L.form, PackSrc{{Rg, Rg + xs, Rg + 2 * xs}}, 3, rows, L.ldN, L.ldN, n8, L.ldN, cd, sN,
-                           L.ns * sN, st)) != XTC_OK ||
+        const auto rhog = L.form == 1 ? k_pack_rhog<1> : L.form == 3 ? k_pack_rhog<3> : k_pack_rhog<6>;
+        hipLaunchKernelGGL(rhog, dim3((L.ldN + 255) / 256, n8, 3), dim3(256), 0, st, pb->w, pb->phi, dphi, L.N, L.Ng, g0,
+                           rows, L.ldN, cd, sN, L.ns * sN);
+        if ((s = launched("pack_rhog")) != XTC_OK ||
             (s = pack_many(L.form, PackSrc{{K, K + ks, K + 2 * ks}}, 3, rows, L.ldP, L.ldP, n8, L.ldL, kd, sL,
                            L.ns * sL, st)) != XTC_OK)
             return s;
