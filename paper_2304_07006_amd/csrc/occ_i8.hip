@@ -35,6 +35,7 @@ double occ_i8_dscale(const JasDev& J) {
     const double u = (gmax + 0.5 * lip / kGrid) * (1.0 + 1e-12);   // + the rounding of this evaluation
     if (!(u < 1e300)) return 0.0;   // no usable bound (coefficients near the FP64 range)
     if (!(u > 0.0)) return 1.0;
+    if (u < 1e-290) return 0.0;     // 2^21 / S_d leaves the FP64 range below 1e-302
     int e = 0;
     const double f = std::frexp(2.0 * u, &e);   // 2u = f 2^e, f in [0.5, 1)
     return f == 0.5 ? 2.0 * u : std::ldexp(1.0, e);

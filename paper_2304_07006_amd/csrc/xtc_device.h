@@ -50,8 +50,9 @@ __device__ __forceinline__ double rcp_f64(double x) {
 // d^x = (x - x') u'(r)/r the caller adds kR2FloorF64 to r^2: the value stays
 // finite at coincident points, where the difference vector it multiplies is
 // exactly zero (the gradient of an isotropic function is taken as 0 there), and
-// the floor is below the last bit of r^2 for every r above 1e-137.  (The value
-// at the floor is about 1e145 scale u': `scale` has to keep that finite.)
+// the floor is below the last bit of r^2 for every r above 1e-137.  `scale` is
+// the reciprocal size of u' and multiplies it first: 1/r at the floor is 1e145,
+// and scale / r by itself overflows for |u'| below 1e-157.
 //   Pade : u = r/(2(1+br))      -> u'/r = 1 / (2 r (1+br)^2)
 //   power: u = sum c_k t^k      -> u'/r = (sum k c_k t^(k-1)) / (r (1+r)^2)
 constexpr double kR2FloorF64 = 1e-290;
@@ -68,7 +69,7 @@ __device__ __forceinline__ double du_over_r_nz_f64(double r2, const JasDev& J, d
         double p = J.dcoef[15];
 #pragma unroll
         for (int k = 14; k >= 0; --k) p = fma(p, t, J.dcoef[k]);
-        return (p * (scale * s)) * (q * q);
+        return ((p * scale) * s) * (q * q);
     }
 }
 
