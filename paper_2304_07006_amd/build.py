@@ -41,11 +41,14 @@ def build(verbose: bool = False, out: str | None = None, sanitize: bool = False)
     sanitizers (a checking build, not the product library)."""
     lib = out or LIB
     tmp = lib + ".tmp"
+    # objects, and what an interrupted compiler leaves beside them, stay in an ignored folder
+    objdir = os.path.join(os.path.dirname(os.path.abspath(lib)), "_build")
+    os.makedirs(objdir, exist_ok=True)
     extra = SANITIZE_FLAGS if sanitize else []
     objs, log = [], []
     jobs = []   # the units compile side by side
     for src, own in UNITS:
-        obj = f"{tmp}.{os.path.splitext(os.path.basename(src))[0]}.o"
+        obj = os.path.join(objdir, f"{os.path.basename(lib)}.{os.path.splitext(os.path.basename(src))[0]}.o")
         objs.append(obj)
         cmd = [HIPCC, *FLAGS, *own, *extra, "-c", src, "-o", obj]
         jobs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
