@@ -23,8 +23,8 @@
  *     are written as zero and otherwise ignored.
  *   - All array pointers are DEVICE pointers owned by the caller unless marked
  *     HOST.  The library never allocates, frees or retains caller memory.
- *   - Scratch memory is a caller-provided device workspace of at least
- *     xtc_workspace_size() bytes (256-byte aligned).  Between xtc_prepare and
+ *   - Scratch memory is a caller-provided device workspace of
+ *     xtc_workspace_size() bytes (256-byte aligned; see there for less).  Between xtc_prepare and
  *     the last call of a pass it carries state (the prepared operands and the
  *     FP64 accumulators of the two- and one-body terms); do not share one
  *     workspace between passes that overlap in time.
@@ -170,9 +170,16 @@ typedef struct {
 /* Padded leading dimension of pair-indexed arrays: Npair rounded up to 128. */
 int32_t xtc_pair_ld(int32_t N);
 
-/* Bytes of workspace needed for problem `pb` with contraction arithmetic
- * `prec` and grid chunks of at most `chunk_rows` rows (1 <= chunk_rows <= Ng).
- * Returns 0 for invalid arguments (message in xtc_last_error()). */
+/* Bytes of workspace for problem `pb` with contraction arithmetic `prec` and
+ * grid chunks of at most `chunk_rows` rows (1 <= chunk_rows <= Ng).  Returns 0
+ * for invalid arguments (message in xtc_last_error()).
+ * In FP64 without XTC_WITH_BACKWARD the count includes the segment partials of
+ * launches whose matrices are too small to fill the chip (at most 192 MiB; N = 8
+ * on 2000 points: 10.4 MiB without and 18.2 with them, N = 64 on 20 000: 1709
+ * and 1817, none from N = 96 on).  A call takes any workspace that holds its rows
+ * without them (XTC_E_WORKSPACE below that): the partials it finds room for
+ * then decide how its sums are split, which changes their speed and, in the
+ * rounding of the FP64 sums, their last bits. */
 size_t xtc_workspace_size(const xtc_problem *pb, int32_t prec, int32_t chunk_rows);
 
 /* Prepare a pass: tabulate the weighted pair densities rho_pq(g) = w_g phi_p phi_q

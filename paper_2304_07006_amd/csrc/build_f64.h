@@ -20,16 +20,22 @@ struct KF64Plan {
 // work per useful column is least, with ncol <= ld.
 KF64Plan kf64_columns(int cols, int ld);
 
-// The whole plan for rows x cols outputs and ngp points, at most max_seg
-// segments (max_seg = 1: no partials).
-KF64Plan kf64_plan(int cols, int ld, int rows, int ngp, int max_seg);
+// The whole plan for rows x cols outputs and ngp points: at most max_seg
+// segments, and only as many as have partials within max_bytes.
+KF64Plan kf64_plan(int cols, int ld, int rows, int ngp, int max_seg, size_t max_bytes);
+
+// Bytes of a plan's segment partials (0 with one segment: none).
+size_t kf64_part_bytes(const KF64Plan& p, int rows);
 
 // The segments of an already tiled build (nb, cw, ncol of p are kept).
 KF64Plan kf64_segments(KF64Plan p, int rows, int ngp, int max_seg);
 
 // K^x_P(g) of rows [g0, g0 + rows) against rho [ngp][ld]: out[x][r][ldo] with
 // zeros in the columns [ncol, ldo) if nseg == 1, else the partials
-// out[seg][x][r][ncol].  Returns the launch status.
+// out[seg][x][r][ncol].  ncol may exceed ld (the occupied pairs, whose rows are
+// packed to 16 columns): the columns from ld on then hold sums of other bits,
+// and up to ncol - ld doubles behind the last row of rho are read, which the
+// caller provides.  Returns the launch status.
 hipError_t kf64_build(const d4* pos, const double* rho, int ld, int ngp, int g0, int rows, const JasDev& J,
                       const KF64Plan& p, double* out, int ldo, hipStream_t st);
 

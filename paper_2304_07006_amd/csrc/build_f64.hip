@@ -76,7 +76,7 @@ KF64Plan kf64_segments(KF64Plan p, int rows, int ngp, int max_seg) {
     return best;
 }
 
-KF64Plan kf64_plan(int cols, int ld, int rows, int ngp, int max_seg) {
+KF64Plan kf64_plan(int cols, int ld, int rows, int ngp, int max_seg, size_t max_bytes) {
     KF64Plan best{0, 0, 0, 0, 0};
     double best_cycles = 1e300;
     for (int nb = 1; nb <= 8; ++nb)
@@ -84,7 +84,8 @@ KF64Plan kf64_plan(int cols, int ld, int rows, int ngp, int max_seg) {
             const int tile = 16 * nb * cw;
             KF64Plan p{nb, cw, (cols + tile - 1) / tile * tile, 1, ngp};
             if (p.ncol > ld) continue;
-            p = kf64_segments(p, rows, ngp, max_seg);
+            const size_t fit = max_bytes / ((size_t)3 * rows * p.ncol * sizeof(double));
+            p = kf64_segments(p, rows, ngp, (int)std::min<size_t>(max_seg, fit));
             const double c = build_cycles(p, rows, ngp);
             if (c < best_cycles) {
                 best_cycles = c;
@@ -92,6 +93,10 @@ KF64Plan kf64_plan(int cols, int ld, int rows, int ngp, int max_seg) {
             }
         }
     return best;
+}
+
+size_t kf64_part_bytes(const KF64Plan& p, int rows) {
+    return p.nseg > 1 ? (size_t)p.nseg * 3 * rows * p.ncol * sizeof(double) : 0;
 }
 
 namespace {
@@ -127,8 +132,8 @@ hipError_t launch_nb(const d4* pos, const double* rho, int ld, int ngp, int g0, 
 
 hipError_t kf64_build(const d4* pos, const double* rho, int ld, int ngp, int g0, int rows, const JasDev& J,
                       const KF64Plan& p, double* out, int ldo, hipStream_t st) {
-    // the kernel assumes whole column tiles inside ld, whole stages and a grid of whole stages
-    if (rows < 1 || p.ncol > ld || (p.nseg == 1 ? ldo < p.ncol : ldo != p.ncol) || p.seg_len % kKSegQuant ||
+    // the kernel assumes whole column tiles, whole stages and a grid of whole stages
+    if (rows < 1 || ld < 16 || ld % 16 || (p.nseg == 1 ? ldo < p.ncol : ldo != p.ncol) || p.seg_len % kKSegQuant ||
         ngp % kKSegQuant || (long)(p.nseg - 1) * p.seg_len >= ngp || (p.cw != 2 && p.cw != 4) ||
         p.ncol % (16 * p.nb * p.cw))
         return hipErrorInvalidValue;

@@ -198,6 +198,11 @@ __global__ __launch_bounds__(256) void k_intermediates(const double* __restrict_
                     }
                 }
         }
+        // padding columns (the adjoint sums over whole 16-column blocks of D)
+        for (int P = N * (N + 1) / 2 + threadIdx.x; P < ldP; P += nt) {
+            double* dg = D + (size_t)g * ldP + P;
+            dg[0] = dg[dstride] = dg[2 * dstride] = dg[3 * dstride] = 0.0;
+        }
         __syncthreads();
     }
 }

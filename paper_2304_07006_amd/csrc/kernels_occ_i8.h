@@ -119,17 +119,19 @@ __global__ __launch_bounds__(256) void k_occ_absmax(const double* __restrict__ r
     }
 }
 
-// Stage blocks of the main kernel, one per k-step kb and column group:
-// the digit tiles of rho for the group's CT column tiles, [ct][s][lane]
-// (16 bytes each; pairs >= nOP are zero), then the positions (x, y, z, 0)
-// of the 64 points of k-steps kb + 1 and kb + 2 (zero past the grid), padded to
-// whole 4 KB (the padding is loaded, never read), so that each stage is one
-// contiguous block of kBlockB bytes.
+// Stage blocks of the main kernel, one per k-step kb and column group: the
+// digit tiles of rho for the group's CT column tiles, [ct][s][lane] (16 bytes
+// each; pairs >= nOP are zero).  In LDS the positions (x, y, z, 0) of the 64
+// points of k-steps kb + 1 and kb + 2 (zero past the grid) stand behind them,
+// and padding to whole 8 KB, one 1 KB chunk per wave and round (4 KB with four
+// waves), so that the loads are the same straight line for every wave: with a
+// branch for the position chunks a chunk of 7500 rows at N=128 took 141.1
+// instead of 140.6 ms.
 template <int CT> struct OccI8Stage {
     static constexpr int kDigitB = CT * kI8Digits * kI8TileB;
-    static constexpr int kUsedB = kDigitB + 2 * kI8Kb * 32;
-    static constexpr int kBlockB = (kUsedB + 4095) / 4096 * 4096;
-    static constexpr int kChunks = kBlockB / 1024;                           // 1 KB direct-load chunks
+    static constexpr int kDigitChunks = kDigitB / 1024;                      // 1 KB direct-load chunks
+    static constexpr int kRounds = (kDigitChunks + 2 * kI8Kb * 32 / 1024 + i8_waves(CT) - 1) / i8_waves(CT);
+    static constexpr int kBlockB = 1024 * i8_waves(CT) * kRounds;            // in LDS
 };
 
 // Digits: one thread per (kb, column tile ct8 of nct8 = groups x CT, lane).
@@ -161,24 +163,10 @@ __global__ __launch_bounds__(256) void k_occ_slice(const double* __restrict__ rh
 #pragma unroll
             for (int s = 0; s < kI8Digits; ++s) w[s][k] = d[s];
         }
-        char* blk = stages + (kb * groups + ct8 / CT) * S::kBlockB + (size_t)(ct8 % CT) * kI8Digits * kI8TileB;
+        char* blk = stages + (kb * groups + ct8 / CT) * S::kDigitB + (size_t)(ct8 % CT) * kI8Digits * kI8TileB;
 #pragma unroll
         for (int s = 0; s < kI8Digits; ++s)
             *(i4*)(blk + (s * 64 + lane) * 16) = (i4){w[s][0], w[s][1], w[s][2], w[s][3]};
-    }
-}
-
-// Positions: one thread per (kb, group, point of the two k-steps).
-template <int CT>
-__global__ __launch_bounds__(256) void k_occ_stage_pos(const d4* __restrict__ pos, int ngp, int groups,
-                                                       char* __restrict__ stages) {
-    typedef OccI8Stage<CT> S;
-    const size_t n = (size_t)(ngp / kI8Kb) * groups * 2 * kI8Kb;
-    for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += (size_t)gridDim.x * blockDim.x) {
-        const int p = (int)(idx % (2 * kI8Kb));
-        const size_t kg = idx / (2 * kI8Kb);   // kb * groups + group
-        const size_t g = (kg / groups + 1) * kI8Kb + p;
-        *(d4*)(stages + kg * S::kBlockB + S::kDigitB + 32 * p) = g < (size_t)ngp ? pos[g] : (d4){0.0, 0.0, 0.0, 0.0};
     }
 }
 
@@ -198,9 +186,9 @@ constexpr int kI8RawBufferWord3 = 0x00020000;
 // component's wave computing its own u'/r, half of the VALU work that bounds the
 // kernel, took 11.2 ms for 136 pairs, 7500 rows, 150 000 points and 4.2 ms for 78
 // pairs, 5000 rows, 100 000 points, power Jastrow; now 10.2 and 3.4.)
-// Each stage block (stages[kb][group], OccI8Stage) is copied by direct 16-byte
-// buffer-to-LDS loads one k-step ahead into the other of two statically named
-// buffers.  part[seg][x][r][ldK] = the FP64 value of the segment's sum, for
+// Each stage block (stages[kb][group], OccI8Stage) and the positions behind it
+// are copied by direct 16-byte buffer-to-LDS loads one k-step ahead into the
+// other of two statically named buffers.  part[seg][x][r][ldK] = the FP64 value of the segment's sum, for
 // pair columns 16 (blockIdx.z CT + ct) + l % 16.
 template <int KIND, int CT>
 __global__ __launch_bounds__(64 * i8_waves(CT), 1) void k_build_K_occ_i8(
@@ -238,14 +226,21 @@ __global__ __launch_bounds__(64 * i8_waves(CT), 1) void k_build_K_occ_i8(
 
     // stage t: the block of k-step kb0 + t
     auto issue = [&](int t, char* buf) {
+        const int kb = kb0 + t;
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            (void*)(stages + ((size_t)(kb0 + t) * groups + cg) * S::kBlockB), (short)0, S::kBlockB,
+            (void*)(stages + ((size_t)kb * groups + cg) * S::kDigitB), (short)0, S::kDigitB, kI8RawBufferWord3);
+        // positions past the grid's last point read as zero
+        const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(pos + (size_t)(kb + 1) * kI8Kb), (short)0, 32 * min(2 * kI8Kb, ngp - (kb + 1) * kI8Kb),
             kI8RawBufferWord3);
 #pragma unroll
-        for (int i = 0; i < (S::kChunks + W - 1) / W; ++i)
-            if (S::kChunks % W == 0 || wave + W * i < S::kChunks)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(buf + 1024 * (wave + W * i)), 16, loff,
-                                                         1024 * (wave + W * i), 0, 0);
+        for (int i = 0; i < S::kRounds; ++i) {
+            const int off = 1024 * (wave + W * i);
+            // (chunks past the positions read as zero)
+            const bool digits = W * (i + 1) <= S::kDigitChunks || off < S::kDigitB;
+            const int src = digits ? off : off - S::kDigitB;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(digits ? rs : rp, (lds_ptr)(buf + off), 16, loff, src, 0, 0);
+        }
     };
 
     // u'/r role: pair i of this thread is row block i * W / 8 .., points 16 fq +

@@ -38,10 +38,9 @@ int balanced_segments(long tiles, long slots, int lo, int hi);
 size_t occ_i8_stage_bytes(const OccI8Plan& plan, int ngp);
 
 // Stage blocks of the occupied pairs' rho (nct8 x 16 pair columns, ngp
-// points) from rho_occ (column tiles of tw pairs, [ngp][tw] each) and the
-// positions pos [ngp].  amax (16 nct8 entries) must hold zeros; it receives
+// points) from rho_occ (column tiles of tw pairs, [ngp][tw] each).  amax (16 nct8 entries) must hold zeros; it receives
 // the per-pair largest |rho|.  Returns the launch status.
-hipError_t occ_i8_prepare(const double* rho_occ, const d4* pos, int ngp, int tw, int nOP, const OccI8Plan& plan,
+hipError_t occ_i8_prepare(const double* rho_occ, int ngp, int tw, int nOP, const OccI8Plan& plan,
                           unsigned long long* amax, void* stages, hipStream_t st);
 
 // The block for rows [g0, g0 + rows): FP64 segment partials

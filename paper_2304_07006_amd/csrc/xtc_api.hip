@@ -11,33 +11,46 @@
 //                                     of the integer occupied block (occ_i8.h)
 //   M      [ldP][ldP] doubles         FP64 accumulator of the two-body term
 //   h1acc  [ldP] doubles              FP64 accumulator of the one-body term
-//   T1     [kT1SplitMax][ldP] doubles per-split partials (one-body, term 1)
+//   T1     [kT1Split][ldP] doubles    per-split partials (one-body, term 1)
 //   E      [kESplit][N][N] doubles    per-split partials (one-body, exchange)
-//   S      [cap][8] doubles           per-point scalars of the current chunk
-//   D      [4][cap][ldP] doubles      A, Bx, By, Bz of the current chunk
-//   Kpart  [nsegK][3][kcap][ldL] f32  K-build segment partials of kcap rows (prec != FP64; FP64: FP64 partials
-//          of a K build split over g', at most kKpartF64Budget bytes)
-//   CDlp   [8][NS][cap/8][ldL][8]     C and D of the chunk, k8-packed (prec != FP64)
-//   Mpart  [group][4][ldL][ldL] f32   two-body partials of a group of row segments
-//          (FP64: partials of a row-split product, at most kMpartF64Budget bytes)
-// and with XTC_WITH_BACKWARD in prec (the adjoint reuses M for Gbar):
-//   Kc [3][cap][ldP], Y [7][cap][ldP], T [cap][3][N][nocc], Wbar [cap][3],
-//   gpart [ceil(cap/32) * ngp/128][16], gacc [16], occw [N] f64, kidx [N],
+// with XTC_WITH_BACKWARD in prec (the adjoint reuses M for Gbar):
+//   gacc [16], occw [N] f64, kidx [N],
 //   reduced forms: rhoR (split rho: FP32 row-major [1][ngp][ldP], split BF16
-//   k-packed [NS][ldP/8][ngp][8]), KbL [7][NS][cap * ldP] (split operands of
-//   the chunk, same two layouts), split-BF16 3-product form: GsL (k-packed
+//   k-packed [NS][ldP/8][ngp][8]), split-BF16 3-product form: GsL (k-packed
 //   split Gbar, [2][ldP/8][ldP][8])
-// and with XTC_WITH_TC2 (two-body TC integrals; ldN = N^2 rounded up to 128):
-//   Atc [ldP][ldP], Btc [ldN][ldP] FP64 accumulators, Ftc [cap][ldP],
-//   Rg [3][cap][ldN] (w phi grad phi of the chunk, FP64 form)
-// ldL = ldP rounded up to 512.  The chunk capacity `cap` is the largest
-// multiple of 32 rows that fits in the bytes the caller passes, so every call
-// with the same ws_bytes agrees on it.  The segment partials of the reduced
-// forms are bounded: the K build runs over a chunk in equal row pieces of at
-// most kcap rows (kcap = min(cap, the multiple of 1024 rows whose partials
-// fit kKpartBudget bytes, at least 1024)), and the two-body GEMM over groups of
-// row segments, each piece reduced into its FP64 result before the
-// next one reuses the partial buffer.
+// with XTC_WITH_TC2 (two-body TC integrals; ldN = N^2 rounded up to 128):
+//   Atc [ldP][ldP], Btc [ldN][ldP] FP64 accumulators
+// All of that has one place for every call on a workspace.  What follows is laid
+// out by each call for its own number of rows (`crows`, a multiple of 32):
+//   Kc     [3][crows][ldP] doubles    K of a chunk of the adjoint
+//   Ftc    [crows][ldP] doubles       F of the TC integrals
+//   S      [crows][8] doubles         per-point scalars of the chunk
+//   D      [4][crows][ldP] doubles    A, Bx, By, Bz of the chunk
+//   Rg     [3][crows][ldN] doubles    w phi grad phi (TC integrals, FP64 form)
+//   CDlp   [8][NS][crows/8][ldL][8]   C and D of the chunk, k8-packed (prec != FP64)
+//   scratch: everything from there to the end of the workspace.
+// S and D are the only ones that outlive a call: xtc_contract_2body leaves them
+// to an xtc_contract_1body_0body with XTC_REUSE_INTERMEDIATES on the same rows,
+// with no call in between.  The K build therefore takes its segment partials
+// (Kpart [nsegK][3][kcap][ldL] f32, or FP64 ones, and those of the occupied
+// block) from S to the end; the two-body products (Mpart: [group][4][ldL][ldL]
+// f32, or FP64 ones), term 1 of the one-body sum and V2's packed sums take the
+// scratch; and the adjoint, which has no two-body products, keeps
+//   Y [7][crows][ldP], T [crows][3][N][nocc], Wbar [crows][3],
+//   gpart [ceil(crows/32) * ngp/128][16], KbL [7][NS][crows * ldP] (split operands
+//   of the chunk, in rhoR's two layouts)
+// there.
+// ldL = ldP rounded up to 512.  The chunk capacity `cap` is the largest multiple
+// of 32 rows whose buffers fit in the bytes the caller passes (layout_bytes).
+// Segment partials beyond the least that a product needs only make it faster:
+// xtc_workspace_size adds what the launch plans would use (plan_extra), and a
+// smaller workspace, or a chunk longer than it was sized for, gets plans with
+// fewer segments.
+// The segment partials of the reduced forms are bounded: the K build runs over a
+// chunk in equal row pieces of at most kcap rows (kcap = min(crows, the multiple
+// of 1024 rows whose partials fit kKpartBudget bytes, at least 1024)), and the
+// two-body GEMM over groups of row segments, each piece reduced into its FP64
+// result before the next one reuses the partial buffer.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -77,7 +90,7 @@ xtc_status fail(xtc_status st, const char* fmt, ...) {
     return st;
 }
 
-constexpr int kT1Split = 64, kT1SplitMax = 256;
+constexpr int kT1Split = 64, kT1SplitMax = 256;   // row splits of term 1 (one-body): in T1, and in the scratch
 constexpr int kESplitMax = 256;
 constexpr size_t kAlign = 256;
 constexpr int kMaxN = 256;
@@ -110,7 +123,7 @@ constexpr int kOccSegMax = 32;  // most segments of the FP64 occupied-block sum 
 constexpr size_t kKpartBudget = (size_t)16 << 30;  // bytes of K-build segment partials
 constexpr int kKpartQuant = 1024;                  // rows: 32 row tiles, one XCD's resident set
 // Row segments per two-body GEMM launch: two, and for smaller matrices as many
-// (up to kMSegGroupMax) as fit kMpartBudget bytes of partials, so that a launch
+// (up to kMSegGroupMax) as fit the scratch and kMpartBudget bytes, so that a launch
 // has rounds enough of workgroups (N=48 in FP32, 4000 rows: four launches of 400
 // workgroups, the second round of each half empty, 173 us each; one of 1600
 // takes 654).
@@ -129,25 +142,25 @@ constexpr int kCus = 256;                          // compute units of an MI355X
 struct Layout {
     int N, Ng, nocc, ldP, ngp, Npair, prec;
     int form, ns, es, ldL, ldO, nOP, nsegK, nspin, ldN, segK, segM;
-    KF64Plan occ64;      // column tiling of the FP64 occupied block (ldO columns)
+    KF64Plan occ64;      // column tiling of the FP64 occupied block (ldO: the pairs rounded up to 16)
     int nY;              // adjoint Y slots: Cbar (3), then Abar, Bbar (4) per spin channel
     OccI8Plan i8;        // column tiling of the integer occupied block
     bool i8ok;           // one column group and the grid fits its int32 segments (else the FP64 block serves)
     int ldK8;            // row stride of its segment partials (16 i8.nct8)
     bool tc2;
     bool bwd;
-    size_t pos, rho, rho_lp, rho_occ, colmap, stg, amax, M, h1acc, T1, E, gacc, occw, kidx, rhoR, GsL, Atc, Btc, GT;
+    size_t pos, rho, rho_lp, rho_occ, colmap, stg, amax, M, h1acc, T1, E, e_end, gacc, occw, kidx, rhoR, GsL, Atc, Btc, GT;
     size_t fixed;        // bytes of everything that does not scale with the chunk rows (plus reserves)
-    size_t chunk0;       // offset of the first chunk buffer (S)
+    size_t chunk0;       // offset of the first chunk buffer (Kc)
     size_t per_row;      // bytes per chunk row (without the K-build partials)
-    size_t kpart_row;    // bytes per row of the K-build partials
+    size_t kpart_row;    // bytes per row of the K-build partials (reduced forms)
     int kcap_max;        // most rows of one K-build piece
     int cap;             // chunk rows that fit (multiple of kRowQuant)
-    int kcap;            // rows of the K-build partial buffer: min(cap, kcap_max)
+    int crows;           // rows of this call's chunk buffers
+    int kcap;            // rows of the K-build partial buffer: min(crows, kcap_max)
     size_t mslab;        // bytes of the two-body partials of one segM-row segment
     size_t cdw;          // packed operand elements per row and split (CDlp)
-    size_t mpart;        // bytes of the two-body partial buffer (Mpart)
-    size_t S, D, Kpart, CDlp, Mpart, Kocc, Kc, Y, T, Wbar, gpart, KbL, Ftc, Rg, end;
+    size_t Kc, Ftc, S, D, Rg, CDlp, scr, Y, T, Wbar, gpart, KbL, end;
 };
 
 int form_of(int prec) {
@@ -171,7 +184,7 @@ Layout make_layout(const xtc_problem* pb, int prec) {
     L.ldL = (int)align_up((size_t)L.ldP, kLpCols);
     L.nOP = pb->nocc * (pb->nocc + 1) / 2;
     L.occ64 = kf64_columns(L.nOP, 1 << 30);
-    L.ldO = L.occ64.ncol;
+    L.ldO = (int)align_up((size_t)L.nOP, 16);
     L.i8 = occ_i8_plan(L.nOP);
     // the integer block serves one column group (at most 144 occupied pairs):
     // with two, each of them regenerates d's digits, and at N=160 with 20
@@ -197,8 +210,9 @@ Layout make_layout(const xtc_problem* pb, int prec) {
     L.amax = off;    off = align_up(off + (i8 ? (size_t)L.ldK8 * sizeof(double) : 0), kAlign);
     L.M = off;       off = align_up(off + (size_t)L.nspin * L.ldP * L.ldP * sizeof(double), kAlign);
     L.h1acc = off;   off = align_up(off + (size_t)L.nspin * L.ldP * sizeof(double), kAlign);
-    L.T1 = off;      off = align_up(off + (size_t)kT1SplitMax * L.ldP * sizeof(double), kAlign);
+    L.T1 = off;      off = align_up(off + (size_t)kT1Split * L.ldP * sizeof(double), kAlign);
     L.E = off;       off = align_up(off + (size_t)kESplitMax * L.N * L.N * sizeof(double), kAlign);
+    L.e_end = off;
     L.gacc = off;    off = align_up(off + (L.bwd ? kGradMax * sizeof(double) : 0), kAlign);
     L.occw = off;    off = align_up(off + (L.bwd ? (size_t)3 * L.N * sizeof(double) : 0), kAlign);
     L.kidx = off;    off = align_up(off + (L.bwd ? (size_t)L.N * sizeof(int) : 0), kAlign);
@@ -219,16 +233,13 @@ Layout make_layout(const xtc_problem* pb, int prec) {
     // packed operands: C and D of the two-body GEMM (8 components of ldL), or
     // w phi grad phi (3 of ldN) and K (3 of ldL) of the TC integrals
     L.cdw = std::max((size_t)8 * L.ldL, L.tc2 ? (size_t)3 * L.ldN + (size_t)3 * L.ldL : 0);
-    L.mpart = lp ? L.mslab * std::min<size_t>(kMSegGroupMax, std::max<size_t>(kMSegGroup, kMpartBudget / L.mslab))
-                 : std::min(kMpartF64Budget, (size_t)kTnSplitMax * std::max(L.ldP, L.tc2 ? L.ldN : 0) * L.ldP * sizeof(double));
     L.chunk0 = off;
-    L.fixed = off + L.mpart + (L.bwd ? gslab : 0) + 16 * kAlign;
+    L.fixed = off + (lp ? (size_t)kMSegGroup * L.mslab : 0) + (L.bwd ? gslab : 0) + 16 * kAlign;
     L.per_row = (size_t)L.nspin * (8 * sizeof(double) + (size_t)4 * L.ldP * sizeof(double));
     if (lp) L.per_row += (size_t)kOccSegMax * 3 * std::max(L.ldO, L.ldK8) * sizeof(double);
     if (lp) L.per_row += L.cdw * L.ns * L.es;
-    L.kpart_row = lp ? (size_t)L.nsegK * 3 * L.ldL * sizeof(float) : (size_t)kKSplitMax * 3 * L.ldP * sizeof(double);
-    L.kcap_max = lp ? (int)std::max<size_t>(kKpartQuant, kKpartBudget / L.kpart_row / kKpartQuant * kKpartQuant)
-                    : (int)(kKpartF64Budget / L.kpart_row);
+    L.kpart_row = lp ? (size_t)L.nsegK * 3 * L.ldL * sizeof(float) : 0;
+    L.kcap_max = lp ? (int)std::max<size_t>(kKpartQuant, kKpartBudget / L.kpart_row / kKpartQuant * kKpartQuant) : 0;
     if (L.tc2) L.per_row += (size_t)L.ldP * sizeof(double) + (lp ? 0 : (size_t)3 * L.ldN * sizeof(double));
     if (L.bwd)
         L.per_row += (size_t)(3 + L.nY) * L.ldP * sizeof(double) + (size_t)3 * L.N * L.nocc * sizeof(double) +
@@ -237,48 +248,58 @@ Layout make_layout(const xtc_problem* pb, int prec) {
     return L;
 }
 
-// Bytes of a workspace for chunks of `rows` rows (a multiple of kRowQuant).
+// Bytes that the buffers of a chunk of `rows` rows (a multiple of kRowQuant)
+// need, without the partials that only make it faster.
 size_t layout_bytes(const Layout& L, size_t rows) {
     return L.fixed + rows * L.per_row + std::min(rows, (size_t)L.kcap_max) * L.kpart_row;
 }
 
 // Chunk capacity that `bytes` allows (the inverse of layout_bytes), and the
-// offsets of the chunk buffers for it.
-void place_chunk(Layout& L, size_t bytes) {
+// offsets of the chunk buffers of a call on `rows` rows (at most the capacity).
+void place_chunk(Layout& L, size_t bytes, long rows) {
     long cap = 0;
     if (bytes > L.fixed) {
         const size_t b = bytes - L.fixed;
         const size_t c1 = b / (L.per_row + L.kpart_row);   // rows, if the partials cover all of them
-        if (c1 <= (size_t)L.kcap_max) cap = (long)c1;
-        else cap = (long)((b - (size_t)L.kcap_max * L.kpart_row) / L.per_row);
+        if (L.kpart_row == 0 || c1 <= (size_t)L.kcap_max) cap = (long)std::min<size_t>(c1, kMaxNg);
+        else cap = (long)std::min<size_t>((b - (size_t)L.kcap_max * L.kpart_row) / L.per_row, kMaxNg);
     }
     cap = cap / kRowQuant * kRowQuant;
     const long most = (long)align_up((size_t)L.Ng, kRowQuant);
     if (cap > most) cap = most;
     L.cap = (int)cap;
-    L.kcap = std::min(L.cap, L.kcap_max);
-    const bool lp = L.form != 0;
+    const size_t n = (size_t)std::min<long>(cap, (long)align_up((size_t)std::max(rows, 1L), kRowQuant));
+    L.crows = (int)n;
+    L.kcap = std::min(L.crows, L.kcap_max);
+    const bool lp = L.form != 0, b = L.bwd;
     const size_t gslab = (size_t)(L.ngp / 128) * kGradMax * sizeof(double);
     size_t off = L.chunk0;
-    L.S = off;       off = align_up(off + (size_t)L.nspin * cap * 8 * sizeof(double), kAlign);
-    L.D = off;       off = align_up(off + (size_t)L.nspin * 4 * cap * L.ldP * sizeof(double), kAlign);
-    L.Kpart = off;   off = align_up(off + (size_t)L.kcap * L.kpart_row, kAlign);
-    L.CDlp = off;    off = align_up(off + (lp ? L.cdw * L.ns * cap * L.es : 0), kAlign);
-    L.Mpart = off;   off = align_up(off + L.mpart, kAlign);
-    L.Kocc = off;    off = align_up(off + (lp ? (size_t)kOccSegMax * 3 * cap * std::max(L.ldO, L.ldK8) * sizeof(double) : 0),
-                                    kAlign);
-    const bool b = L.bwd;
-    L.Kc = off;      off = align_up(off + (b ? (size_t)3 * cap * L.ldP * sizeof(double) : 0), kAlign);
-    L.Y = off;       off = align_up(off + (b ? (size_t)L.nY * cap * L.ldP * sizeof(double) : 0), kAlign);
-    L.T = off;       off = align_up(off + (b ? (size_t)cap * 3 * L.N * L.nocc * sizeof(double) : 0), kAlign);
-    L.Wbar = off;    off = align_up(off + (b ? (size_t)cap * 3 * sizeof(double) : 0), kAlign);
-    L.gpart = off;   off = align_up(off + (b ? (size_t)((cap + 31) / 32) * gslab : 0), kAlign);
-    L.KbL = off;     off = align_up(off + (b && lp ? (size_t)7 * L.ns * cap * L.ldP * L.es : 0), kAlign);
-    L.Ftc = off;     off = align_up(off + (L.tc2 ? (size_t)cap * L.ldP * sizeof(double) : 0), kAlign);
-    L.Rg = off;      off = align_up(off + (L.tc2 && !lp ? (size_t)3 * cap * L.ldN * sizeof(double) : 0), kAlign);
-    L.end = off;
-    if (L.end > bytes) L.cap = 0;   // cannot happen by construction; refuse rather than overrun
+    L.Kc = off;      off = align_up(off + (b ? 3 * n * L.ldP * sizeof(double) : 0), kAlign);
+    L.Ftc = off;     off = align_up(off + (L.tc2 ? n * L.ldP * sizeof(double) : 0), kAlign);
+    L.S = off;       off = align_up(off + L.nspin * n * 8 * sizeof(double), kAlign);
+    L.D = off;       off = align_up(off + L.nspin * 4 * n * L.ldP * sizeof(double), kAlign);
+    L.Rg = off;      off = align_up(off + (L.tc2 && !lp ? 3 * n * L.ldN * sizeof(double) : 0), kAlign);
+    L.CDlp = off;    off = align_up(off + (lp ? L.cdw * L.ns * n * L.es : 0), kAlign);
+    L.scr = off;
+    L.Y = off;       off = align_up(off + (b ? L.nY * n * L.ldP * sizeof(double) : 0), kAlign);
+    L.T = off;       off = align_up(off + (b ? n * 3 * L.N * L.nocc * sizeof(double) : 0), kAlign);
+    L.Wbar = off;    off = align_up(off + (b ? n * 3 * sizeof(double) : 0), kAlign);
+    L.gpart = off;   off = align_up(off + (b ? (n + 31) / 32 * gslab : 0), kAlign);
+    L.KbL = off;     off = align_up(off + (b && lp ? 7 * L.ns * n * L.ldP * L.es : 0), kAlign);
+    L.end = bytes / kAlign * kAlign;
+    // the K build's partials (reduced forms: its own, then those of the occupied
+    // block) and the two-body products' least
+    const size_t build = lp ? std::max((size_t)L.kcap * L.kpart_row,
+                                       (size_t)kOccSegMax * 3 * n * std::max(L.ldO, L.ldK8) * sizeof(double)) : 0;
+    if (std::max({off, L.S + build, L.scr + (lp ? (size_t)kMSegGroup * L.mslab : 0)}) > L.end)
+        L.cap = 0;   // cannot happen by construction; refuse rather than overrun
 }
+
+// What the segment partials of a K build (from S on) and those of the two-body
+// products, the one-body sums and V2 (from scr on) may take of this call's
+// workspace.
+size_t build_bytes(const Layout& L) { return L.end - L.S; }
+size_t scratch_bytes(const Layout& L) { return L.end - L.scr; }
 
 // LDS of k_intermediates: the padded layout (16 bytes after every 4 entries)
 // when it fits, else the plain one (check_problem admits sizes up to the
@@ -415,7 +436,7 @@ xtc_status run_intermediates(const Layout& L, const xtc_problem* pb, const doubl
                              void* ws, hipStream_t st) {
     const int rows = g1 - g0;
     const double* rho_rows = at<double>(ws, L.rho) + (size_t)g0 * L.ldP;
-    const size_t dstride = (size_t)L.cap * L.ldP;
+    const size_t dstride = (size_t)L.crows * L.ldP;
     const size_t lds = lds_intermediates(L);
     const bool pad = intermediates_padded(L);
     const int nb = (L.N + kITile - 1) / kITile, tiles = nb * (nb + 1) / 2;
@@ -432,7 +453,7 @@ xtc_status run_intermediates(const Layout& L, const xtc_problem* pb, const doubl
     for (int sp = 0; sp < L.nspin; ++sp) {
         const OccList occ = make_occ(pb, sp);
         double* D = at<double>(ws, L.D) + (size_t)sp * 4 * dstride;
-        double* S = at<double>(ws, L.S) + (size_t)sp * L.cap * 8;
+        double* S = at<double>(ws, L.S) + (size_t)sp * L.crows * 8;
         hipLaunchKernelGGL((pad ? k_intermediates<true> : k_intermediates<false>), dim3(blocks), dim3(threads), lds, st,
                            rho_rows, K, rows, L.ldP, L.N, occ, D, dstride, S);
         xtc_status s;
@@ -506,7 +527,7 @@ void launch_build_lp_tile(const Layout& L, int coff, int ncol, int g0, int rows,
     const int n_ct = (ncol - coff + cols - 1) / cols;
     hipLaunchKernelGGL((k_build_K_lp<KIND, FORM, NC, NW, NB>), dim3(n_rt * n_ct * L.nsegK), dim3(64 * NW), 0, st,
                        at<d4>(ws, L.pos), at<void>(ws, L.rho_lp), (size_t)L.ngp * L.ldL, L.ldL, L.ngp, g0, rows, n_rt,
-                       L.segK, J, at<float>(ws, L.Kpart), L.kcap, coff, ncol, n_ct, L.nsegK);
+                       L.segK, J, at<float>(ws, L.S), L.kcap, coff, ncol, n_ct, L.nsegK);
 }
 
 // Variant (0: standard) for a last column tile of `cols` < standard columns, by
@@ -576,7 +597,7 @@ xtc_status build_lp_pieces(const Layout& L, int g0, int rows, const JasDev& J, d
         if ((s = launched(NC == 3 ? "build_K_lp" : "build_F_lp")) != XTC_OK) return s;
         const size_t n4 = (size_t)NC * nr * L.ldP / 4;   // k_reduce_K: four pairs per thread
         const unsigned blocks = (unsigned)std::min<size_t>((n4 + 255) / 256, 16384);
-        hipLaunchKernelGGL(k_reduce_K, dim3(blocks), dim3(256), 0, st, at<float>(ws, L.Kpart), L.nsegK, L.kcap,
+        hipLaunchKernelGGL(k_reduce_K, dim3(blocks), dim3(256), 0, st, at<float>(ws, L.S), L.nsegK, L.kcap,
                            L.ldL, nr, L.ldP, L.Npair, out + (size_t)r0 * L.ldP, rows, NC);
         if ((s = launched("reduce_K")) != XTC_OK) return s;
     }
@@ -598,8 +619,8 @@ xtc_status build_K_lp(const Layout& L, int g0, int rows, const JasDev& J, double
     // occupied-occupied pairs, written over the reduced-precision values:
     // segments of the sum over g' (enough, and evenly enough, to fill the chip),
     // FP64 partials, then a fixed-order reduction scattered into K
-    double* part = at<double>(ws, L.Kocc);
-    int nseg = 0, ldK = L.ldO;
+    double* part = at<double>(ws, L.S);
+    int nseg = 0, ldK = L.occ64.ncol;
     if (occ == kOccExact && L.i8ok && occ_i8_dscale(J) > 0.0) {
         ldK = L.ldK8;
         nseg = occ_i8_build(at<d4>(ws, L.pos), at<void>(ws, L.stg), L.i8, L.ngp, g0, rows, J,
@@ -611,10 +632,11 @@ xtc_status build_K_lp(const Layout& L, int g0, int rows, const JasDev& J, double
         }
         if ((s = launched("build_K_occ_i8")) != XTC_OK) return s;
     } else {
-        const KF64Plan p = kf64_segments(L.occ64, rows, L.ngp, kOccSegMax);
+        const size_t fit = build_bytes(L) / ((size_t)3 * rows * ldK * sizeof(double));
+        const KF64Plan p = kf64_segments(L.occ64, rows, L.ngp, (int)std::min<size_t>(kOccSegMax, fit));
         nseg = p.nseg;
         const hipError_t e = kf64_build(at<d4>(ws, L.pos), at<double>(ws, L.rho_occ), L.ldO, L.ngp, g0, rows, J, p,
-                                        part, L.ldO, st);
+                                        part, ldK, st);
         if (e != hipSuccess) return fail(XTC_E_HIP, "build_K_occ_f64: %s", hipGetErrorString(e));
     }
     const size_t nel = (size_t)3 * rows * L.nOP;
@@ -679,6 +701,12 @@ xtc_status reduce_parts(const float* part, int nparts, int ldC, int ldD, int pma
     return launched("reduce_M");
 }
 
+// Row segments per launch that `bytes` of partials allow (at least kMSegGroup).
+int m_seg_group(const Layout& L, size_t bytes) {
+    const size_t fit = std::min(bytes, kMpartBudget) / L.mslab;
+    return (int)std::min<size_t>(kMSegGroupMax, std::max<size_t>(kMSegGroup, fit));
+}
+
 // M (+)= C^T D over rows32 packed operand rows (reduced forms), launched in
 // groups of row segments of segM rows that fit the partial buffer: each group's FP32 partials
 // are summed in FP64 into M before the next group reuses the partial buffer.
@@ -686,8 +714,8 @@ xtc_status gemm_tn_grouped(const Layout& L, const char* C, int ldC, size_t c_spl
                            size_t d_split, int rows32, int pmax, int rmax, int ncomp, int cpw, double* M, int ldM,
                            int accumulate, void* ws, hipStream_t st) {
     xtc_status s;
-    float* part = at<float>(ws, L.Mpart);
-    const int group = (int)(L.mpart / L.mslab) * L.segM;
+    float* part = at<float>(ws, L.scr);
+    const int group = m_seg_group(L, scratch_bytes(L)) * L.segM;
     for (int q0 = 0; q0 < rows32; q0 += group) {
         const int nr = std::min(group, rows32 - q0);
         const size_t shift = (size_t)(q0 / 8) * 8 * L.es;   // bytes per packed row group and column
@@ -705,17 +733,17 @@ xtc_status gemm2b_lp(const Layout& L, const double* K, int g0, int rows, int acc
     xtc_status s;
     const int rows32 = (int)align_up((size_t)rows, kRowQuant);
     const int n8 = rows32 / 8;
-    const size_t split_stride = (size_t)L.cap * L.ldL;                 // elements of one split of one component
+    const size_t split_stride = (size_t)L.crows * L.ldL;                 // elements of one split of one component
     const size_t comp_bytes = (size_t)L.ns * split_stride * L.es;
     char* cd = at<char>(ws, L.CDlp);
     const double* rho_rows = at<double>(ws, L.rho) + (size_t)g0 * L.ldP;
-    const size_t ks = (size_t)rows * L.ldP, ds = (size_t)L.cap * L.ldP, comp = (size_t)L.ns * split_stride;
+    const size_t ks = (size_t)rows * L.ldP, ds = (size_t)L.crows * L.ldP, comp = (size_t)L.ns * split_stride;
     if ((s = pack_many(L.form, PackSrc{{rho_rows, K, K + ks, K + 2 * ks}}, 4, rows, L.ldP, L.ldP, n8, L.ldL, cd,
                        split_stride, comp, st)) != XTC_OK)
         return s;
     // one spin channel at a time: its D into the operand buffer, GEMM, reduction into M^s
     for (int sp = 0; sp < L.nspin; ++sp) {
-        const double* D = at<double>(ws, L.D) + (size_t)sp * 4 * L.cap * L.ldP;
+        const double* D = at<double>(ws, L.D) + (size_t)sp * 4 * L.crows * L.ldP;
         if ((s = pack_many(L.form, PackSrc{{D, D + ds, D + 2 * ds, D + 3 * ds}}, 4, rows, L.ldP, L.ldP, n8, L.ldL,
                            cd + 4 * comp_bytes, split_stride, comp, st)) != XTC_OK)
             return s;
@@ -757,11 +785,13 @@ xtc_status pack_kmajor_any(int form, const double* src, int nrows, int ld, void*
 // rows in 128 x 128 tiles; a product with fewer tiles than CUs is cut along
 // the rows until the chip is full (N=8 on 2000 points is one tile: 1565 us in
 // one piece), and the 64 x 64 tiles, whose waves share the rows, waste less on
-// the padding of a small matrix.
+// the padding of a small matrix.  A partial takes msize doubles; `bytes` are
+// there for all of them.
 struct TnF64Plan {
     int split, nseg, seg_rows;
 };
-TnF64Plan plan_tn_f64(int imax, int jmax, int ncomp, int rows, size_t max_parts) {
+TnF64Plan plan_tn_f64(int imax, int jmax, int ncomp, int rows, size_t msize, size_t bytes) {
+    const size_t max_parts = std::min(bytes, kMpartF64Budget) / (msize * sizeof(double));
     TnF64Plan best{1, 1, (int)align_up((size_t)rows, 16)};
     double best_cycles = 1e300;
     for (int split = 1; split <= 4; split += 3) {
@@ -788,11 +818,10 @@ TnF64Plan plan_tn_f64(int imax, int jmax, int ncomp, int rows, size_t max_parts)
 // [0, jmax) of M (leading dimension ldm, padded to whole 128 x 128 tiles).
 xtc_status gemm_tn_f64(const Layout& L, const TnOperand& A, const TnOperand& B, int ncomp, int rows, int imax, int jmax,
                        double* M, int ldm, int accumulate, void* ws, hipStream_t st) {
-    const size_t ld_rows = align_up((size_t)imax, 128);
-    const size_t msize = ld_rows * ldm;
-    const TnF64Plan p = plan_tn_f64(imax, jmax, ncomp, rows, L.mpart / (msize * sizeof(double)));
+    const size_t msize = align_up((size_t)imax, 128) * ldm;
+    const TnF64Plan p = plan_tn_f64(imax, jmax, ncomp, rows, msize, scratch_bytes(L));
     const bool parts = p.nseg > 1;
-    double* out = parts ? at<double>(ws, L.Mpart) : M;
+    double* out = parts ? at<double>(ws, L.scr) : M;
     const int tile = p.split == 1 ? 128 : 64;
     const int n_it = (imax + tile - 1) / tile, n_jt = (jmax + tile - 1) / tile;
     const dim3 grid(n_it * n_jt, p.nseg);
@@ -812,11 +841,15 @@ xtc_status gemm_tn_f64(const Layout& L, const TnOperand& A, const TnOperand& B, 
 }
 
 // One spin block of V2 from the accumulators, in slabs of rows P whose packed
-// sums fit the two-body partial buffer (free by then).
+// sums fit the scratch, or the one-body partials T1 and E (free at that time; at
+// least kT1Split rows) if those hold more.
 xtc_status finalize_V2(const Layout& L, const double* M1, const double* M2, double* V2, void* ws, hipStream_t st) {
     xtc_status s;
-    double* W = at<double>(ws, L.Mpart);
-    const int slab = (int)std::min<size_t>(L.ldP, L.mpart / (L.ldP * sizeof(double)) / 32 * 32);
+    const size_t t1e = L.e_end - L.T1;
+    const bool big = scratch_bytes(L) > t1e;
+    double* W = at<double>(ws, big ? L.scr : L.T1);
+    const size_t bytes = big ? scratch_bytes(L) : t1e;
+    const int slab = (int)std::min<size_t>(L.ldP, bytes / (L.ldP * sizeof(double)) / 32 * 32);
     for (int P0 = 0; P0 < L.Npair; P0 += slab) {
         const int np = std::min(slab, L.Npair - P0);
         hipLaunchKernelGGL(k_sym_sum, dim3(L.ldP / 32, (np + 31) / 32), dim3(256), 0, st, M1, M2, L.ldP, P0, W);
@@ -844,14 +877,57 @@ xtc_status xg_group(const __bf16* X, size_t a_comp, size_t a_split, int rows, co
     return launched("gemm_xg_bf16");
 }
 
+KF64Plan plan_build_f64(const Layout& L, int rows, size_t bytes) {
+    // the budget in whole rows of kKSplitMax segments of ldP columns
+    const size_t row = (size_t)kKSplitMax * 3 * L.ldP * sizeof(double);
+    const size_t most = kKpartF64Budget / row * kKSplitMax / rows;
+    return kf64_plan(L.Npair, L.ldP, rows, L.ngp, (int)std::min<size_t>(most, kKSplitMax), bytes);
+}
+
+// Row splits of the one-body term 1: kT1Split, more where few pairs leave the
+// chip idle, if `bytes` hold their partials.
+int t1_splits(const Layout& L, int rows, size_t bytes) {
+    const int blocks = (L.Npair + 255) / 256;
+    const int fit = (int)std::min<size_t>(kT1SplitMax, bytes / (L.ldP * sizeof(double)));
+    return std::min(rows, std::max(kT1Split, std::min({kT1SplitMax, 1024 / blocks, fit})));
+}
+
+// Bytes beyond layout_bytes with which every launch plan of a chunk of `rows`
+// rows has the partials it asks for.  (None for the adjoint's workspaces: their
+// own buffers leave the forward calls more than that.)
+size_t plan_extra(Layout L, int rows) {
+    if (L.bwd) return 0;
+    const size_t base = layout_bytes(L, align_up((size_t)rows, kRowQuant)), all = (size_t)1 << 62;
+    place_chunk(L, base, rows);
+    size_t scratch = (size_t)t1_splits(L, rows, all) * L.ldP * sizeof(double), build = 0;
+    if (scratch <= (size_t)kT1Split * L.ldP * sizeof(double)) scratch = 0;
+    if (L.form != 0) {
+        const int nseg = (rows + L.segM - 1) / L.segM;
+        scratch = std::max(scratch, std::min(nseg, m_seg_group(L, all)) * L.mslab);
+    } else {
+        const auto tn = [&](int imax, int ncomp) {
+            const size_t msize = align_up((size_t)imax, 128) * L.ldP;
+            const TnF64Plan p = plan_tn_f64(imax, L.Npair, ncomp, rows, msize, all);
+            if (p.nseg > 1) scratch = std::max(scratch, p.nseg * msize * sizeof(double));
+        };
+        tn(L.Npair, 4);
+        if (L.tc2) {
+            tn(L.Npair, 1);
+            tn(L.N * L.N, 3);
+        }
+        build = kf64_part_bytes(plan_build_f64(L, rows, all), rows);
+    }
+    const size_t s = scratch > scratch_bytes(L) ? scratch - scratch_bytes(L) : 0;
+    const size_t b = build > build_bytes(L) ? build - build_bytes(L) : 0;
+    return align_up(std::max(s, b), kAlign);
+}
+
 // The FP64 K build: in one piece, or split over g' where the grid is too small
 // to fill the chip, the FP64 partials then summed into K.
 xtc_status build_K_f64(const Layout& L, const JasDev& J, int g0, int rows, double* K, void* ws, hipStream_t st) {
-    // segments whose partials fit the buffer: kcap rows of kKSplitMax segments of ldP columns
-    const size_t fit = (size_t)L.kcap * kKSplitMax / rows;
-    const KF64Plan p = kf64_plan(L.Npair, L.ldP, rows, L.ngp, (int)std::min<size_t>(fit, kKSplitMax));
+    const KF64Plan p = plan_build_f64(L, rows, build_bytes(L));
     const bool parts = p.nseg > 1;
-    double* out = parts ? at<double>(ws, L.Kpart) : K;
+    double* out = parts ? at<double>(ws, L.S) : K;
     const hipError_t e = kf64_build(at<d4>(ws, L.pos), at<double>(ws, L.rho), L.ldP, L.ngp, g0, rows, J, p, out,
                                     parts ? p.ncol : L.ldP, st);
     if (e != hipSuccess) return fail(XTC_E_HIP, "build_K: %s", hipGetErrorString(e));
@@ -883,8 +959,8 @@ size_t xtc_workspace_size(const xtc_problem* pb, int32_t prec, int32_t chunk_row
         fail(XTC_E_ARG, "chunk_rows=%d outside [1,Ng]", chunk_rows);
         return 0;
     }
-    Layout L = make_layout(pb, prec);
-    return layout_bytes(L, align_up((size_t)chunk_rows, kRowQuant));
+    const Layout L = make_layout(pb, prec);
+    return layout_bytes(L, align_up((size_t)chunk_rows, kRowQuant)) + plan_extra(L, chunk_rows);
 }
 
 xtc_status xtc_prepare(const xtc_problem* pb, int32_t prec, int32_t chunk_rows, void* ws, size_t ws_bytes,
@@ -893,7 +969,7 @@ xtc_status xtc_prepare(const xtc_problem* pb, int32_t prec, int32_t chunk_rows, 
     if ((s = check_problem(pb)) != XTC_OK) return s;
     if ((s = check_prec(prec)) != XTC_OK) return s;
     Layout L = make_layout(pb, prec);
-    place_chunk(L, ws_bytes);
+    place_chunk(L, ws_bytes, chunk_rows);
     if ((s = check_ws(L, ws, ws_bytes)) != XTC_OK) return s;
     if (chunk_rows < 1 || chunk_rows > L.cap)
         return fail(XTC_E_WORKSPACE, "chunk_rows=%d exceeds the workspace capacity of %d rows", chunk_rows, L.cap);
@@ -917,7 +993,7 @@ xtc_status xtc_prepare(const xtc_problem* pb, int32_t prec, int32_t chunk_rows, 
         if ((s = launched("gather_occ")) != XTC_OK) return s;
         if (L.i8ok) {
             if ((s = fill(at<double>(ws, L.amax), (size_t)L.ldK8, st)) != XTC_OK) return s;
-            if (occ_i8_prepare(at<double>(ws, L.rho_occ), at<d4>(ws, L.pos), L.ngp, L.ldO, L.nOP, L.i8,
+            if (occ_i8_prepare(at<double>(ws, L.rho_occ), L.ngp, L.ldO, L.nOP, L.i8,
                                at<unsigned long long>(ws, L.amax), at<void>(ws, L.stg), st) != hipSuccess)
                 return fail(XTC_E_HIP, "occ_i8_prepare: %s", hipGetErrorString(hipGetLastError()));
         }
@@ -931,12 +1007,9 @@ xtc_status xtc_prepare(const xtc_problem* pb, int32_t prec, int32_t chunk_rows, 
                                  (size_t)L.ngp * L.ldP, st)) != XTC_OK)
             return s;
     }
-    // zero the accumulators of every spin channel and the chunk buffers of the
-    // intermediates (their padding columns are never written afterwards and
-    // must read as 0: the adjoint sums over all ldP columns of D)
+    // zero the accumulators of every spin channel
     if ((s = fill(at<double>(ws, L.M), (size_t)L.nspin * L.ldP * L.ldP, st)) != XTC_OK) return s;
     if ((s = fill(at<double>(ws, L.h1acc), (size_t)L.nspin * L.ldP, st)) != XTC_OK) return s;
-    if ((s = fill(at<double>(ws, L.D), (size_t)L.nspin * 4 * L.cap * L.ldP, st)) != XTC_OK) return s;
     if (L.tc2) {
         if ((s = fill(at<double>(ws, L.Atc), (size_t)L.ldP * L.ldP, st)) != XTC_OK) return s;
         if ((s = fill(at<double>(ws, L.Btc), (size_t)L.ldN * L.ldP, st)) != XTC_OK) return s;
@@ -958,7 +1031,7 @@ xtc_status xtc_build_K(const xtc_problem* pb, const xtc_jastrow* jas, int32_t g0
     if (!K) return fail(XTC_E_ARG, "K is NULL");
     if ((s = check_align(K, "K")) != XTC_OK) return s;
     Layout L = make_layout(pb, prec);
-    place_chunk(L, ws_bytes);
+    place_chunk(L, ws_bytes, (long)g1 - g0);
     if ((s = check_ws(L, ws, ws_bytes)) != XTC_OK) return s;
     if ((s = check_range(L, g0, g1)) != XTC_OK) return s;
     return build_K_any(L, J, g0, g1 - g0, K, occ, ws, (hipStream_t)stream);
@@ -974,7 +1047,7 @@ xtc_status xtc_contract_2body(const xtc_problem* pb, const double* K, int32_t g0
     if (flags & ~(XTC_RESET | XTC_FINALIZE)) return fail(XTC_E_ARG, "flags=%d unknown bits", flags);
     if ((flags & XTC_FINALIZE) && !V2) return fail(XTC_E_ARG, "V2 is NULL with XTC_FINALIZE");
     Layout L = make_layout(pb, prec);
-    place_chunk(L, ws_bytes);
+    place_chunk(L, ws_bytes, (long)g1 - g0);
     if ((s = check_ws(L, ws, ws_bytes)) != XTC_OK) return s;
     if ((s = check_range(L, g0, g1)) != XTC_OK) return s;
     hipStream_t st = (hipStream_t)stream;
@@ -984,7 +1057,7 @@ xtc_status xtc_contract_2body(const xtc_problem* pb, const double* K, int32_t g0
         if ((s = gemm2b_lp(L, K, g0, rows, (flags & XTC_RESET) ? 0 : 1, ws, st)) != XTC_OK) return s;
     } else {
         const double* rho_rows = at<double>(ws, L.rho) + (size_t)g0 * L.ldP;
-        const size_t dstride = (size_t)L.cap * L.ldP;
+        const size_t dstride = (size_t)L.crows * L.ldP;
         const TnOperand C{rho_rows, K, (size_t)rows * L.ldP, L.ldP};
         for (int sp = 0; sp < L.nspin; ++sp) {
             const double* D = at<double>(ws, L.D) + (size_t)sp * 4 * dstride;
@@ -1020,7 +1093,7 @@ xtc_status xtc_contract_1body_0body(const xtc_problem* pb, const double* K, int3
         return fail(XTC_E_ARG, "flags=%d unknown bits", flags);
     if ((flags & XTC_FINALIZE) && (!h1 || !E0)) return fail(XTC_E_ARG, "h1/E0 NULL with XTC_FINALIZE");
     Layout L = make_layout(pb, prec);
-    place_chunk(L, ws_bytes);
+    place_chunk(L, ws_bytes, (long)g1 - g0);
     if ((s = check_ws(L, ws, ws_bytes)) != XTC_OK) return s;
     if ((s = check_range(L, g0, g1)) != XTC_OK) return s;
     hipStream_t st = (hipStream_t)stream;
@@ -1029,10 +1102,9 @@ xtc_status xtc_contract_1body_0body(const xtc_problem* pb, const double* K, int3
     if (!(flags & XTC_REUSE_INTERMEDIATES) && (s = run_intermediates(L, pb, K, g0, g1, ws, st)) != XTC_OK) return s;
     const int rows = g1 - g0;
     const double* rho_rows = at<double>(ws, L.rho) + (size_t)g0 * L.ldP;
-    const size_t dstride = (size_t)L.cap * L.ldP;
-    // term 1: kT1Split row splits, more where few pairs leave the chip idle
-    const int t1_blocks = (L.Npair + 255) / 256;
-    const int nsplit_t1 = std::min(rows, std::max(kT1Split, std::min(kT1SplitMax, 1024 / t1_blocks)));
+    const size_t dstride = (size_t)L.crows * L.ldP;
+    const int nsplit_t1 = t1_splits(L, rows, scratch_bytes(L));
+    double* T1 = at<double>(ws, nsplit_t1 > kT1Split ? L.scr : L.T1);
     // exchange term: tiles of 64 outputs a side (16, 32 for smaller N), and row
     // splits until the four-wave workgroups fill the chip about twice
     const int tb = L.N <= 16 ? 1 : L.N <= 32 ? 2 : 4;
@@ -1040,13 +1112,13 @@ xtc_status xtc_contract_1body_0body(const xtc_problem* pb, const double* K, int3
     int nsplit_e = std::max(1, std::min(kESplitMax, 1024 / (n_t * n_t)));
     nsplit_e = std::min(nsplit_e, (rows + 7) / 8);
     const double* S = at<double>(ws, L.S);
-    const size_t sstride = (size_t)L.cap * 8;
+    const size_t sstride = (size_t)L.crows * 8;
     // per spin channel (T1 and E are scratch of one channel at a time)
     for (int sp = 0; sp < L.nspin; ++sp) {
         const double* Ds = at<double>(ws, L.D) + (size_t)sp * 4 * dstride;
         hipLaunchKernelGGL(k_onebody_T1, dim3((L.Npair + 255) / 256, nsplit_t1), dim3(256), 0, st, rho_rows, K, Ds,
                            dstride, S + sp * sstride, L.nspin == 2 ? S + (1 - sp) * sstride : nullptr, rows, L.ldP,
-                           L.Npair, at<double>(ws, L.T1));
+                           L.Npair, T1);
         if ((s = launched("onebody_T1")) != XTC_OK) return s;
         const auto exchange = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3(n_t * n_t, nsplit_e), dim3(256), 0, st, rho_rows, K, Ds, dstride, rows,
@@ -1057,7 +1129,7 @@ xtc_status xtc_contract_1body_0body(const xtc_problem* pb, const double* K, int3
         else exchange(k_onebody_E<4>);
         if ((s = launched("onebody_E")) != XTC_OK) return s;
         hipLaunchKernelGGL(k_onebody_accumulate, dim3((L.Npair + 31) / 32), dim3(256), 0, st,
-                           at<double>(ws, L.T1), nsplit_t1, at<double>(ws, L.E), nsplit_e, L.ldP, L.N,
+                           T1, nsplit_t1, at<double>(ws, L.E), nsplit_e, L.ldP, L.N,
                            at<double>(ws, L.h1acc) + (size_t)sp * L.ldP, (flags & XTC_RESET) ? 0 : 1);
         if ((s = launched("onebody_accumulate")) != XTC_OK) return s;
     }
@@ -1083,7 +1155,7 @@ xtc_status xtc_backward(const xtc_problem* pb, const xtc_jastrow* jas, int32_t p
     if (!gcoef) return fail(XTC_E_ARG, "gcoef is NULL");
     if (!std::isfinite(gE0)) return fail(XTC_E_ARG, "gE0 not finite");
     Layout L = make_layout(pb, prec);
-    place_chunk(L, ws_bytes);
+    place_chunk(L, ws_bytes, L.Ng);   // chunks of the capacity
     if ((s = check_ws(L, ws, ws_bytes)) != XTC_OK) return s;
     hipStream_t st = (hipStream_t)stream;
     const bool open = L.nspin == 2;
@@ -1122,7 +1194,7 @@ xtc_status xtc_backward(const xtc_problem* pb, const xtc_jastrow* jas, int32_t p
             (s = pack_kmajor_any(L.form, Gm[i], L.ldP, L.ldP, (void*)Gs[i], gsz, st)) != XTC_OK)
             return s;
     }
-    const size_t ystride = (size_t)L.cap * L.ldP;
+    const size_t ystride = (size_t)L.crows * L.ldP;
     double* Kc = at<double>(ws, L.Kc);
     double* Y = at<double>(ws, L.Y);
     const int n_jt_pi = L.ngp / 128;
@@ -1338,7 +1410,7 @@ xtc_status xtc_tc_2body(const xtc_problem* pb, const xtc_jastrow* jas, const dou
     if (flags & ~(XTC_RESET | XTC_FINALIZE)) return fail(XTC_E_ARG, "flags=%d unknown bits", flags);
     if ((flags & XTC_FINALIZE) && !K2) return fail(XTC_E_ARG, "K2 is NULL with XTC_FINALIZE");
     Layout L = make_layout(pb, prec);
-    place_chunk(L, ws_bytes);
+    place_chunk(L, ws_bytes, (long)g1 - g0);
     if ((s = check_ws(L, ws, ws_bytes)) != XTC_OK) return s;
     if ((s = check_range(L, g0, g1)) != XTC_OK) return s;
     hipStream_t st = (hipStream_t)stream;
@@ -1366,7 +1438,7 @@ xtc_status xtc_tc_2body(const xtc_problem* pb, const xtc_jastrow* jas, const dou
     double* Btc = at<double>(ws, L.Btc);
     if (L.form == 0) {
         double* Rg = at<double>(ws, L.Rg);
-        const size_t xs = (size_t)L.cap * L.ldN;
+        const size_t xs = (size_t)L.crows * L.ldN;
         const size_t nrg = (size_t)rows * L.ldN;
         hipLaunchKernelGGL(k_rhog, dim3((unsigned)std::min<size_t>((nrg + 255) / 256, 16384)), dim3(256), 0, st, pb->w,
                            pb->phi, dphi, L.N, L.Ng, g0, rows, L.ldN, xs, Rg);
@@ -1384,7 +1456,7 @@ xtc_status xtc_tc_2body(const xtc_problem* pb, const xtc_jastrow* jas, const dou
         const int rows32 = (int)align_up((size_t)rows, kRowQuant);
         const int n8 = rows32 / 8;
         char* cd = at<char>(ws, L.CDlp);
-        const size_t sL = (size_t)L.cap * L.ldL, sN = (size_t)L.cap * L.ldN;   // elements of one split
+        const size_t sL = (size_t)L.crows * L.ldL, sN = (size_t)L.crows * L.ldN;   // elements of one split
         const size_t cL = (size_t)L.ns * sL * L.es, cN = (size_t)L.ns * sN * L.es;   // bytes of one component
         if ((s = pack_any(L.form, rho_rows, rows, L.ldP, L.ldP, n8, L.ldL, cd, sL, st)) != XTC_OK) return s;
         if ((s = pack_any(L.form, F, rows, L.ldP, L.ldP, n8, L.ldL, cd + cL, sL, st)) != XTC_OK) return s;

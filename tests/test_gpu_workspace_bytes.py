@@ -1,0 +1,95 @@
+"""Passes in the smallest workspace that holds their chunk (the byte counts of
+test_workspace_bytes): the launch plans then have few or no segment partials,
+and the outputs agree with those of a workspace of xtc_workspace_size bytes to
+the rounding of the FP64 sums.  The workspace is filled with NaN first and a
+guard behind it has to stay as it was."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from paper_2304_07006_amd import inputs
+from test_workspace_bytes import BWD, TABLE, TC2
+
+pytestmark = pytest.mark.gpu
+
+# sums of at most 2000 terms in another order: 2000 x 1.1e-16 of the largest
+# magnitude, with a factor 5 for the products of two such sums
+TOL = 1e-12
+GUARD = 1 << 16
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    return torch
+
+
+def _problem(N, nocc, Ng, open_shell):
+    """The first N functions of a problem of whole centres, orthonormalised."""
+    nc = max(1, (N + 3) // 4)
+    p = inputs.make_problem(4 * nc, min(4 * nc, nocc), Ng, nc, "chain", "power16", seed=500 + N + Ng)
+    chi = p.chi[:N]
+    lam, U = np.linalg.eigh((chi * p.w) @ chi.T)
+    p.phi = np.ascontiguousarray((U * lam ** -0.5) @ U.T @ chi)
+    occ = np.arange(nocc, dtype=np.int32)
+    beta = np.where(occ < nocc - 1, 1.0, 0.0) if open_shell else None
+    return p, occ, (np.ones(nocc) if open_shell else None), beta
+
+
+def _guarded(torch, nbytes):
+    buf = torch.empty(nbytes + GUARD, dtype=torch.uint8, device="cuda")
+    buf.fill_(0xFF)
+    return buf, buf[:nbytes]
+
+
+def _close(a, b):
+    a, b = a.cpu().numpy(), b.cpu().numpy()
+    assert np.all(np.isfinite(b))
+    assert np.abs(a - b).max() <= TOL * max(1.0, np.abs(a).max())
+
+
+@pytest.mark.parametrize("N,nocc,Ng,chunk,prec,open_shell,nbytes", [t for t in TABLE if t[0] < 64])
+def test_smallest_workspace_gives_the_same_outputs(torch_cuda, N, nocc, Ng, chunk, prec, open_shell, nbytes):
+    from paper_2304_07006_amd import xtc
+    torch = torch_cuda
+    print(f"case: N={N} nocc={nocc} Ng={Ng} chunk={chunk} prec={prec:#x} open={open_shell} in {nbytes} bytes", flush=True)
+    p, occ, occ_n, occ_b = _problem(N, nocc, Ng, open_shell)
+    dp = xtc.device_problem(p.xyz, p.w, p.phi, occ, occ_n=occ_n, occ_n_beta=occ_b)
+    jas = xtc.make_jastrow(p.jastrow)
+    buf, ws = _guarded(torch, nbytes)
+    ref = xtc.Pass(dp, prec, chunk)
+    got = xtc.Pass(dp, prec, chunk)
+    got.ws = ws
+    for a, b in zip(ref.run(jas), got.run(jas)):
+        _close(a, b)
+    if prec & BWD:
+        G = torch.as_tensor(inputs.loss_weights(N, 7)[1]).cuda()
+        g = torch.empty(16, dtype=torch.float64, device="cuda")
+        coef = list(p.jastrow.coef)
+        xtc.xtc_prepare(dp, prec, chunk, ws)
+        xtc.xtc_backward(dp, xtc.power_jastrow(coef), prec, G, None, 1.0, g, ws)
+        _close(xtc.backward(dp, coef, G, None, 1.0, prec & ~BWD, chunk), g)
+    if prec & TC2:
+        rng = np.random.default_rng(3)
+        dphi = torch.as_tensor(rng.standard_normal((3, N, Ng))).cuda()
+        outs = []
+        for w in (ref.ws, ws):
+            K2 = torch.empty((N,) * 4, dtype=torch.float64, device="cuda")
+            xtc.xtc_prepare(dp, prec, chunk, w)
+            for g0 in range(0, Ng, chunk):
+                g1 = min(Ng, g0 + chunk)
+                K = got.K_view(g0, g1)
+                xtc.xtc_build_K(dp, jas, g0, g1, prec | xtc.XTC_K_REDUCED_OCC, K, w)
+                st = xtc.load().xtc_tc_2body(
+                    ctypes.byref(dp.c), ctypes.byref(jas), ctypes.c_void_p(dphi.data_ptr()),
+                    ctypes.c_void_p(K.data_ptr()), g0, g1, prec, xtc.XTC_FINALIZE if g1 == Ng else 0,
+                    ctypes.c_void_p(K2.data_ptr()), ctypes.c_void_p(w.data_ptr()), w.numel(),
+                    ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+                assert st == 0, xtc.last_error()
+            outs.append(K2)
+        _close(*outs)
+    torch.cuda.synchronize()
+    assert bool((buf[nbytes:] == 0xFF).all())
