@@ -267,7 +267,12 @@ xtc_status xtc_backward(const xtc_problem *pb, const xtc_jastrow *jas, int32_t p
  * small eigenvalues to high relative accuracy; S must be positive definite).
  * chi, phi: device [N][Ng]; w: device [Ng]; lambda: device [N] (eigenvalues
  * of S, unordered) or NULL.  Workspace of xtc_lowdin_workspace_size(N, Ng)
- * bytes, 256-byte aligned; no state is kept in it after the call.
+ * bytes, 256-byte aligned; no state is kept in it after the call.  The count
+ * includes up to 32 MiB that only make the call faster (N = 128 on 150 000
+ * points: 5.0 MiB without, 32.1 with them); a smaller workspace is taken, with
+ * longer segments of the overlap's sum and fewer sweeps per pass of the
+ * eigensolver, down to about 8 N'^2 (Ng / 4096 + 4) bytes, N' = N rounded up to 64
+ * (XTC_E_WORKSPACE below).
  * 1 <= N <= 256 and Ng >= 1 (XTC_E_ARG), Ng <= 2^28 (XTC_E_UNSUPPORTED).
  * Unlike the other calls it synchronises `stream` once, after the eigensolver,
  * to check it: XTC_E_ARG if the Jacobi sweeps did not converge or S is not

@@ -93,8 +93,10 @@ __global__ void k_syrk_reduce(const double* __restrict__ part, int nseg, int N, 
 // even, the extra index is a dummy) to the rows and the columns.  Sweeps continue
 // while the off-diagonal mass exceeds (1e-15)^2 of the diagonal mass, at most
 // max_sweeps (every thread takes the same decision).  On exit diag(S) holds the
-// eigenvalues; the rotations of every round (c, s, NaN-free) are left in rot
-// [sweep (N' - 1) + round][N'/2][2] for k_jacobi_vectors.
+// eigenvalues (and S the rotated matrix, for a further pass); the rotations of
+// every round (c, s, NaN-free) are left in rot [sweep (N' - 1) + round][N'/2][2]
+// for k_jacobi_vectors.  sweeps_out[1] = the sweeps of this pass, sweeps_out[0]
+// those of all (`more`: this pass continues an earlier one).
 // Bound by the latency of its rounds (N=128: 127 a sweep, each a pass over the
 // matrix between barriers), so the matrix stays in LDS where it fits (LDS =
 // true: N <= kJacobiLdsN, 8 N^2 bytes), a pass rotates rows and columns of a
@@ -106,7 +108,8 @@ constexpr int kJacobiThreads = 1024;
 constexpr int kJacobiLdsN = 140;
 template <bool LDS>
 __global__ __launch_bounds__(kJacobiThreads) void k_jacobi(double* __restrict__ S, int N, int max_sweeps,
-                                                           double* __restrict__ rot, int* __restrict__ sweeps_out) {
+                                                           int more, double* __restrict__ rot,
+                                                           int* __restrict__ sweeps_out) {
     extern __shared__ double lds[];
     __shared__ double cs[128][2];
     __shared__ int pq[128][2];
@@ -196,22 +199,26 @@ __global__ __launch_bounds__(kJacobiThreads) void k_jacobi(double* __restrict__ 
         }
     }
     if constexpr (LDS)
-        for (int i = tid; i < N; i += kJacobiThreads) S[(size_t)i * N + i] = A[i * N + i];
-    if (tid == 0) *sweeps_out = sweep;
+        for (int idx = tid; idx < N * N; idx += kJacobiThreads) S[idx] = A[idx];
+    if (tid == 0) {
+        sweeps_out[1] = sweep;
+        sweeps_out[0] = (more ? sweeps_out[0] : 0) + sweep;
+    }
 }
 
-// U <- I J_1 J_2 ... : the rotations of k_jacobi applied to the rows of the
-// identity, one wave per row (rows do not meet), the row in LDS and the
+// U <- I J_1 J_2 ... : the rotations of a pass of k_jacobi applied to the rows of
+// the identity, or with `more` of U, one wave per row (rows do not meet), the row in LDS and the
 // rotations of a round read one lane per pair.  The columns of U are the
 // eigenvectors.
 __global__ __launch_bounds__(64) void k_jacobi_vectors(const double* __restrict__ rot, const int* __restrict__ sweeps,
-                                                       int N, double* __restrict__ U) {
+                                                       int N, int more, double* __restrict__ U) {
     __shared__ double row[256];
     const int Np = N + (N & 1), half = Np / 2;
     const int k = blockIdx.x, lane = threadIdx.x;
-    for (int j = lane; j < N; j += 64) row[j] = j == k ? 1.0 : 0.0;
+    const int rounds = sweeps[1] * (Np - 1);
+    if (more && rounds == 0) return;
+    for (int j = lane; j < N; j += 64) row[j] = more ? U[(size_t)k * N + j] : j == k ? 1.0 : 0.0;
     __syncthreads();
-    const int rounds = *sweeps * (Np - 1);
     const double2* rt = (const double2*)rot;
     constexpr int kAhead = 4;                        // rounds of rotations in flight
     double2 next[kAhead][2];

@@ -1321,33 +1321,43 @@ xtc_status xtc_backward(const xtc_problem* pb, const xtc_jastrow* jas, int32_t p
 namespace {
 constexpr int kLowdinSeg = 4096;
 constexpr int kJacobiMaxSweeps = 40;
-// Points per partial of S: at most kLowdinSeg, and short enough that the tiles
-// of a mid-size grid fill the chip, while the partials stay within 32 MiB.
+// Bytes of S partials that shorter segments than kLowdinSeg may take.
 constexpr size_t kLowdinPartBudget = (size_t)32 << 20;
 struct LowdinLayout {
     int ldS, nseg, seg;
+    int pass_sweeps;     // Jacobi sweeps whose rotations fit where the partials were
     size_t part, S, U, X, rot, sweeps, status, total;
 };
-LowdinLayout lowdin_layout(int N, int Ng) {
+// full: segments short enough that the tiles of a mid-size grid fill the chip,
+// with partials of at most kLowdinPartBudget (or those of kLowdinSeg points each),
+// and room for the rotations of every sweep the eigensolver may take.  Otherwise
+// segments of kLowdinSeg points, and as many sweeps at a time as their partials
+// leave room for (at least one: 8 N' (N' - 1) bytes, N' = N rounded up to even).
+LowdinLayout lowdin_layout(int N, int Ng, bool full) {
     LowdinLayout L{};
     L.ldS = (int)align_up((size_t)N, 64);
     const size_t psize = (size_t)L.ldS * L.ldS * sizeof(double);
     const int want = (int)std::min<size_t>(256, kLowdinPartBudget / psize);
-    L.seg = std::min(kLowdinSeg, std::max(64, (int)align_up((size_t)((Ng + want - 1) / want), 16)));
+    L.seg = !full || Ng <= 128 ? kLowdinSeg
+                               : std::min(kLowdinSeg, std::max(64, (int)align_up((size_t)((Ng + want - 1) / want), 16)));
     L.nseg = (Ng + L.seg - 1) / L.seg;
-    // the rotations (c, s) of every round the eigensolver may take go where the
-    // partials were
-    const size_t rot = (size_t)kJacobiMaxSweeps * (N + 1) * ((N + 1) / 2) * 2 * sizeof(double);
+    const size_t Np = align_up((size_t)N, 2), sweep = (Np - 1) * (Np / 2) * 2 * sizeof(double);
     size_t off = 0;
     L.part = L.rot = off;
-    off = align_up(off + std::max((size_t)L.nseg * psize, rot), kAlign);
+    off = align_up(off + std::max(L.nseg * psize, full ? kJacobiMaxSweeps * sweep : 0), kAlign);
+    L.pass_sweeps = (int)std::min<size_t>(kJacobiMaxSweeps, off / sweep);
     L.S = off;      off = align_up(off + (size_t)N * N * sizeof(double), kAlign);
     L.U = off;      off = align_up(off + (size_t)N * N * sizeof(double), kAlign);
     L.X = off;      off = align_up(off + (size_t)N * N * sizeof(double), kAlign);
-    L.sweeps = off; off = align_up(off + sizeof(int), kAlign);
+    L.sweeps = off; off = align_up(off + 2 * sizeof(int), kAlign);
     L.status = off; off = align_up(off + 2 * sizeof(double), kAlign);
     L.total = off;
     return L;
+}
+// The full layout if `bytes` hold it, else the small one.
+LowdinLayout lowdin_layout_for(int N, int Ng, size_t bytes) {
+    const LowdinLayout L = lowdin_layout(N, Ng, true);
+    return L.total <= bytes ? L : lowdin_layout(N, Ng, false);
 }
 
 xtc_status check_lowdin_args(int N, int Ng, const double* chi, const double* w, const double* phi) {
@@ -1518,7 +1528,7 @@ size_t xtc_lowdin_workspace_size(int32_t N, int32_t Ng) {
         fail(Ng > kMaxNg ? XTC_E_UNSUPPORTED : XTC_E_ARG, "N=%d or Ng=%d out of range", N, Ng);
         return 0;
     }
-    return lowdin_layout(N, Ng).total;
+    return lowdin_layout(N, Ng, true).total;
 }
 
 xtc_status xtc_lowdin(int32_t N, int32_t Ng, const double* chi, const double* w, double* phi, double* lambda,
@@ -1527,7 +1537,7 @@ xtc_status xtc_lowdin(int32_t N, int32_t Ng, const double* chi, const double* w,
     if ((s = check_lowdin_args(N, Ng, chi, w, phi)) != XTC_OK) return s;
     if (!ws) return fail(XTC_E_WORKSPACE, "workspace is NULL");
     if ((uintptr_t)ws % kAlign) return fail(XTC_E_WORKSPACE, "workspace not 256-byte aligned");
-    const LowdinLayout L = lowdin_layout(N, Ng);
+    const LowdinLayout L = lowdin_layout_for(N, Ng, ws_bytes);
     if (ws_bytes < L.total) return fail(XTC_E_WORKSPACE, "workspace of %zu bytes < %zu", ws_bytes, L.total);
     return run_lowdin(L, N, Ng, chi, w, phi, lambda, ws, (hipStream_t)stream);
 }
@@ -1536,7 +1546,7 @@ xtc_status xtc_lowdin_noalloc(int32_t N, int32_t Ng, const double* chi, const do
                               double* lambda, void* stream) {
     xtc_status s;
     if ((s = check_lowdin_args(N, Ng, chi, w, phi)) != XTC_OK) return s;
-    const LowdinLayout L = lowdin_layout(N, Ng);
+    const LowdinLayout L = lowdin_layout_for(N, Ng, kNoAllocBytes);
     if (L.total > kNoAllocBytes)
         return fail(XTC_E_UNSUPPORTED, "N=%d, Ng=%d needs %zu bytes of scratch, above the %zu of the static array", N,
                     Ng, L.total, kNoAllocBytes);
@@ -1567,12 +1577,16 @@ xtc_status run_lowdin(const LowdinLayout& L, int N, int Ng, const double* chi, c
             return fail(XTC_E_HIP, "jacobi LDS attribute: %s", hipGetErrorString(e));
         }
     }
-    hipLaunchKernelGGL((lds ? k_jacobi<true> : k_jacobi<false>), dim3(1), dim3(kJacobiThreads), lds, st,
-                       at<double>(ws, L.S), N, kJacobiMaxSweeps, at<double>(ws, L.rot), at<int>(ws, L.sweeps));
-    if ((s = launched("jacobi")) != XTC_OK) return s;
-    hipLaunchKernelGGL(k_jacobi_vectors, dim3(N), dim3(64), 0, st, at<double>(ws, L.rot), at<int>(ws, L.sweeps), N,
-                       at<double>(ws, L.U));
-    if ((s = launched("jacobi_vectors")) != XTC_OK) return s;
+    // (a pass on a matrix that has converged changes nothing)
+    for (int done = 0; done < kJacobiMaxSweeps; done += L.pass_sweeps) {
+        hipLaunchKernelGGL((lds ? k_jacobi<true> : k_jacobi<false>), dim3(1), dim3(kJacobiThreads), lds, st,
+                           at<double>(ws, L.S), N, std::min(L.pass_sweeps, kJacobiMaxSweeps - done), done > 0 ? 1 : 0,
+                           at<double>(ws, L.rot), at<int>(ws, L.sweeps));
+        if ((s = launched("jacobi")) != XTC_OK) return s;
+        hipLaunchKernelGGL(k_jacobi_vectors, dim3(N), dim3(64), 0, st, at<double>(ws, L.rot), at<int>(ws, L.sweeps), N,
+                           done > 0 ? 1 : 0, at<double>(ws, L.U));
+        if ((s = launched("jacobi_vectors")) != XTC_OK) return s;
+    }
     // convergence and positive definiteness are checked before anything is
     // written to phi or lambda (one synchronisation of the stream)
     hipLaunchKernelGGL(k_lowdin_status, dim3(1), dim3(64), 0, st, at<double>(ws, L.S), N, at<int>(ws, L.sweeps),

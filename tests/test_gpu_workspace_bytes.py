@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 from paper_2304_07006_amd import inputs
-from test_workspace_bytes import BWD, TABLE, TC2
+from test_workspace_bytes import BWD, LOWDIN, TABLE, TC2
 
 pytestmark = pytest.mark.gpu
 
@@ -92,4 +92,28 @@ def test_smallest_workspace_gives_the_same_outputs(torch_cuda, N, nocc, Ng, chun
             outs.append(K2)
         _close(*outs)
     torch.cuda.synchronize()
+    assert bool((buf[nbytes:] == 0xFF).all())
+
+
+@pytest.mark.parametrize("N,Ng,nbytes", LOWDIN)
+def test_smallest_lowdin_workspace(torch_cuda, N, Ng, nbytes):
+    """Rotations of a few sweeps at a time (one for N=64 and 65: a pass per
+    sweep): against the oracle with the tolerance of the solver's other tests."""
+    from oracle import lowdin as ol
+    from paper_2304_07006_amd import xtc
+    torch = torch_cuda
+    print(f"case: lowdin N={N} Ng={Ng} in {nbytes} bytes", flush=True)
+    rng = np.random.default_rng(70 + N)
+    centres = inputs.chain_centres(max(1, (N + 3) // 4), rng)
+    xyz, w = inputs.sample_grid(centres, Ng, rng)
+    chi = np.ascontiguousarray(inputs.basis_values(xyz, centres, 4, rng)[0][:N])
+    phi_o, _, lam_o = ol.lowdin(chi, w)
+    buf, ws = _guarded(torch, nbytes)
+    chi_t, w_t = torch.as_tensor(chi).cuda(), torch.as_tensor(w).cuda()
+    phi, lam = torch.empty_like(chi_t), torch.empty(N, dtype=torch.float64, device="cuda")
+    xtc.xtc_lowdin(N, Ng, chi_t, w_t, phi, lam, ws)
+    eps = np.finfo(float).eps
+    tol = 50 * eps * lam_o.max() / lam_o.min() * max(1, N / 8)
+    assert np.abs(np.sort(lam.cpu().numpy()) - np.sort(lam_o)).max() < 50 * N * eps * lam_o.max()
+    assert np.abs(phi.cpu().numpy() - phi_o).max() < tol * max(1.0, np.abs(phi_o).max())
     assert bool((buf[nbytes:] == 0xFF).all())

@@ -36,6 +36,12 @@ TABLE = [
     (64, 8, 20000, 20000, xtc.XTC_FP64, False, 1791798272),
     (128, 16, 150000, 7500, xtc.XTC_BF16X3, False, 38388347904),
 ]
+# Loewdin: N, Ng, bytes
+LOWDIN = [
+    (1, 40, 34048), (3, 50, 34048), (8, 2000, 34816), (37, 1500, 66304),
+    (64, 700, 131584), (65, 2100, 233728), (128, 9000, 786944), (140, 3000, 766208),
+    (141, 3000, 773120), (256, 5000, 2621952),
+]
 
 
 @pytest.fixture(scope="module")
@@ -80,3 +86,12 @@ def test_partials_are_reserved_where_a_plan_uses_them(lib, N, nocc, Ng, chunk, p
     assert 0 < n <= nbytes + ((192 << 20) if prec in (xtc.XTC_FP64, xtc.XTC_FP64 | TC2) else 0)
     big = _problem(128, 16, 150000, False)
     assert lib.xtc_workspace_size(ctypes.byref(big), xtc.XTC_FP64, 7500) <= 12584135680
+
+
+@nodevice
+@pytest.mark.parametrize("N,Ng,nbytes", LOWDIN)
+def test_the_first_lowdin_byte_counts_are_accepted(lib, N, Ng, nbytes):
+    f, ws = ctypes.c_void_p(0x10000), ctypes.c_void_p(0x100000)
+    assert lib.xtc_lowdin(N, Ng, f, f, f, None, ws, nbytes, None) == xtc.XTC_E_HIP
+    assert lib.xtc_lowdin(N, Ng, f, f, f, None, ws, nbytes - 1, None) == xtc.XTC_E_WORKSPACE
+    assert nbytes <= lib.xtc_lowdin_workspace_size(N, Ng) <= nbytes + (32 << 20)
