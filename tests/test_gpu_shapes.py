@@ -25,6 +25,8 @@ def torch_cuda():
 
 # one orbital pair; one 64-tile and one more pair than it (N=11: 66); the 128 edge
 # (N=15: 120, N=16: 136); grids of one row tile, one row more, ragged chunks
+# (the sizes below are whole centres of four functions; one pair, N=11, N=15 and
+# other N between them run in test_gpu_odd_sizes.py)
 @pytest.mark.parametrize("N,nocc,Ng,chunk,centres", [
     (4, 1, 17, 17, 1), (8, 2, 64, 64, 2), (8, 2, 65, 33, 2), (8, 3, 1999, 1999, 2), (12, 3, 129, 97, 3),
     (16, 4, 1025, 1025, 4), (20, 5, 2047, 700, 5), (32, 6, 1500, 1500, 4), (40, 8, 4000, 4000, 5)])
