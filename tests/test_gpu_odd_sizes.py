@@ -147,6 +147,7 @@ class Plan(ctypes.Structure):
 
 def _plan(N, rows, Ng):
     """kf64_plan as xtc_build_K calls it with room for every partial."""
+    import torch  # noqa: F401  (its HIP runtime before the library's, so that the process has one)
     fn = xtc.load()._ZN3xtc9kf64_planEiiiiim
     fn.restype, fn.argtypes = Plan, [ctypes.c_int] * 5 + [ctypes.c_size_t]
     P = N * (N + 1) // 2
