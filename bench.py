@@ -63,8 +63,7 @@ def traffic_record(prec, workload, chunk):
     return e
 
 
-KBUILD_KERNELS = ("k_build_K_lp", "k_reduce_K", "k_build_K_occ_i8", "k_build_K_occ", "k_reduce_occ", "k_build_K_f64",
-                  "k_reduce_K_f64")
+KBUILD_KERNELS = ("k_build_K_lp", "k_reduce_K", "k_build_K_occ_i8", "k_reduce_occ", "k_build_K_f64", "k_reduce_K_f64")
 
 
 def traffic_from(fetch_dir, write_dir, workload, prec, chunk, path=None):
@@ -233,7 +232,9 @@ def kernel_rooflines(times, N, nocc, Ng, prec):
     and its useful rate is given beside it as an FP64-class rate."""
     P = N * (N + 1) // 2
     nOP = nocc * (nocc + 1) // 2
-    table = {"k_build_K_lp": (6 * Ng * Ng * P, PEAK[prec]), "k_build_K_f64": (6 * Ng * Ng * (P if prec == "fp64" else nOP), PEAK["fp64"]),
+    # (k_build_K_occ: the FP64 occupied block in the traces of earlier builds; it is k_build_K_f64 now)
+    table = {"k_build_K_lp": (6 * Ng * Ng * P, PEAK[prec]),
+             "k_build_K_f64": (6 * Ng * Ng * (P if prec == "fp64" else nOP), PEAK["fp64"]),
              "k_build_K_occ": (6 * Ng * Ng * nOP, PEAK["fp64"]),
              "k_build_K_occ_i8": (6 * Ng * Ng * occ_i8_columns(nocc) * I8_PRODUCTS, I8_PEAK),
              "k_gemm_tn_lds": (8 * Ng * P * P, PEAK[prec]), "k_gemm_tn_lp": (8 * Ng * P * P, PEAK[prec]),

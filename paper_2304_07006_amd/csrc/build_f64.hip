@@ -11,6 +11,11 @@ namespace {
 
 constexpr int kCus = 256;   // compute units of an MI355X (launch shapes only)
 
+// Most 16-column blocks per wave.  With eight, as with seven, one workgroup has a
+// CU to itself (at N=128 112 x 2 columns reach 60.8 TFLOP/s, 64 x 2 66.2), and
+// the cost below never takes eight.
+constexpr int kMaxBlocks = 7;
+
 // Workgroups of a shape that share a CU (24 nb accumulation registers and about
 // 110 others, of 512 per lane).
 int resident(int nb) { return nb >= 7 ? 1 : nb >= 3 ? 2 : 3; }
@@ -29,7 +34,7 @@ double step_cycles(int nb, int cw) {
 KF64Plan kf64_columns(int cols, int ld) {
     KF64Plan best{1, 2, 0, 1, 0};
     double best_cost = 1e300;
-    for (int nb = 1; nb <= 8; ++nb)
+    for (int nb = 1; nb <= kMaxBlocks; ++nb)
         for (int cw = 2; cw <= 4; cw += 2) {
             const int tile = 16 * nb * cw;
             const int ncol = (cols + tile - 1) / tile * tile;
@@ -79,7 +84,7 @@ KF64Plan kf64_segments(KF64Plan p, int rows, int ngp, int max_seg) {
 KF64Plan kf64_plan(int cols, int ld, int rows, int ngp, int max_seg, size_t max_bytes) {
     KF64Plan best{0, 0, 0, 0, 0};
     double best_cycles = 1e300;
-    for (int nb = 1; nb <= 8; ++nb)
+    for (int nb = 1; nb <= kMaxBlocks; ++nb)
         for (int cw = 2; cw <= 4; cw += 2) {
             const int tile = 16 * nb * cw;
             KF64Plan p{nb, cw, (cols + tile - 1) / tile * tile, 1, ngp};
@@ -123,7 +128,6 @@ hipError_t launch_nb(const d4* pos, const double* rho, int ld, int ngp, int g0, 
         case 5: return launch<KIND, 5, CW>(pos, rho, ld, ngp, g0, rows, J, p, out, ldo, st);
         case 6: return launch<KIND, 6, CW>(pos, rho, ld, ngp, g0, rows, J, p, out, ldo, st);
         case 7: return launch<KIND, 7, CW>(pos, rho, ld, ngp, g0, rows, J, p, out, ldo, st);
-        case 8: return launch<KIND, 8, CW>(pos, rho, ld, ngp, g0, rows, J, p, out, ldo, st);
         default: return hipErrorInvalidValue;
     }
 }

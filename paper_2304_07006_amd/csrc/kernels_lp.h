@@ -194,15 +194,11 @@ __global__ __launch_bounds__(256) void k_pack_rhog(const double* __restrict__ w,
 // u'(r)/r in FP32 for the reduced forms, from the hardware reciprocal and
 // reciprocal square root (about 1 ulp each; the split-BF16 operands carry
 // 2^-16 .. 2^-24 relative error, so IEEE division and square root would buy
-// nothing).  Exactly 0 at r^2 == 0.
-template <int KIND>
-__device__ __forceinline__ float du_over_r_fast(float r2, const JasDev& J);
-
-// The same without the r^2 == 0 branch, for d^x = (x - x') u'(r)/r: the caller
-// passes r^2 + kR2Floor, so the value stays finite at coincident points, where
-// the difference vector it multiplies is exactly zero (d^x = 0 exactly, as the
-// branch gives).  kR2Floor is far below every r^2 the grid produces between
-// distinct points (it moves a distance of 1e-6 bohr by 5e-19 relative).
+// nothing).  For d^x = (x - x') u'(r)/r the caller passes r^2 + kR2Floor, so the
+// value stays finite at coincident points, where the difference vector it
+// multiplies is exactly zero (d^x = 0 exactly).  kR2Floor is far below every r^2
+// the grid produces between distinct points (it moves a distance of 1e-6 bohr by
+// 5e-19 relative).
 constexpr float kR2Floor = 1e-30f;
 template <int KIND>
 __device__ __forceinline__ float du_over_r_nz(float r2, const JasDev& J) {
@@ -219,25 +215,6 @@ __device__ __forceinline__ float du_over_r_nz(float r2, const JasDev& J) {
         for (int k = 14; k >= 0; --k) p = fmaf(p, t, J.fdcoef[k]);
         return p * q * q * rs;
     }
-}
-
-template <int KIND>
-__device__ __forceinline__ float du_over_r_fast(float r2, const JasDev& J) {
-    const float rs = __builtin_amdgcn_rsqf(r2);      // 1/r
-    const float r = r2 * rs;
-    float f;
-    if constexpr (KIND == 0) {
-        const float t = __builtin_amdgcn_rcpf(fmaf(J.fb, r, 1.0f));
-        f = 0.5f * rs * t * t;
-    } else {
-        const float q = __builtin_amdgcn_rcpf(1.0f + r);
-        const float t = r * q;
-        float p = J.fdcoef[15];
-#pragma unroll
-        for (int k = 14; k >= 0; --k) p = fmaf(p, t, J.fdcoef[k]);
-        f = p * q * q * rs;
-    }
-    return r2 > 0.0f ? f : 0.0f;
 }
 
 // S = u'' + 2 u'/r + u'^2 in FP32 (the scalar kernel of the two-body TC
@@ -279,7 +256,6 @@ __device__ __forceinline__ float scalar_S_fast(float r2, const JasDev& J) {
 // the eight waves: generation is amortised over 512 columns.
 // NC = 1 builds F = S rho instead (the scalar kernel of the two-body TC
 // integrals, one component), with the same tiling.
-constexpr int kLpThreads = 512;
 // Tile variants: NW waves (4 NW grid rows) and NB 16-column blocks per wave.
 // The standard one is 8 waves of 4 blocks.  The one-component build (F)
 // generates as much per k-step as the three-component one but multiplies a

@@ -95,3 +95,14 @@ def test_integer_occupied_block_roofline():
     executed = 6 * 150000 ** 2 * 144 * 21
     assert abs(r["tflops"] - executed / t / 1e12) < 1e-9 and r["peak_tflops"] == 5000.0
     assert abs(r["useful_tflops"] - 6 * 150000 ** 2 * 136 / t / 1e12) < 1e-9
+
+
+def test_fp64_build_roofline_follows_the_form():
+    """k_build_K_f64 builds every pair in FP64 and the occupied pairs alone in
+    the reduced forms (XTC_K_OCC_FP64, or more than 144 of them)."""
+    P, nOP, t = 160 * 161 // 2, 210, 0.5
+    full = bench.kernel_rooflines({"k_build_K_f64": (10, t)}, 160, 20, 250000, "fp64")["k_build_K_f64"]
+    occ = bench.kernel_rooflines({"k_build_K_f64": (25, t)}, 160, 20, 250000, "bf16x3")["k_build_K_f64"]
+    assert abs(full["tflops"] - 6 * 250000 ** 2 * P / t / 1e12) < 1e-6
+    assert abs(occ["tflops"] - 6 * 250000 ** 2 * nOP / t / 1e12) < 1e-9
+    assert full["peak_tflops"] == occ["peak_tflops"] == 78.6
