@@ -28,7 +28,7 @@ struct OccList {
 // --------------------------------------------------------------------------
 // Intermediates.  One workgroup handles one grid point at a time (grid-stride
 // over the rows of the chunk).  The occupied columns (rho_rk, K_rk) of that
-// point are gathered into LDS as [nocc][N][4] (each thread's loads of up to
+// point are gathered into LDS as [nocc][N] of (rho, Kx, Ky, Kz) (each thread's loads of up to
 // kIGather entries issued together); each thread then owns kITile x kITile
 // output blocks (r-block <= s-block) of the upper triangle and accumulates
 // Zt and Z over k with register blocking.  The kernel waits on its loads and
@@ -37,37 +37,20 @@ struct OccList {
 // none left for K), in workgroups of as many waves as the blocks fill.  N=128,
 // 7500 rows: 1572 -> 1075 us (8 reads and writes of 62.5 M pair values: 4.0 GB);
 // N=160, 5000 rows: 2068 -> 1690; N=64, 20 000 rows: 1084 -> 575; N=8, 2000
-// rows: 33 -> 9 us.
+// rows: 33 -> 12 us.  (16 bytes of LDS padding after every four entries, which
+// 4 x 4 blocks needed, make no difference to 2 x 2 ones: N=128 1009 and 1005 us,
+// N=64 583 and 576.)
 // One spin channel s per launch: Z~ and Z carry the occupations n_k of that
 // spin, W and W~ those of the total density.  Per-point scalars
 // S[g] = (W~/2, W/2 (3), sum_k n_k A_kk, sum_k n_k B_kk (3)) feed the one-body
 // reduction.
 constexpr int kIGather = 4, kITile = 2;
-// Staged entry e of the intermediates' LDS array: 32 bytes, and with PAD 16
-// more bytes after every 4 entries, so that the 16 lanes of a b128 read phase
-// that fetch entries 4 apart (consecutive 4x4 tiles) hit distinct banks.
-// (Entries are then 16-byte aligned only: accessed as two 16-byte halves.)
-typedef double dpair __attribute__((ext_vector_type(2)));
-template <bool PAD> __device__ __forceinline__ dpair* staged(char* base, int e) {
-    return (dpair*)(base + 32 * e + (PAD ? 16 * (e >> 2) : 0));
-}
-template <bool PAD> __device__ __forceinline__ d4 ld_staged(char* base, int e) {
-    const dpair* p = staged<PAD>(base, e);
-    const dpair lo = p[0], hi = p[1];
-    return (d4){lo.x, lo.y, hi.x, hi.y};
-}
-template <bool PAD> __device__ __forceinline__ void st_staged(char* base, int e, const d4& v) {
-    dpair* p = staged<PAD>(base, e);
-    p[0] = (dpair){v.x, v.y};
-    p[1] = (dpair){v.z, v.w};
-}
-template <bool PAD>
 __global__ __launch_bounds__(256) void k_intermediates(const double* __restrict__ rho_rows,
                                                        const double* __restrict__ K, int rows,
                                                        int ldP, int N, OccList occ,
                                                        double* __restrict__ D, size_t dstride,
                                                        double* __restrict__ S) {
-    extern __shared__ __attribute__((aligned(16))) char lraw[];   // [nocc][N] of (rho, Kx, Ky, Kz)
+    extern __shared__ d4 lcol[];                   // [nocc][N] of (rho, Kx, Ky, Kz)
     __shared__ double sW[4];                       // Wx, Wy, Wz, Wt
     const int n = occ.n;
     const size_t kstride = (size_t)rows * ldP;
@@ -91,7 +74,7 @@ __global__ __launch_bounds__(256) void k_intermediates(const double* __restrict_
             }
 #pragma unroll
             for (int u = 0; u < kIGather; ++u)
-                if (base + nt * u < n * N) st_staged<PAD>(lraw, base + nt * u, e[u]);
+                if (base + nt * u < n * N) lcol[base + nt * u] = e[u];
         }
         __syncthreads();
         if (threadIdx.x < 64) {
@@ -103,7 +86,7 @@ __global__ __launch_bounds__(256) void k_intermediates(const double* __restrict_
             // w0..w2 = W/2, wt = W~/2
             double w0 = 0, w1 = 0, w2 = 0, wt = 0;
             for (int kk = 0; kk < n; ++kk) {           // every lane, same order
-                const d4 e = ld_staged<PAD>(lraw, kk * N + occ.k[kk]);
+                const d4 e = lcol[kk * N + occ.k[kk]];
                 const double nk = occ.wt[kk];
                 wt = fma(nk, e.x, wt); w0 = fma(nk, e.y, w0); w1 = fma(nk, e.z, w1); w2 = fma(nk, e.w, w2);
             }
@@ -111,10 +94,10 @@ __global__ __launch_bounds__(256) void k_intermediates(const double* __restrict_
             double a = 0, b0 = 0, b1 = 0, b2 = 0;
             for (int kk = lane; kk < n; kk += 64) {
                 const int k = occ.k[kk];
-                const d4 e = ld_staged<PAD>(lraw, kk * N + k);       // (rho_kk, K_kk)
+                const d4 e = lcol[kk * N + k];       // (rho_kk, K_kk)
                 double zt = 0, z0 = 0, z1 = 0, z2 = 0;
                 for (int ll = 0; ll < n; ++ll) {
-                    const d4 f = ld_staged<PAD>(lraw, ll * N + k);   // (rho_kl, K_kl)
+                    const d4 f = lcol[ll * N + k];   // (rho_kl, K_kl)
                     const double nl = occ.w[ll];
                     zt = fma(nl, f.y * f.y + f.z * f.z + f.w * f.w, zt);
                     z0 = fma(nl, 2.0 * f.x * f.y, z0); z1 = fma(nl, 2.0 * f.x * f.z, z1);
@@ -169,8 +152,8 @@ __global__ __launch_bounds__(256) void k_intermediates(const double* __restrict_
                 d4 a[kITile], b[kITile];
 #pragma unroll
                 for (int i = 0; i < kITile; ++i) {
-                    a[i] = ld_staged<PAD>(lraw, row + ri[i]);
-                    b[i] = nk * ld_staged<PAD>(lraw, row + sj[i]);
+                    a[i] = lcol[row + ri[i]];
+                    b[i] = nk * lcol[row + sj[i]];
                 }
 #pragma unroll
                 for (int i = 0; i < kITile; ++i)
@@ -416,7 +399,8 @@ __global__ __launch_bounds__(256, 2) void k_onebody_E(const double* __restrict__
 //   h1acc[pair(p,q)] (+)= sum_s T1[s][P] - 1/2 (sum_s E[s][p][q] + sum_s E[s][q][p])
 // 32 pairs per workgroup, the partials of each shared by kAccSlices threads
 // (slice t takes s = t, t + kAccSlices, ...) whose sums meet in a fixed order:
-// one thread per pair took 84-115 us of load latency, this takes 6-8.
+// one thread per pair took 84-115 us of load latency, this takes 9 (N=8), 15
+// (N=64) and 31 (N=128).
 constexpr int kAccSlices = 8;
 __global__ __launch_bounds__(256) void k_onebody_accumulate(const double* __restrict__ T1, int nsplit_t1,
                                                             const double* __restrict__ E, int nsplit_e, int ldP, int N,

@@ -4,7 +4,8 @@
 //   E  = E0 + 2 sum_c h1[c][c] + sum_{c,d} (2 (cc|dd) - (cd|dc))
 //   h[i][j] = h1[a_i][a_j] + sum_c (2 (a_i a_j|cc) - (a_i c|c a_j))
 //   V[i][j][k][l] = V2[a_i][a_j][a_k][a_l]
-// Every output element is one thread's fixed-order sum (deterministic).
+// Every element of h is one thread's fixed-order sum, E one workgroup's sum by a
+// fixed tree (deterministic).
 #pragma once
 #include "xtc_device.h"
 

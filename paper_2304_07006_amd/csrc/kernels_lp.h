@@ -908,8 +908,7 @@ __global__ void k_reduce_M(const float* __restrict__ part, int nseg, size_t sstr
 
 // --------------------------------------------------------------------------
 // Occupied-occupied pairs: colmap[j] = pair(occ[a], occ[b]) for a <= b (j in
-// row-major order of (a, b)); rho_occ = rho[g][colmap[j]] in column tiles of
-// tw pairs, tile-major ([ldO / tw][ngp][tw]), zero padded.
+// row-major order of (a, b)); rho_occ[g][j] = rho[g][colmap[j]], zero padded.
 __global__ void k_occ_pairs(OccList occ, int N, int* __restrict__ colmap, int ldO) {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= ldO) return;
@@ -938,14 +937,11 @@ __global__ void k_reduce_occ(const double* __restrict__ part, int nseg, int rows
 }
 
 __global__ void k_gather_occ(const double* __restrict__ rho, int ldP, int ngp, const int* __restrict__ colmap,
-                             int ldO, int tw, double* __restrict__ rho_occ) {
-    // column tiles of tw pairs, each [ngp][tw] contiguous: rho_occ[(j / tw) ngp tw + g tw + j % tw]
+                             int ldO, double* __restrict__ rho_occ) {
     const size_t n = (size_t)ngp * ldO;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        const int j = (int)(i % ldO);
-        const size_t g = i / ldO;
-        const int P = colmap[j];
-        rho_occ[((size_t)(j / tw) * ngp + g) * tw + j % tw] = P >= 0 ? rho[g * ldP + P] : 0.0;
+        const int P = colmap[i % ldO];
+        rho_occ[i] = P >= 0 ? rho[i / ldO * ldP + P] : 0.0;
     }
 }
 

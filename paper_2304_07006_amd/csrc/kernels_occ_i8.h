@@ -96,11 +96,10 @@ __device__ __forceinline__ void i8_digits4(const double (&h)[4], int (&w)[kI8Dig
 }
 
 // Per-pair largest |rho_P(g')| of the gathered occupied pairs
-// (rho_occ[(P / tw) ngp tw + g' tw + P % tw]), as the bit pattern of a
-// non-negative double (ordered like the value), max-combined into amax[P]
+// (rho_occ[g'][ldO]), as the bit pattern of a non-negative double (ordered like the value), max-combined into amax[P]
 // (zero before the first launch).  Grid: (column tiles of 16 pairs, row
 // chunks); 256 threads: 16 pairs x 16 rows at a time.
-__global__ __launch_bounds__(256) void k_occ_absmax(const double* __restrict__ rho_occ, int ngp, int tw, int nOP,
+__global__ __launch_bounds__(256) void k_occ_absmax(const double* __restrict__ rho_occ, int ngp, int ldO, int nOP,
                                                     int rows_per_block, unsigned long long* __restrict__ amax) {
     __shared__ double red[256];
     const int j = threadIdx.x & 15, rs = threadIdx.x >> 4;
@@ -108,8 +107,8 @@ __global__ __launch_bounds__(256) void k_occ_absmax(const double* __restrict__ r
     const int r0 = blockIdx.y * rows_per_block, r1 = min(ngp, r0 + rows_per_block);
     double m = 0.0;
     if (P < nOP) {
-        const double* col = rho_occ + (size_t)(P / tw) * ngp * tw + P % tw;
-        for (int g = r0 + rs; g < r1; g += 16) m = fmax(m, fabs(col[(size_t)g * tw]));
+        const double* col = rho_occ + P;
+        for (int g = r0 + rs; g < r1; g += 16) m = fmax(m, fabs(col[(size_t)g * ldO]));
     }
     red[threadIdx.x] = m;
     __syncthreads();
@@ -136,7 +135,7 @@ template <int CT> struct OccI8Stage {
 
 // Digits: one thread per (kb, column tile ct8 of nct8 = groups x CT, lane).
 template <int CT>
-__global__ __launch_bounds__(256) void k_occ_slice(const double* __restrict__ rho_occ, int ngp, int tw, int nOP,
+__global__ __launch_bounds__(256) void k_occ_slice(const double* __restrict__ rho_occ, int ngp, int ldO, int nOP,
                                                    int groups, const unsigned long long* __restrict__ amax,
                                                    char* __restrict__ stages) {
     typedef OccI8Stage<CT> S;
@@ -151,13 +150,13 @@ __global__ __launch_bounds__(256) void k_occ_slice(const double* __restrict__ rh
         const int gq = (int)kb * kI8Kb + 16 * (lane >> 4);
         const bool on = P < nOP;
         const double hs = on ? 2097152.0 / i8_scale(__builtin_bit_cast(double, amax[P])) : 0.0;
-        const double* col = rho_occ + (on ? (size_t)(P / tw) * ngp * tw + P % tw : 0);
+        const double* col = rho_occ + (on ? P : 0);
         int w[kI8Digits][4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             double h[4];
 #pragma unroll
-            for (int b = 0; b < 4; ++b) h[b] = (on ? col[(size_t)(gq + 4 * k + b) * tw] : 0.0) * hs;
+            for (int b = 0; b < 4; ++b) h[b] = (on ? col[(size_t)(gq + 4 * k + b) * ldO] : 0.0) * hs;
             int d[kI8Digits];
             i8_digits4(h, d);
 #pragma unroll

@@ -10,8 +10,7 @@ namespace xtc {
 
 // Column tiling of nOP occupied pairs: groups of ct 16-pair tiles (ct <= 9,
 // the accumulators one wave holds), nct8 = groups x ct tiles in all.  The
-// library uses the block for one group only (more regenerate d's digits
-// once per group and measured slower than the FP64 block).
+// library uses the block for one group only.
 struct OccI8Plan {
     int ct, groups, nct8;
 };
@@ -38,9 +37,9 @@ int balanced_segments(long tiles, long slots, int lo, int hi);
 size_t occ_i8_stage_bytes(const OccI8Plan& plan, int ngp);
 
 // Stage blocks of the occupied pairs' rho (nct8 x 16 pair columns, ngp
-// points) from rho_occ (column tiles of tw pairs, [ngp][tw] each).  amax (16 nct8 entries) must hold zeros; it receives
+// points) from rho_occ [ngp][ldO].  amax (16 nct8 entries) must hold zeros; it receives
 // the per-pair largest |rho|.  Returns the launch status.
-hipError_t occ_i8_prepare(const double* rho_occ, int ngp, int tw, int nOP, const OccI8Plan& plan,
+hipError_t occ_i8_prepare(const double* rho_occ, int ngp, int ldO, int nOP, const OccI8Plan& plan,
                           unsigned long long* amax, void* stages, hipStream_t st);
 
 // The block for rows [g0, g0 + rows): FP64 segment partials

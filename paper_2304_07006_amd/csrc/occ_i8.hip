@@ -64,35 +64,35 @@ size_t occ_i8_stage_bytes(const OccI8Plan& plan, int ngp) {
 namespace {
 
 template <int CT>
-hipError_t prepare_ct(const double* rho_occ, int ngp, int tw, int nOP, int groups,
+hipError_t prepare_ct(const double* rho_occ, int ngp, int ldO, int nOP, int groups,
                       const unsigned long long* amax, char* stages, hipStream_t st) {
     const size_t nd = (size_t)(ngp / kI8Kb) * groups * CT * 64;
     hipLaunchKernelGGL(k_occ_slice<CT>, dim3((unsigned)std::min<size_t>((nd + 255) / 256, 16384)), dim3(256), 0, st,
-                       rho_occ, ngp, tw, nOP, groups, amax, stages);
+                       rho_occ, ngp, ldO, nOP, groups, amax, stages);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t occ_i8_prepare(const double* rho_occ, int ngp, int tw, int nOP, const OccI8Plan& plan,
+hipError_t occ_i8_prepare(const double* rho_occ, int ngp, int ldO, int nOP, const OccI8Plan& plan,
                           unsigned long long* amax, void* stages, hipStream_t st) {
     const int chunks = std::max(1, std::min(64, ngp / 2048));
     const int per = (ngp + chunks - 1) / chunks;
     hipLaunchKernelGGL(k_occ_absmax, dim3((unsigned)((nOP + 15) / 16), (unsigned)chunks), dim3(256), 0, st, rho_occ,
-                       ngp, tw, nOP, per, amax);
+                       ngp, ldO, nOP, per, amax);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     char* sb = (char*)stages;
     switch (plan.ct) {
-        case 1: return prepare_ct<1>(rho_occ, ngp, tw, nOP, plan.groups, amax, sb, st);
-        case 2: return prepare_ct<2>(rho_occ, ngp, tw, nOP, plan.groups, amax, sb, st);
-        case 3: return prepare_ct<3>(rho_occ, ngp, tw, nOP, plan.groups, amax, sb, st);
-        case 4: return prepare_ct<4>(rho_occ, ngp, tw, nOP, plan.groups, amax, sb, st);
-        case 5: return prepare_ct<5>(rho_occ, ngp, tw, nOP, plan.groups, amax, sb, st);
-        case 6: return prepare_ct<6>(rho_occ, ngp, tw, nOP, plan.groups, amax, sb, st);
-        case 7: return prepare_ct<7>(rho_occ, ngp, tw, nOP, plan.groups, amax, sb, st);
-        case 8: return prepare_ct<8>(rho_occ, ngp, tw, nOP, plan.groups, amax, sb, st);
-        case 9: return prepare_ct<9>(rho_occ, ngp, tw, nOP, plan.groups, amax, sb, st);
+        case 1: return prepare_ct<1>(rho_occ, ngp, ldO, nOP, plan.groups, amax, sb, st);
+        case 2: return prepare_ct<2>(rho_occ, ngp, ldO, nOP, plan.groups, amax, sb, st);
+        case 3: return prepare_ct<3>(rho_occ, ngp, ldO, nOP, plan.groups, amax, sb, st);
+        case 4: return prepare_ct<4>(rho_occ, ngp, ldO, nOP, plan.groups, amax, sb, st);
+        case 5: return prepare_ct<5>(rho_occ, ngp, ldO, nOP, plan.groups, amax, sb, st);
+        case 6: return prepare_ct<6>(rho_occ, ngp, ldO, nOP, plan.groups, amax, sb, st);
+        case 7: return prepare_ct<7>(rho_occ, ngp, ldO, nOP, plan.groups, amax, sb, st);
+        case 8: return prepare_ct<8>(rho_occ, ngp, ldO, nOP, plan.groups, amax, sb, st);
+        case 9: return prepare_ct<9>(rho_occ, ngp, ldO, nOP, plan.groups, amax, sb, st);
         default: return hipErrorInvalidValue;
     }
 }

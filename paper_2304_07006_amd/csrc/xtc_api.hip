@@ -186,9 +186,11 @@ Layout make_layout(const xtc_problem* pb, int prec) {
     L.occ64 = kf64_columns(L.nOP, 1 << 30);
     L.ldO = (int)align_up((size_t)L.nOP, 16);
     L.i8 = occ_i8_plan(L.nOP);
-    // the integer block serves one column group (at most 144 occupied pairs):
-    // with two, each of them regenerates d's digits, and at N=160 with 20
-    // occupied orbitals it measured slower than the FP64 block
+    // the integer block serves one column group (at most 144 occupied pairs).
+    // Larger sets keep the FP64 block, the more accurate of the two (N=160, 20
+    // occupied, 250 000 points: E0 7e-15 Eh from the oracle against 4.7e-11),
+    // although two groups of the integer one would take less time (12 500 rows,
+    // 100 000 points: 18.6 against 26.9 ms Pade, 21.4 against 27.0 power)
     L.i8ok = L.ngp <= occ_i8_max_points(kOccSegMax) && L.i8.groups == 1;
     L.ldK8 = 16 * L.i8.nct8;
     L.segK = L.form == 1 ? kSegKF32 : kSegK;
@@ -300,18 +302,6 @@ void place_chunk(Layout& L, size_t bytes, long rows) {
 // workspace.
 size_t build_bytes(const Layout& L) { return L.end - L.S; }
 size_t scratch_bytes(const Layout& L) { return L.end - L.scr; }
-
-// LDS of k_intermediates: the padded layout (16 bytes after every 4 entries)
-// when it fits, else the plain one (check_problem admits sizes up to the
-// plain layout's limit)
-bool intermediates_padded(const Layout& L) {
-    const size_t e = (size_t)L.nocc * L.N;
-    return e * 32 + ((e + 3) / 4) * 16 <= kLdsMax - kLdsStaticReserve;
-}
-size_t lds_intermediates(const Layout& L) {
-    const size_t e = (size_t)L.nocc * L.N;
-    return e * 32 + (intermediates_padded(L) ? ((e + 3) / 4) * 16 : 0);
-}
 
 xtc_status check_problem(const xtc_problem* pb) {
     if (!pb) return fail(XTC_E_ARG, "problem is NULL");
@@ -437,14 +427,13 @@ xtc_status run_intermediates(const Layout& L, const xtc_problem* pb, const doubl
     const int rows = g1 - g0;
     const double* rho_rows = at<double>(ws, L.rho) + (size_t)g0 * L.ldP;
     const size_t dstride = (size_t)L.crows * L.ldP;
-    const size_t lds = lds_intermediates(L);
-    const bool pad = intermediates_padded(L);
+    const size_t lds = (size_t)L.nocc * L.N * 4 * sizeof(double);
     const int nb = (L.N + kITile - 1) / kITile, tiles = nb * (nb + 1) / 2;
     const int threads = std::min(256, (int)align_up((size_t)tiles, 64));
     const int blocks = std::min(rows, 16384);
-    const void* fn = pad ? (const void*)k_intermediates<true> : (const void*)k_intermediates<false>;
     if (lds > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        const hipError_t e = hipFuncSetAttribute((const void*)k_intermediates,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) {
             (void)hipGetLastError();   // do not leave the error for the caller's next HIP call
             return fail(XTC_E_HIP, "intermediates LDS attribute: %s", hipGetErrorString(e));
@@ -454,7 +443,7 @@ xtc_status run_intermediates(const Layout& L, const xtc_problem* pb, const doubl
         const OccList occ = make_occ(pb, sp);
         double* D = at<double>(ws, L.D) + (size_t)sp * 4 * dstride;
         double* S = at<double>(ws, L.S) + (size_t)sp * L.crows * 8;
-        hipLaunchKernelGGL((pad ? k_intermediates<true> : k_intermediates<false>), dim3(blocks), dim3(threads), lds, st,
+        hipLaunchKernelGGL(k_intermediates, dim3(blocks), dim3(threads), lds, st,
                            rho_rows, K, rows, L.ldP, L.N, occ, D, dstride, S);
         xtc_status s;
         if ((s = launched("intermediates")) != XTC_OK) return s;
@@ -989,7 +978,7 @@ xtc_status xtc_prepare(const xtc_problem* pb, int32_t prec, int32_t chunk_rows, 
                            at<int>(ws, L.colmap), L.ldO);
         if ((s = launched("occ_pairs")) != XTC_OK) return s;
         hipLaunchKernelGGL(k_gather_occ, dim3(4096), dim3(256), 0, st, at<double>(ws, L.rho), L.ldP, L.ngp,
-                           at<int>(ws, L.colmap), L.ldO, L.ldO, at<double>(ws, L.rho_occ));
+                           at<int>(ws, L.colmap), L.ldO, at<double>(ws, L.rho_occ));
         if ((s = launched("gather_occ")) != XTC_OK) return s;
         if (L.i8ok) {
             if ((s = fill(at<double>(ws, L.amax), (size_t)L.ldK8, st)) != XTC_OK) return s;
