@@ -478,13 +478,16 @@ __global__ __launch_bounds__(64 * NW) void k_build_K_lp(const d4* __restrict__ p
 #pragma unroll
                 for (int t = 0; t < Terms<FORM>::n; ++t)
 #pragma unroll
-                    for (int c0 = 0; c0 < NC; ++c0)
+                    for (int b0 = 0; b0 < NB; ++b0)
 #pragma unroll
-                        for (int b0 = 0; b0 < NB; ++b0) {
-                            // neighbours share an operand: 1.4% at N=128, where the
-                            // chip's power is the limit (115.5 -> 113.9 ms a chunk)
-                            const int c = t & 1 ? NC - 1 - c0 : c0;
-                            const int b = (c0 + t) & 1 ? NB - 1 - b0 : b0;
+                        for (int c0 = 0; c0 < NC; ++c0) {
+                            // column blocks outermost and both walked back and forth, so that
+                            // neighbours share an operand and the k-step's blocks of rho are needed
+                            // one after the other.  With the components outermost the workgroups
+                            // of an XCD drift apart on their strip: a call at N=128 then misses
+                            // 142-228 GB instead of 46-54 in L2, and takes 114.1 instead of 111.2 ms.
+                            const int b = t & 1 ? NB - 1 - b0 : b0;
+                            const int c = (b0 + t) & 1 ? NC - 1 - c0 : c0;
                             acc[c][h][b] = mma_bf16(av[c][Terms<FORM>::a[t]], bv[b][Terms<FORM>::b[t]], acc[c][h][b]);
                         }
             }
