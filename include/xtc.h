@@ -174,12 +174,15 @@ int32_t xtc_pair_ld(int32_t N);
  * grid chunks of at most `chunk_rows` rows (1 <= chunk_rows <= Ng).  Returns 0
  * for invalid arguments (message in xtc_last_error()).
  * In FP64 without XTC_WITH_BACKWARD the count includes the segment partials of
- * launches whose matrices are too small to fill the chip (at most 192 MiB; N = 8
- * on 2000 points: 10.4 MiB without and 18.2 with them, N = 64 on 20 000: 1709
- * and 1817, none from N = 96 on).  A call takes any workspace that holds its rows
- * without them (XTC_E_WORKSPACE below that): the partials it finds room for
- * then decide how its sums are split, which changes their speed and, in the
- * rounding of the FP64 sums, their last bits. */
+ * launches whose matrices are too small to fill the chip (at most 192 MiB for the
+ * K build and 192 for the products; N = 8 on 2000 points: 10.4 MiB without and
+ * 30.0 with them, N = 64 on 20 000: 1709 and 1953, none at N = 128).  A call takes
+ * any workspace that holds its rows without them (XTC_E_WORKSPACE below that):
+ * the partials it finds room for then decide how its sums are split, which
+ * changes their speed and, in the rounding of the FP64 sums, their last bits.
+ * In a workspace of this many bytes for its longest chunk, xtc_build_K of one
+ * chunk may run on another stream beside the contraction of another (with a K
+ * buffer each); a smaller one is for calls one after the other. */
 size_t xtc_workspace_size(const xtc_problem *pb, int32_t prec, int32_t chunk_rows);
 
 /* Prepare a pass: tabulate the weighted pair densities rho_pq(g) = w_g phi_p phi_q

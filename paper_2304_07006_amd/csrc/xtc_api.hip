@@ -28,14 +28,16 @@
 //   D      [4][crows][ldP] doubles    A, Bx, By, Bz of the chunk
 //   Rg     [3][crows][ldN] doubles    w phi grad phi (TC integrals, FP64 form)
 //   CDlp   [8][NS][crows/8][ldL][8]   C and D of the chunk, k8-packed (prec != FP64)
-//   scratch: everything from there to the end of the workspace.
+//   scratch: from there to the K build's part
+//   K build's part: the last kres bytes (a function of the workspace alone).
 // S and D are the only ones that outlive a call: xtc_contract_2body leaves them
 // to an xtc_contract_1body_0body with XTC_REUSE_INTERMEDIATES on the same rows,
-// with no call in between.  The K build therefore takes its segment partials
-// (Kpart [nsegK][3][kcap][ldL] f32, or FP64 ones, and those of the occupied
-// block) from S to the end; the two-body products (Mpart: [group][4][ldL][ldL]
-// f32, or FP64 ones), term 1 of the one-body sum and V2's packed sums take the
-// scratch; and the adjoint, which has no two-body products, keeps
+// with no call in between.  The K build keeps its segment partials (Kpart
+// [nsegK][3][kcap][ldL] f32, then those of the occupied block; or FP64 ones) in
+// its own part, so that it may run beside the contraction of another chunk.  The
+// two-body products' partials (Mpart: [group][4][ldL][ldL] f32, or FP64 ones),
+// those of term 1 of the one-body sum and V2's packed sums take the scratch; and
+// the adjoint, which has no two-body products, keeps
 //   Y [7][crows][ldP], T [crows][3][N][nocc], Wbar [crows][3],
 //   gpart [ceil(crows/32) * ngp/128][16], KbL [7][NS][crows * ldP] (split operands
 //   of the chunk, in rhoR's two layouts)
@@ -160,12 +162,22 @@ struct Layout {
     int kcap;            // rows of the K-build partial buffer: min(crows, kcap_max)
     size_t mslab;        // bytes of the two-body partials of one segM-row segment
     size_t cdw;          // packed operand elements per row and split (CDlp)
-    size_t Kc, Ftc, S, D, Rg, CDlp, scr, Y, T, Wbar, gpart, KbL, end;
+    size_t ek;           // most bytes of K-build partials that a plan asks for (FP64)
+    size_t kres;         // bytes of the K build's part
+    size_t Kc, Ftc, S, D, Rg, CDlp, scr, Y, T, Wbar, gpart, KbL, kpart, end;
 };
 
 int form_of(int prec) {
     prec &= 0xF;
     return prec == XTC_FP32 ? 1 : prec == XTC_BF16X3 ? 3 : prec == XTC_BF16X6 ? 6 : 0;
+}
+
+// The FP64 K build's plan for `rows` rows with `bytes` of partials.
+KF64Plan plan_build_f64(const Layout& L, int rows, size_t bytes) {
+    // the budget in whole rows of kKSplitMax segments of ldP columns
+    const size_t row = (size_t)kKSplitMax * 3 * L.ldP * sizeof(double);
+    const size_t most = kKpartF64Budget / row * kKSplitMax / rows;
+    return kf64_plan(L.Npair, L.ldP, rows, L.ngp, (int)std::min<size_t>(most, kKSplitMax), bytes);
 }
 
 Layout make_layout(const xtc_problem* pb, int prec) {
@@ -247,6 +259,9 @@ Layout make_layout(const xtc_problem* pb, int prec) {
         L.per_row += (size_t)(3 + L.nY) * L.ldP * sizeof(double) + (size_t)3 * L.N * L.nocc * sizeof(double) +
                      3 * sizeof(double) + (gslab + 31) / 32 + (lp ? (size_t)7 * L.ns * L.ldP * L.es : 0);
     L.cap = 0;
+    // (calls of fewer rows split their sums as far as that goes)
+    for (int rows = L.Ng; !lp && (rows == L.Ng || rows >= 256); rows /= 2)
+        L.ek = std::max(L.ek, align_up(kf64_part_bytes(plan_build_f64(L, rows, (size_t)1 << 62), rows), kAlign));
     return L;
 }
 
@@ -256,52 +271,64 @@ size_t layout_bytes(const Layout& L, size_t rows) {
     return L.fixed + rows * L.per_row + std::min(rows, (size_t)L.kcap_max) * L.kpart_row;
 }
 
-// Chunk capacity that `bytes` allows (the inverse of layout_bytes), and the
-// offsets of the chunk buffers of a call on `rows` rows (at most the capacity).
-void place_chunk(Layout& L, size_t bytes, long rows) {
-    long cap = 0;
-    if (bytes > L.fixed) {
-        const size_t b = bytes - L.fixed;
-        const size_t c1 = b / (L.per_row + L.kpart_row);   // rows, if the partials cover all of them
-        if (L.kpart_row == 0 || c1 <= (size_t)L.kcap_max) cap = (long)std::min<size_t>(c1, kMaxNg);
-        else cap = (long)std::min<size_t>((b - (size_t)L.kcap_max * L.kpart_row) / L.per_row, kMaxNg);
-    }
-    cap = cap / kRowQuant * kRowQuant;
-    const long most = (long)align_up((size_t)L.Ng, kRowQuant);
-    if (cap > most) cap = most;
-    L.cap = (int)cap;
-    const size_t n = (size_t)std::min<long>(cap, (long)align_up((size_t)std::max(rows, 1L), kRowQuant));
-    L.crows = (int)n;
-    L.kcap = std::min(L.crows, L.kcap_max);
-    const bool lp = L.form != 0, b = L.bwd;
-    const size_t gslab = (size_t)(L.ngp / 128) * kGradMax * sizeof(double);
-    size_t off = L.chunk0;
-    L.Kc = off;      off = align_up(off + (b ? 3 * n * L.ldP * sizeof(double) : 0), kAlign);
-    L.Ftc = off;     off = align_up(off + (L.tc2 ? n * L.ldP * sizeof(double) : 0), kAlign);
-    L.S = off;       off = align_up(off + L.nspin * n * 8 * sizeof(double), kAlign);
-    L.D = off;       off = align_up(off + L.nspin * 4 * n * L.ldP * sizeof(double), kAlign);
-    L.Rg = off;      off = align_up(off + (L.tc2 && !lp ? 3 * n * L.ldN * sizeof(double) : 0), kAlign);
-    L.CDlp = off;    off = align_up(off + (lp ? L.cdw * L.ns * n * L.es : 0), kAlign);
-    L.scr = off;
-    L.Y = off;       off = align_up(off + (b ? L.nY * n * L.ldP * sizeof(double) : 0), kAlign);
-    L.T = off;       off = align_up(off + (b ? n * 3 * L.N * L.nocc * sizeof(double) : 0), kAlign);
-    L.Wbar = off;    off = align_up(off + (b ? n * 3 * sizeof(double) : 0), kAlign);
-    L.gpart = off;   off = align_up(off + (b ? (n + 31) / 32 * gslab : 0), kAlign);
-    L.KbL = off;     off = align_up(off + (b && lp ? 7 * L.ns * n * L.ldP * L.es : 0), kAlign);
-    L.end = bytes / kAlign * kAlign;
-    // the K build's partials (reduced forms: its own, then those of the occupied
-    // block) and the two-body products' least
-    const size_t build = lp ? std::max((size_t)L.kcap * L.kpart_row,
-                                       (size_t)kOccSegMax * 3 * n * std::max(L.ldO, L.ldK8) * sizeof(double)) : 0;
-    if (std::max({off, L.S + build, L.scr + (lp ? (size_t)kMSegGroup * L.mslab : 0)}) > L.end)
-        L.cap = 0;   // cannot happen by construction; refuse rather than overrun
+// Chunk capacity that `bytes` allows (the inverse of layout_bytes).
+long chunk_capacity(const Layout& L, size_t bytes) {
+    if (bytes <= L.fixed) return 0;
+    const size_t b = bytes - L.fixed;
+    size_t cap = b / (L.per_row + L.kpart_row);            // rows, if the partials cover all of them
+    if (L.kpart_row > 0 && cap > (size_t)L.kcap_max) cap = (b - (size_t)L.kcap_max * L.kpart_row) / L.per_row;
+    return std::min((long)std::min<size_t>(cap, kMaxNg) / kRowQuant * kRowQuant,
+                    (long)align_up((size_t)L.Ng, kRowQuant));
 }
 
-// What the segment partials of a K build (from S on) and those of the two-body
-// products, the one-body sums and V2 (from scr on) may take of this call's
-// workspace.
-size_t build_bytes(const Layout& L) { return L.end - L.S; }
-size_t scratch_bytes(const Layout& L) { return L.end - L.scr; }
+// The capacity, and the offsets of the chunk buffers of a call on `rows` rows (at
+// most the capacity).
+void place_chunk(Layout& L, size_t bytes, long rows) {
+    const bool lp = L.form != 0, b = L.bwd;
+    const size_t gslab = (size_t)(L.ngp / 128) * kGradMax * sizeof(double);
+    L.cap = (int)chunk_capacity(L, bytes);
+    L.end = bytes / kAlign * kAlign;
+    const auto place = [&](size_t n) {
+        size_t off = L.chunk0;
+        L.Kc = off;      off = align_up(off + (b ? 3 * n * L.ldP * sizeof(double) : 0), kAlign);
+        L.Ftc = off;     off = align_up(off + (L.tc2 ? n * L.ldP * sizeof(double) : 0), kAlign);
+        L.S = off;       off = align_up(off + L.nspin * n * 8 * sizeof(double), kAlign);
+        L.D = off;       off = align_up(off + L.nspin * 4 * n * L.ldP * sizeof(double), kAlign);
+        L.Rg = off;      off = align_up(off + (L.tc2 && !lp ? 3 * n * L.ldN * sizeof(double) : 0), kAlign);
+        L.CDlp = off;    off = align_up(off + (lp ? L.cdw * L.ns * n * L.es : 0), kAlign);
+        L.scr = off;
+        L.Y = off;       off = align_up(off + (b ? L.nY * n * L.ldP * sizeof(double) : 0), kAlign);
+        L.T = off;       off = align_up(off + (b ? n * 3 * L.N * L.nocc * sizeof(double) : 0), kAlign);
+        L.Wbar = off;    off = align_up(off + (b ? n * 3 * sizeof(double) : 0), kAlign);
+        L.gpart = off;   off = align_up(off + (b ? (n + 31) / 32 * gslab : 0), kAlign);
+        L.KbL = off;     off = align_up(off + (b && lp ? 7 * L.ns * n * L.ldP * L.es : 0), kAlign);
+        return off;
+    };
+    // the K build's part.  Reduced forms: its partials for a chunk of the capacity,
+    // and those of the occupied block after them in time.  FP64: what plans ask for,
+    // if the call's rows fit beside it; with the adjoint's buffers half of those,
+    // which are dead while K is built.
+    const size_t cap = (size_t)L.cap, full = place(cap);
+    if (lp)
+        L.kres = align_up(std::max(std::min(cap, (size_t)L.kcap_max) * L.kpart_row,
+                                   (size_t)kOccSegMax * 3 * cap * std::max(L.ldO, L.ldK8) * sizeof(double)), kAlign);
+    else if (b)
+        L.kres = std::min(L.ek, (L.end > L.scr ? L.end - L.scr : 0) / 2 / kAlign * kAlign);
+    else
+        L.kres = bytes > L.ek && rows <= chunk_capacity(L, bytes - L.ek) ? L.ek : 0;
+    if (std::max(full, L.scr + (lp ? (size_t)kMSegGroup * L.mslab : 0)) + (lp ? L.kres : 0) > L.end)
+        L.cap = 0;   // cannot happen by construction; refuse rather than overrun
+    const size_t n = std::min(cap, align_up((size_t)std::max(rows, 1L), kRowQuant));
+    place(n);
+    L.crows = (int)n;
+    L.kcap = std::min(L.crows, L.kcap_max);
+    L.kpart = L.end - L.kres;
+}
+
+// Bytes for the segment partials of a K build (from kpart on), and for those of
+// the two-body products, the one-body sums and V2 (from scr on).
+size_t build_bytes(const Layout& L) { return L.kres; }
+size_t scratch_bytes(const Layout& L) { return L.kpart - L.scr; }
 
 xtc_status check_problem(const xtc_problem* pb) {
     if (!pb) return fail(XTC_E_ARG, "problem is NULL");
@@ -516,7 +543,7 @@ void launch_build_lp_tile(const Layout& L, int coff, int ncol, int g0, int rows,
     const int n_ct = (ncol - coff + cols - 1) / cols;
     hipLaunchKernelGGL((k_build_K_lp<KIND, FORM, NC, NW, NB>), dim3(n_rt * n_ct * L.nsegK), dim3(64 * NW), 0, st,
                        at<d4>(ws, L.pos), at<void>(ws, L.rho_lp), (size_t)L.ngp * L.ldL, L.ldL, L.ngp, g0, rows, n_rt,
-                       L.segK, J, at<float>(ws, L.S), L.kcap, coff, ncol, n_ct, L.nsegK);
+                       L.segK, J, at<float>(ws, L.kpart), L.kcap, coff, ncol, n_ct, L.nsegK);
 }
 
 // Variant (0: standard) for a last column tile of `cols` < standard columns, by
@@ -586,7 +613,7 @@ xtc_status build_lp_pieces(const Layout& L, int g0, int rows, const JasDev& J, d
         if ((s = launched(NC == 3 ? "build_K_lp" : "build_F_lp")) != XTC_OK) return s;
         const size_t n4 = (size_t)NC * nr * L.ldP / 4;   // k_reduce_K: four pairs per thread
         const unsigned blocks = (unsigned)std::min<size_t>((n4 + 255) / 256, 16384);
-        hipLaunchKernelGGL(k_reduce_K, dim3(blocks), dim3(256), 0, st, at<float>(ws, L.S), L.nsegK, L.kcap,
+        hipLaunchKernelGGL(k_reduce_K, dim3(blocks), dim3(256), 0, st, at<float>(ws, L.kpart), L.nsegK, L.kcap,
                            L.ldL, nr, L.ldP, L.Npair, out + (size_t)r0 * L.ldP, rows, NC);
         if ((s = launched("reduce_K")) != XTC_OK) return s;
     }
@@ -608,7 +635,7 @@ xtc_status build_K_lp(const Layout& L, int g0, int rows, const JasDev& J, double
     // occupied-occupied pairs, written over the reduced-precision values:
     // segments of the sum over g' (enough, and evenly enough, to fill the chip),
     // FP64 partials, then a fixed-order reduction scattered into K
-    double* part = at<double>(ws, L.S);
+    double* part = at<double>(ws, L.kpart);
     int nseg = 0, ldK = L.occ64.ncol;
     if (occ == kOccExact && L.i8ok && occ_i8_dscale(J) > 0.0) {
         ldK = L.ldK8;
@@ -866,13 +893,6 @@ xtc_status xg_group(const __bf16* X, size_t a_comp, size_t a_split, int rows, co
     return launched("gemm_xg_bf16");
 }
 
-KF64Plan plan_build_f64(const Layout& L, int rows, size_t bytes) {
-    // the budget in whole rows of kKSplitMax segments of ldP columns
-    const size_t row = (size_t)kKSplitMax * 3 * L.ldP * sizeof(double);
-    const size_t most = kKpartF64Budget / row * kKSplitMax / rows;
-    return kf64_plan(L.Npair, L.ldP, rows, L.ngp, (int)std::min<size_t>(most, kKSplitMax), bytes);
-}
-
 // Row splits of the one-body term 1: kT1Split, more where few pairs leave the
 // chip idle, if `bytes` hold their partials.
 int t1_splits(const Layout& L, int rows, size_t bytes) {
@@ -881,34 +901,32 @@ int t1_splits(const Layout& L, int rows, size_t bytes) {
     return std::min(rows, std::max(kT1Split, std::min({kT1SplitMax, 1024 / blocks, fit})));
 }
 
-// Bytes beyond layout_bytes with which every launch plan of a chunk of `rows`
-// rows has the partials it asks for.  (None for the adjoint's workspaces: their
+// Bytes beyond layout_bytes with which the launch plans of chunks of `rows` rows
+// have the partials they ask for.  (None for the adjoint's workspaces: their
 // own buffers leave the forward calls more than that.)
 size_t plan_extra(Layout L, int rows) {
     if (L.bwd) return 0;
-    const size_t base = layout_bytes(L, align_up((size_t)rows, kRowQuant)), all = (size_t)1 << 62;
-    place_chunk(L, base, rows);
-    size_t scratch = (size_t)t1_splits(L, rows, all) * L.ldP * sizeof(double), build = 0;
-    if (scratch <= (size_t)kT1Split * L.ldP * sizeof(double)) scratch = 0;
+    const size_t all = (size_t)1 << 62;
+    place_chunk(L, layout_bytes(L, align_up((size_t)rows, kRowQuant)), rows);
+    const size_t have = L.end - (L.form != 0 ? L.kres : 0) - L.scr;
+    size_t need = (size_t)t1_splits(L, rows, all) * L.ldP * sizeof(double);
+    if (need <= (size_t)kT1Split * L.ldP * sizeof(double)) need = 0;
     if (L.form != 0) {
         const int nseg = (rows + L.segM - 1) / L.segM;
-        scratch = std::max(scratch, std::min(nseg, m_seg_group(L, all)) * L.mslab);
+        need = std::max(need, std::min(nseg, m_seg_group(L, all)) * L.mslab);
     } else {
         const auto tn = [&](int imax, int ncomp) {
             const size_t msize = align_up((size_t)imax, 128) * L.ldP;
             const TnF64Plan p = plan_tn_f64(imax, L.Npair, ncomp, rows, msize, all);
-            if (p.nseg > 1) scratch = std::max(scratch, p.nseg * msize * sizeof(double));
+            if (p.nseg > 1) need = std::max(need, p.nseg * msize * sizeof(double));
         };
         tn(L.Npair, 4);
         if (L.tc2) {
             tn(L.Npair, 1);
             tn(L.N * L.N, 3);
         }
-        build = kf64_part_bytes(plan_build_f64(L, rows, all), rows);
     }
-    const size_t s = scratch > scratch_bytes(L) ? scratch - scratch_bytes(L) : 0;
-    const size_t b = build > build_bytes(L) ? build - build_bytes(L) : 0;
-    return align_up(std::max(s, b), kAlign);
+    return align_up(need > have ? need - have : 0, kAlign) + L.ek;
 }
 
 // The FP64 K build: in one piece, or split over g' where the grid is too small
@@ -916,7 +934,7 @@ size_t plan_extra(Layout L, int rows) {
 xtc_status build_K_f64(const Layout& L, const JasDev& J, int g0, int rows, double* K, void* ws, hipStream_t st) {
     const KF64Plan p = plan_build_f64(L, rows, build_bytes(L));
     const bool parts = p.nseg > 1;
-    double* out = parts ? at<double>(ws, L.S) : K;
+    double* out = parts ? at<double>(ws, L.kpart) : K;
     const hipError_t e = kf64_build(at<d4>(ws, L.pos), at<double>(ws, L.rho), L.ldP, L.ngp, g0, rows, J, p, out,
                                     parts ? p.ncol : L.ldP, st);
     if (e != hipSuccess) return fail(XTC_E_HIP, "build_K: %s", hipGetErrorString(e));

@@ -117,3 +117,41 @@ def test_smallest_lowdin_workspace(torch_cuda, N, Ng, nbytes):
     assert np.abs(np.sort(lam.cpu().numpy()) - np.sort(lam_o)).max() < 50 * N * eps * lam_o.max()
     assert np.abs(phi.cpu().numpy() - phi_o).max() < tol * max(1.0, np.abs(phi_o).max())
     assert bool((buf[nbytes:] == 0xFF).all())
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3"])
+@pytest.mark.parametrize("N,nocc,Ng,chunk", [(8, 2, 2000, 512), (24, 6, 3000, 800), (40, 17, 2600, 700)])
+def test_next_K_build_beside_the_contraction(torch_cuda, N, nocc, Ng, chunk, prec):
+    """K of chunk c + 1 built on a second stream while chunk c is contracted, on
+    one workspace and two K buffers (ragged last chunk): the K build's partials
+    have a part of the workspace of their own, so the outputs are those of the
+    pass on one stream, bit for bit."""
+    from paper_2304_07006_amd import xtc
+    torch = torch_cuda
+    print(f"case: K build beside the contraction N={N} Ng={Ng} chunk={chunk} {prec}", flush=True)
+    p, occ, _, _ = _problem(N, nocc, Ng, False)
+    dp = xtc.device_problem(p.xyz, p.w, p.phi, occ)
+    jas = xtc.make_jastrow(p.jastrow)
+    ref = [t.clone() for t in xtc.Pass(dp, xtc.PRECISIONS[prec], chunk).run(jas)]
+    ps = xtc.Pass(dp, xtc.PRECISIONS[prec], chunk)
+    K2 = torch.empty_like(ps.K)
+    for _ in range(3):
+        build, contract = torch.cuda.Stream(), torch.cuda.Stream()
+        torch.cuda.synchronize()
+        xtc.xtc_prepare(dp, ps.prec, ps.chunk, ps.ws, build)
+        ch = ps.chunks()
+        free = [None, None]
+        for i, (g0, g1) in enumerate(ch):
+            n = 3 * (g1 - g0) * ps.ldP
+            K = (ps.K, K2)[i % 2].view(-1)[:n].view(3, g1 - g0, ps.ldP)
+            if free[i % 2] is not None:
+                build.wait_event(free[i % 2])
+            xtc.xtc_build_K(dp, jas, g0, g1, ps.prec, K, ps.ws, build)
+            contract.wait_event(build.record_event())
+            flags = (xtc.XTC_RESET if i == 0 else 0) | (xtc.XTC_FINALIZE if i == len(ch) - 1 else 0)
+            xtc.xtc_contract_2body(dp, K, g0, g1, ps.prec, flags, ps.V2, ps.ws, contract)
+            xtc.xtc_contract_1body_0body(dp, K, g0, g1, ps.prec, flags, ps.h1, ps.E0, ps.ws, contract)
+            free[i % 2] = contract.record_event()
+        torch.cuda.synchronize()
+        for a, b in zip(ref, (ps.V2, ps.h1, ps.E0)):
+            assert torch.equal(a, b)
