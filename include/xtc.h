@@ -176,7 +176,7 @@ int32_t xtc_pair_ld(int32_t N);
  * In FP64 without XTC_WITH_BACKWARD the count includes the segment partials of
  * launches whose matrices are too small to fill the chip (at most 192 MiB for the
  * K build and 192 for the products; N = 8 on 2000 points: 10.4 MiB without and
- * 30.0 with them, N = 64 on 20 000: 1709 and 1953, none at N = 128).  A call takes
+ * 39.6 with them, N = 64 on 20 000: 1709 and 2009, none at N = 128).  A call takes
  * any workspace that holds its rows without them (XTC_E_WORKSPACE below that):
  * the partials it finds room for then decide how its sums are split, which
  * changes their speed and, in the rounding of the FP64 sums, their last bits.

@@ -162,7 +162,6 @@ struct Layout {
     int kcap;            // rows of the K-build partial buffer: min(crows, kcap_max)
     size_t mslab;        // bytes of the two-body partials of one segM-row segment
     size_t cdw;          // packed operand elements per row and split (CDlp)
-    size_t ek;           // most bytes of K-build partials that a plan asks for (FP64)
     size_t kres;         // bytes of the K build's part
     size_t Kc, Ftc, S, D, Rg, CDlp, scr, Y, T, Wbar, gpart, KbL, kpart, end;
 };
@@ -259,10 +258,25 @@ Layout make_layout(const xtc_problem* pb, int prec) {
         L.per_row += (size_t)(3 + L.nY) * L.ldP * sizeof(double) + (size_t)3 * L.N * L.nocc * sizeof(double) +
                      3 * sizeof(double) + (gslab + 31) / 32 + (lp ? (size_t)7 * L.ns * L.ldP * L.es : 0);
     L.cap = 0;
-    // (calls of fewer rows split their sums as far as that goes)
-    for (int rows = L.Ng; !lp && (rows == L.Ng || rows >= 256); rows /= 2)
-        L.ek = std::max(L.ek, align_up(kf64_part_bytes(plan_build_f64(L, rows, (size_t)1 << 62), rows), kAlign));
     return L;
+}
+
+// Most bytes of K-build partials that FP64 plans of 512 rows and more ask for
+// (fewer rows split their sums as far as that goes): the largest over rows a
+// factor 0.7 apart, and 1.3 of that for those between them.  A function of N and
+// Ng alone, for every call on a workspace; the plans take 3 us each, so a thread
+// keeps its last result (passes of eight 190-row chunks at N=12: 426 -> 391 us).
+size_t most_build_partials(const Layout& L) {
+    thread_local int last_N = 0, last_Ng = 0;
+    thread_local size_t last = 0;
+    if (L.N == last_N && L.Ng == last_Ng) return last;
+    size_t most = 0;
+    for (double rows = L.Ng; rows == L.Ng || rows >= 512; rows *= 0.7)
+        most = std::max(most, kf64_part_bytes(plan_build_f64(L, (int)rows, (size_t)1 << 62), (int)rows));
+    last = align_up(std::min(most + most / 10 * 3, kKpartF64Budget), kAlign);
+    last_N = L.N;
+    last_Ng = L.Ng;
+    return last;
 }
 
 // Bytes that the buffers of a chunk of `rows` rows (a multiple of kRowQuant)
@@ -313,9 +327,9 @@ void place_chunk(Layout& L, size_t bytes, long rows) {
         L.kres = align_up(std::max(std::min(cap, (size_t)L.kcap_max) * L.kpart_row,
                                    (size_t)kOccSegMax * 3 * cap * std::max(L.ldO, L.ldK8) * sizeof(double)), kAlign);
     else if (b)
-        L.kres = std::min(L.ek, (L.end > L.scr ? L.end - L.scr : 0) / 2 / kAlign * kAlign);
-    else
-        L.kres = bytes > L.ek && rows <= chunk_capacity(L, bytes - L.ek) ? L.ek : 0;
+        L.kres = std::min(most_build_partials(L), (L.end > L.scr ? L.end - L.scr : 0) / 2 / kAlign * kAlign);
+    else if (const size_t k = most_build_partials(L))
+        L.kres = bytes > k && rows <= chunk_capacity(L, bytes - k) ? k : 0;
     if (std::max(full, L.scr + (lp ? (size_t)kMSegGroup * L.mslab : 0)) + (lp ? L.kres : 0) > L.end)
         L.cap = 0;   // cannot happen by construction; refuse rather than overrun
     const size_t n = std::min(cap, align_up((size_t)std::max(rows, 1L), kRowQuant));
@@ -926,7 +940,7 @@ size_t plan_extra(Layout L, int rows) {
             tn(L.N * L.N, 3);
         }
     }
-    return align_up(need > have ? need - have : 0, kAlign) + L.ek;
+    return align_up(need > have ? need - have : 0, kAlign) + (L.form != 0 ? 0 : most_build_partials(L));
 }
 
 // The FP64 K build: in one piece, or split over g' where the grid is too small
@@ -976,7 +990,7 @@ xtc_status xtc_prepare(const xtc_problem* pb, int32_t prec, int32_t chunk_rows, 
     if ((s = check_problem(pb)) != XTC_OK) return s;
     if ((s = check_prec(prec)) != XTC_OK) return s;
     Layout L = make_layout(pb, prec);
-    place_chunk(L, ws_bytes, chunk_rows);
+    L.cap = (int)chunk_capacity(L, ws_bytes);
     if ((s = check_ws(L, ws, ws_bytes)) != XTC_OK) return s;
     if (chunk_rows < 1 || chunk_rows > L.cap)
         return fail(XTC_E_WORKSPACE, "chunk_rows=%d exceeds the workspace capacity of %d rows", chunk_rows, L.cap);
@@ -1164,6 +1178,10 @@ xtc_status xtc_backward(const xtc_problem* pb, const xtc_jastrow* jas, int32_t p
     Layout L = make_layout(pb, prec);
     place_chunk(L, ws_bytes, L.Ng);   // chunks of the capacity
     if ((s = check_ws(L, ws, ws_bytes)) != XTC_OK) return s;
+    if (L.form == 0) {                // nothing of a chunk but Kc is live while its K is built
+        L.kpart = L.S;
+        L.kres = L.end - L.S;
+    }
     hipStream_t st = (hipStream_t)stream;
     const bool open = L.nspin == 2;
     const OccList occ = make_occ(pb, 0);
